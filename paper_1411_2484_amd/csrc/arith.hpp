@@ -26,12 +26,24 @@ namespace dev {
 
 // ---- skip generator mod 2^31 - 1 (eq. (5), width 32) ----------------------
 
-// x y mod (2^31 - 1) for x, y in [1, 2^31 - 2]: fold the 62-bit product.
+// One skip step left unreduced: v' = a v mod p up to one subtraction of p,
+// for v < 2^32 nonzero mod p.  With the doubled multiplier the product's high
+// word is (a v) >> 31 and its low word is twice (a v) mod 2^31, so the
+// Mersenne fold needs no mask and no funnel shift.  v' = (low half) + (high
+// word) <= p + 2a < 2p, and v' is never 0 or p.
+__device__ __forceinline__ uint32_t step_p31(uint32_t v) {
+  static_assert(2ull * kA32 < kP32, "the doubled multiplier keeps v' below 2p");
+  const uint64_t t = (uint64_t)v * (2u * kA32);
+  return ((uint32_t)t >> 1) + (uint32_t)(t >> 32);
+}
+
+// v mod p for v < 2p, v != p: subtract p once when v > p.
+__device__ __forceinline__ uint32_t fold_p31(uint32_t v) { return min(v, v - kP32); }
+
+// x y mod (2^31 - 1) for x, y in [1, 2^31 - 2] (the same fold, y doubled here).
 __device__ __forceinline__ uint32_t mulmod_p31(uint32_t x, uint32_t y) {
-  uint64_t t = (uint64_t)x * y;
-  uint32_t v = ((uint32_t)t & 0x7fffffffu) + (uint32_t)(t >> 31);
-  uint32_t w = v - 0x7fffffffu;
-  return min(v, w);  // v < 2p, v != p: subtract p once when v > p
+  const uint64_t t = (uint64_t)x * (y + y);
+  return fold_p31(((uint32_t)t >> 1) + (uint32_t)(t >> 32));
 }
 
 __device__ __forceinline__ uint32_t powmod_p31(uint32_t b, uint64_t e) {
@@ -72,6 +84,19 @@ __device__ __forceinline__ uint32_t mont32(uint32_t x, uint32_t y, uint32_t n, u
   return r + (borrow ? n : 0u);
 }
 
+// +-(x^2 2^{-32}) mod n for x <= n: the absolute value of the difference that
+// mont32 corrects by n.  The next squaring does not see the sign, and one
+// v_sad_u32 replaces the borrow, the select and the add (4 instructions
+// instead of 6, 4.1 instead of 5.3 issue cycles).
+__device__ __forceinline__ uint32_t msqr32_abs(uint32_t x, uint32_t n, uint32_t ninv) {
+  const uint64_t t = (uint64_t)x * x;
+  const uint32_t q = (uint32_t)t * ninv;
+  const uint32_t qh = __umulhi(q, n);
+  uint32_t r;
+  asm("v_sad_u32 %0, %1, %2, 0" : "=v"(r) : "v"((uint32_t)(t >> 32)), "v"(qh));
+  return r;
+}
+
 // v 2^{-32} mod n for v < n 2^32.
 __device__ __forceinline__ uint32_t redc32(uint64_t v, uint32_t n, uint32_t ninv) {
   uint32_t q = (uint32_t)v * ninv;
@@ -88,51 +113,61 @@ __device__ __forceinline__ uint32_t addmod32(uint32_t m, uint32_t s, uint32_t n)
   return m < ns ? d + n : d;
 }
 
-// m^e mod n by left-to-right square-and-multiply on the unconverted message:
-// the chain yields m^e 2^{-32(e-1)}, and one product with kc = 2^{32 e} mod n
-// removes the factor.  EK selects a fixed chain (3, 5, 9, 17) or 0 for a
-// chain over the bits of e.
-template <int EK>
+// (w - s) mod n for w <= n, 1 <= s < n: the borrow selects the n added back
+// (one instruction less than the sum).
+__device__ __forceinline__ uint32_t submod32(uint32_t w, uint32_t s, uint32_t n) {
+  uint32_t r;
+  const bool borrow = __builtin_usub_overflow(w, s, &r);
+  return r + (borrow ? n : 0u);
+}
+
+// x^e mod n (plus PLUS, 0 or 1) by left-to-right square-and-multiply on the
+// unconverted x <= n, e odd: the chain yields x^e 2^{-32(e-1)}, and one
+// product with kc = 2^{32 e} mod n removes the factor.  With kc =
+// -2^{32 e} mod n and x = n - m it returns m^e (e is odd).  Squarings that
+// feed another squaring keep only the absolute value.  EK selects a fixed
+// chain (3, 5, 9, 17) or 0 for a chain over the bits of e.
+template <int EK, int PLUS = 0>
 __device__ __forceinline__ uint32_t encrypt32(uint32_t m, uint32_t n, uint32_t ninv, uint32_t kc, uint64_t e,
                                               int ebits) {
-  uint32_t x;
-  if constexpr (EK == 3) {
-    x = mont32(m, m, n, ninv);
-    x = mont32(x, m, n, ninv);
-  } else if constexpr (EK == 5) {
-    x = mont32(m, m, n, ninv);
-    x = mont32(x, x, n, ninv);
-    x = mont32(x, m, n, ninv);
+  uint32_t x = m;
+  if constexpr (EK == 5) {
+    x = msqr32_abs(x, n, ninv);
   } else if constexpr (EK == 9) {
-    x = mont32(m, m, n, ninv);
-    x = mont32(x, x, n, ninv);
-    x = mont32(x, x, n, ninv);
-    x = mont32(x, m, n, ninv);
+    x = msqr32_abs(x, n, ninv);
+    x = msqr32_abs(x, n, ninv);
   } else if constexpr (EK == 17) {
-    x = mont32(m, m, n, ninv);
-    x = mont32(x, x, n, ninv);
-    x = mont32(x, x, n, ninv);
+    x = msqr32_abs(x, n, ninv);
+    x = msqr32_abs(x, n, ninv);
+    x = msqr32_abs(x, n, ninv);
+  }
+  if constexpr (EK != 0) {
     x = mont32(x, x, n, ninv);
     x = mont32(x, m, n, ninv);
   } else {
-    x = m;
     for (int b = ebits - 2; b >= 0; --b) {
-      x = mont32(x, x, n, ninv);
-      if ((e >> b) & 1) x = mont32(x, m, n, ninv);
+      if ((e >> b) & 1)
+        x = mont32(mont32(x, x, n, ninv), m, n, ninv);
+      else
+        x = msqr32_abs(x, n, ninv);
     }
   }
-  return mont32(x, kc, n, ninv);
+  // the last product, with PLUS in the two values that the borrow selects
+  const uint64_t t = (uint64_t)x * kc;
+  const uint32_t q = (uint32_t)t * ninv;
+  const uint32_t qh = __umulhi(q, n);
+  uint32_t r;
+  const bool borrow = __builtin_usub_overflow((uint32_t)(t >> 32), qh, &r);
+  return r + (borrow ? n + PLUS : (uint32_t)PLUS);
 }
 
-// (c + 1) / (n + 1) correctly rounded, with rcp = RN(1/(n+1)) and den = n + 1
-// (both exact integers below 2^33): q0 = a rcp is within 2 ulp, the remainder
-// a - q0 den is exact, and one correction q0 + r rcp lands within 2^-52 ulp of
-// a/den, which no rounding boundary approaches closer than ulp/2^33.
-__device__ __forceinline__ double uniform32(uint32_t c, double den, double rcp) {
-  double a = (double)(c + 1u);
-  double q0 = a * rcp;
-  double r = __builtin_fma(-q0, den, a);
-  return __builtin_fma(r, rcp, q0);
+// a / den correctly rounded for integers 1 <= a < den <= 2^33, with rcp =
+// RN(1/den) and rcp_lo = RN(1/den - rcp): a rcp + RN(a rcp_lo) is within
+// 2^-105 of a/den (relative) and the fma rounds it once, while no rounding
+// boundary of binary64 comes closer to a/den than 2^-88 (ulp/2^34).
+__device__ __forceinline__ double uniform32(uint32_t c1, double rcp, double rcp_lo) {
+  const double a = (double)c1;
+  return __builtin_fma(a, rcp, a * rcp_lo);
 }
 
 // ---- 64-bit moduli from 32-bit limbs --------------------------------------
@@ -495,6 +530,29 @@ __device__ __forceinline__ uint64_t shfl_xor_u64(uint64_t v, int mask) {
   uint32_t lo = __shfl_xor((int)(uint32_t)v, mask, 64);
   uint32_t hi = __shfl_xor((int)(uint32_t)(v >> 32), mask, 64);
   return ((uint64_t)hi << 32) | lo;
+}
+
+// Lane value moved by a DPP control word; lanes without a source (and rows
+// outside ROWS) get 0.
+template <int CTRL, int ROWS>
+__device__ __forceinline__ uint64_t dpp_u64(uint64_t v) {
+  const uint32_t lo = __builtin_amdgcn_update_dpp(0, (int)(uint32_t)v, CTRL, ROWS, 0xf, false);
+  const uint32_t hi = __builtin_amdgcn_update_dpp(0, (int)(uint32_t)(v >> 32), CTRL, ROWS, 0xf, false);
+  return ((uint64_t)hi << 32) | lo;
+}
+
+// Inclusive prefix sum of v over the lanes of the wave, all lanes active:
+// shifts by 1, 2, 4, 8 inside the rows of 16 lanes, then the last lane of a
+// row (of two rows) added to the next ones.  Six register moves without the
+// LDS round trip that a shuffle takes.
+__device__ __forceinline__ uint64_t wave_inclusive_sum(uint64_t v) {
+  v += dpp_u64<0x111, 0xf>(v);  // row_shr:1
+  v += dpp_u64<0x112, 0xf>(v);  // row_shr:2
+  v += dpp_u64<0x114, 0xf>(v);  // row_shr:4
+  v += dpp_u64<0x118, 0xf>(v);  // row_shr:8
+  v += dpp_u64<0x142, 0xa>(v);  // row_bcast:15 into rows 1 and 3
+  v += dpp_u64<0x143, 0xc>(v);  // row_bcast:31 into rows 2 and 3
+  return v;
 }
 
 // Sum of v over the 64 lanes of the wave, mod n (v < n < 2^63); every lane

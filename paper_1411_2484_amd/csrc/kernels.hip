@@ -56,7 +56,7 @@ __global__ void __launch_bounds__(256) table_segments32(uint64_t nseg, uint64_t 
   seg_start[i] = s;
   uint64_t sum = 0;
   for (uint64_t j = 0; j < kTableStride; ++j) {
-    s = dev::mulmod_p31(kA32, s);
+    s = dev::fold_p31(dev::step_p31(s));
     sum += s;
   }
   seg_sum[i] = sum;
@@ -129,12 +129,12 @@ __global__ void __launch_bounds__(256) build_records(const uint64_t *n_arr, cons
     const uint32_t re1 = dev::mpow32(r2, e, one, n32, ninv);
     rec.ninv = ninv;
     rec.r2 = r2;
-    rec.kcorr = dev::mont32(re1, 1u, n32, ninv);
+    rec.kcorr = n32 - dev::mont32(re1, 1u, n32, ninv);
     // p(p-1)/2 mod n, then times R^2: mont(b, R^3) with R^3 = mont(R^2, R^2)
     const uint64_t full = ((uint64_t)kP32 * ((uint64_t)kP32 - 1)) / 2;
     const uint32_t b = dev::mont32(dev::redc32(full, n32, ninv), r2, n32, ninv);
     rec.br2 = dev::mont32(b, dev::mont32(r2, r2, n32, ninv), n32, ninv);
-    rec.rcp = 1.0 / (double)(n + 1);
+    rec.rcp = 1.0 / rec.den;
   } else {
     const uint64_t ninv = dev::inv64(n);
     uint64_t one = 0ull - n;
@@ -148,6 +148,7 @@ __global__ void __launch_bounds__(256) build_records(const uint64_t *n_arr, cons
     rec.br2 = 0;
     rec.rcp = 1.0 / rec.den;
   }
+  rec.rcp_lo = __builtin_fma(-rec.den, rec.rcp, 1.0) / rec.den;  // the fma is exact
   out[i] = rec;
 }
 
@@ -509,8 +510,20 @@ struct Enc32 {
   uint32_t n, ninv, kc;
   uint64_t e;
   int ebits;
-  double den, rcp;
+  double rcp, rcp_lo;
 };
+
+// Ciphertext and uniform of one message of a width-32 tile (x = n - m).
+template <int EK, int OUT>
+__device__ __forceinline__ void emit32(uint32_t x, const Enc32 &K, uint32_t *c32, double *rr) {
+  if constexpr (OUT & kOutC) {
+    const uint32_t c = dev::encrypt32<EK>(x, K.n, K.ninv, K.kc, K.e, K.ebits);
+    *c32 = c;
+    if constexpr (OUT & kOutR) *rr = dev::uniform32(c + 1u, K.rcp, K.rcp_lo);
+  } else {
+    *rr = dev::uniform32(dev::encrypt32<EK, 1>(x, K.n, K.ninv, K.kc, K.e, K.ebits), K.rcp, K.rcp_lo);
+  }
+}
 
 // Pass C, width 32: draw t = i*64 + lane of the tile lives at LDS row t / 32,
 // column t % 32.  MASKED tiles write only t in [t_lo, t_hi).
@@ -521,11 +534,9 @@ __device__ __forceinline__ void passC32(const uint32_t *L, uint32_t lane, const 
   const uint32_t span = t_hi - t_lo;
 #pragma unroll UNROLL
   for (int i = 0; i < kRun32; ++i) {
-    const uint32_t m = src[i * 2 * kRow32];
+    const uint32_t x = src[i * 2 * kRow32];
     if (!MASKED || ((uint32_t)i * 64u + lane - t_lo < span)) {
-      const uint32_t c = dev::encrypt32<EK>(m, K.n, K.ninv, K.kc, K.e, K.ebits);
-      if (OUT & kOutC) c32[i * 64] = c;
-      if (OUT & kOutR) rr[i * 64] = dev::uniform32(c, K.den, K.rcp);
+      emit32<EK, OUT>(x, K, c32 + i * 64, rr + i * 64);
     }
   }
 }
@@ -557,7 +568,7 @@ __device__ void run_chunk32(const GenArgs &A, const InstRec &I, const ReqRec &R,
   const uint32_t br2 = (uint32_t)I.br2;
   const uint64_t e = I.e;
   const int ebits = (int)I.ebits, ekind = (int)I.ekind;
-  const double den = I.den, rcp = I.rcp;
+  const Enc32 K{n, ninv, kc, e, ebits, I.rcp, I.rcp_lo};
   const uint64_t pm1 = (uint64_t)kP32 - 1;
   const uint32_t lane_mul = A.lanemul->m32[lane];
   const uint32_t one = dev::opaque_one();
@@ -579,32 +590,34 @@ __device__ void run_chunk32(const GenArgs &A, const InstRec &I, const ReqRec &R,
       uint32_t mq = dev::mont32(dev::redc32(q, n, ninv), br2, n, ninv);
       m_t = dev::addmod32(mu, mq, n);
     }
-    // ---- pass A: skips of this lane's run, their sum
+    // ---- pass A: skips of this lane's run, their sum (two skips < 2^31 add
+    // below 2^32 before they enter the 64-bit sum)
     uint32_t *row = L + lane * kRow32;
     uint32_t s = dev::mulmod_p31(s_t, lane_mul);
     uint64_t sum = 0;
+#pragma unroll 4
+    for (int i = 0; i < kRun32; i += 2) {
+      const uint32_t v0 = dev::step_p31(s);
+      const uint32_t v1 = dev::step_p31(v0);
+      const uint32_t s0 = dev::fold_p31(v0);
+      s = dev::fold_p31(v1);
+      row[i] = s0;
+      row[i + 1] = s;
+      sum = dev::acc_u32(sum, s0 + s, one);
+    }
+    // ---- pass B: exclusive wave scan of run sums -> run start message,
+    // carried as x = n - m: the encryption takes the sign back (kcorr), and
+    // x - s mod n is one instruction shorter than m + s mod n
+    const uint64_t incl = dev::wave_inclusive_sum(sum);
+    uint32_t x = n - dev::mont32(dev::redc32(incl - sum + m_t, n, ninv), r2, n, ninv);
 #pragma unroll 8
     for (int i = 0; i < kRun32; ++i) {
-      s = dev::mulmod_p31(kA32, s);
-      row[i] = s;
-      sum = dev::acc_u32(sum, s, one);
-    }
-    // ---- pass B: exclusive wave scan of run sums -> run start message
-    uint64_t incl = sum;
-#pragma unroll
-    for (int d = 1; d < 64; d <<= 1) {
-      uint64_t v = dev::shfl_up_u64(incl, d);
-      if ((int)lane >= d) incl += v;
-    }
-    uint32_t m = dev::mont32(dev::redc32(incl - sum + m_t, n, ninv), r2, n, ninv);
-#pragma unroll 8
-    for (int i = 0; i < kRun32; ++i) {
-      m = dev::addmod32(m, row[i], n);
-      row[i] = m;
+      x = dev::submod32(x, row[i], n);
+      row[i] = x;
     }
     // state at the end of the tile (lane 63's last message and skip)
-    m_t = (uint32_t)__shfl((int)m, 63, 64);
-    s_t = (uint32_t)__shfl((int)s, 63, 64);
+    m_t = n - (uint32_t)__builtin_amdgcn_readlane((int)x, 63);
+    s_t = (uint32_t)__builtin_amdgcn_readlane((int)s, 63);
     carried = true;
     dev::wave_lds_sync();
     // ---- pass C: encrypt in draw order
@@ -618,7 +631,6 @@ __device__ void run_chunk32(const GenArgs &A, const InstRec &I, const ReqRec &R,
     const int64_t base = (int64_t)R.out_off + (int64_t)(tile_first - R.x) + (int64_t)lane;
     uint32_t *c32 = A.out_c32 ? A.out_c32 + base : nullptr;
     double *rr = A.out_r ? A.out_r + base : nullptr;
-    const Enc32 K{n, ninv, kc, e, ebits, den, rcp};
     if (t_lo == 0 && t_hi == (uint32_t)kTile32)
       passC32_e<UNROLL, false>(ekind, L, lane, K, c32, rr, t_lo, t_hi);
     else
@@ -745,17 +757,15 @@ __device__ void run_chunk64(const GenArgs &A, const InstRec &I, const ReqRec &R,
 // ---------------------------------------------------------------------------
 
 template <int UNROLL, int EK, int OUT, bool MASKED>
-__device__ __forceinline__ void passCS32(uint32_t m, uint32_t step, uint32_t lane, const Enc32 &K, uint32_t *c32,
+__device__ __forceinline__ void passCS32(uint32_t x, uint32_t step, uint32_t lane, const Enc32 &K, uint32_t *c32,
                                          double *rr, uint32_t t_lo, uint32_t t_hi) {
   const uint32_t span = t_hi - t_lo;
 #pragma unroll UNROLL
   for (int i = 0; i < kTileCS / 64; ++i) {
     if (!MASKED || ((uint32_t)i * 64u + lane - t_lo < span)) {
-      const uint32_t c = dev::encrypt32<EK>(m, K.n, K.ninv, K.kc, K.e, K.ebits);
-      if (OUT & kOutC) c32[i * 64] = c;
-      if (OUT & kOutR) rr[i * 64] = dev::uniform32(c, K.den, K.rcp);
+      emit32<EK, OUT>(x, K, c32 + i * 64, rr + i * 64);
     }
-    m = dev::addmod32(m, step, K.n);
+    x = dev::submod32(x, step, K.n);
   }
 }
 
@@ -782,7 +792,7 @@ __device__ __forceinline__ void passCS32_e(int ekind, uint32_t m, uint32_t step,
 template <int UNROLL>
 __device__ void run_chunk32_cs(const GenArgs &A, const InstRec &I, const ReqRec &R, uint64_t chunk, uint32_t lane) {
   const uint32_t n = (uint32_t)I.n, ninv = (uint32_t)I.ninv;
-  const Enc32 K{n, ninv, (uint32_t)I.kcorr, I.e, (int)I.ebits, I.den, I.rcp};
+  const Enc32 K{n, ninv, (uint32_t)I.kcorr, I.e, (int)I.ebits, I.rcp, I.rcp_lo};
   const uint32_t bR2 = (uint32_t)I.bR2, step = (uint32_t)I.b64, mbase = (uint32_t)I.mbase;
   const uint64_t g_begin = R.g1 + chunk * A.tiles_per_chunk;
   const uint64_t g_end = min(g_begin + A.tiles_per_chunk, R.g1 + R.ntiles);
@@ -794,7 +804,7 @@ __device__ void run_chunk32_cs(const GenArgs &A, const InstRec &I, const ReqRec 
     uint32_t vh = (uint32_t)(v >> 32);
     vh = vh >= n ? vh - n : vh;
     const uint64_t vr = ((uint64_t)vh << 32) | (uint32_t)v;
-    const uint32_t m = dev::addmod32(mbase, dev::mont32(dev::redc32(vr, n, ninv), bR2, n, ninv), n);
+    const uint32_t m = n - dev::addmod32(mbase, dev::mont32(dev::redc32(vr, n, ninv), bR2, n, ninv), n);
     const uint64_t req_end = R.x + R.count;
     const uint32_t t_lo = R.x > x0 ? (uint32_t)(R.x - x0) : 0u;
     const uint32_t t_hi = (uint32_t)min(req_end - x0, (uint64_t)kTileCS);

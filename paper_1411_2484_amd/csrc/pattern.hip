@@ -34,7 +34,7 @@ constexpr unsigned kChiBlocks = 1024;
 constexpr uint64_t kMaxGroups = 1ull << 22;  // workgroups per pattern launch
 
 struct PatArgs {
-  uint32_t n, ninv, kc, kd;  // kc = 2^(32 e) mod n, kd = 2^(32 d) mod n
+  uint32_t n, ninv, kc, kd;  // kc = -2^(32 e) mod n, kd = -2^(32 d) mod n
   uint64_t e, d;
   int ebits, dbits;
   uint32_t x0, bins;
@@ -62,7 +62,9 @@ __global__ __launch_bounds__(256) void pattern_kernel(PatArgs A, ph::PartSet P) 
   __shared__ uint32_t stage[kHalf];
   const uint64_t i = blockIdx.x / A.nchunks;
   const uint64_t ch = blockIdx.x - i * A.nchunks;
-  const uint32_t m = dev::encrypt32<0>(A.x0 + (uint32_t)i, A.n, A.ninv, A.kd, A.d, A.dbits);
+  // messages are carried negated (x = n - m), like in the generation kernels:
+  // c^d with -2^(32 d) gives n - m, and the forward chain takes the sign back
+  const uint32_t x0 = dev::encrypt32<0>(A.x0 + (uint32_t)i, A.n, A.ninv, A.kd, A.d, A.dbits);
   for (uint32_t half = 0; half < kChunk / kHalf; ++half) {
     const uint64_t s0 = A.s_lo + ch * kChunk + half * kHalf + threadIdx.x;
     uint32_t key[kHalf / 256];
@@ -70,13 +72,13 @@ __global__ __launch_bounds__(256) void pattern_kernel(PatArgs A, ph::PartSet P) 
     for (uint32_t it = 0; it < kHalf / 256; ++it) {
       const uint64_t s = s0 + (uint64_t)it * 256;
       uint32_t sk = (uint32_t)(s < A.s_hi ? s : A.s_lo);  // lanes past the range compute a valid dummy
-      uint32_t mk = dev::addmod32(m, sk, A.n);
-      uint32_t cell = cell_bin(dev::encrypt32<EK>(mk, A.n, A.ninv, A.kc, A.e, A.ebits), A);
+      uint32_t xk = dev::submod32(x0, sk, A.n);
+      uint32_t cell = cell_bin(dev::encrypt32<EK>(xk, A.n, A.ninv, A.kc, A.e, A.ebits), A);
 #pragma unroll
       for (int j = 2; j < D; ++j) {
-        sk = dev::mulmod_p31(sk, kA32);
-        mk = dev::addmod32(mk, sk, A.n);
-        cell = cell * A.bins + cell_bin(dev::encrypt32<EK>(mk, A.n, A.ninv, A.kc, A.e, A.ebits), A);
+        sk = dev::fold_p31(dev::step_p31(sk));
+        xk = dev::submod32(xk, sk, A.n);
+        cell = cell * A.bins + cell_bin(dev::encrypt32<EK>(xk, A.n, A.ninv, A.kc, A.e, A.ebits), A);
       }
       key[it] = s < A.s_hi ? cell : ph::kNoKey;
     }
@@ -221,8 +223,8 @@ phprng_status phprng_pattern_histogram(const phprng_pattern *P, uint64_t *hist, 
   const uint64_t R = (1ull << 32) % P->n;
   A.e = P->e;
   A.d = inverse_mod(P->e, P->n - 1);
-  A.kc = (uint32_t)M.powmod(R, A.e);
-  A.kd = (uint32_t)M.powmod(R, A.d);
+  A.kc = n - (uint32_t)M.powmod(R, A.e);
+  A.kd = n - (uint32_t)M.powmod(R, A.d);
   A.ebits = pat::bit_length(A.e);
   A.dbits = pat::bit_length(A.d);
   A.x0 = (uint32_t)P->x0;

@@ -4,6 +4,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <cmath>
 #include <chrono>
 #include <cstdarg>
 #include <cstdio>
@@ -315,10 +316,10 @@ struct phprng_ctx {
       const uint64_t R = (1ull << 32) % h.n;
       const uint64_t R2 = M.mulmod(R, R);
       rec.r2 = R2;
-      rec.kcorr = M.powmod(R, h.e);
+      rec.kcorr = h.n - M.powmod(R, h.e);
       rec.br2 = M.mulmod(b, R2);
       rec.den = (double)(h.n + 1);
-      rec.rcp = 1.0 / (double)(h.n + 1);
+      rec.rcp = 1.0 / rec.den;
     } else {
       rec.ninv = M.ninv;
       rec.r2 = M.r2;
@@ -327,6 +328,7 @@ struct phprng_ctx {
       rec.den = (double)(h.n + 1);
       rec.rcp = 1.0 / rec.den;
     }
+    rec.rcp_lo = std::fma(-rec.den, rec.rcp, 1.0) / rec.den;  // the fma is exact
     return rec;
   }
 
