@@ -280,8 +280,139 @@ __device__ __forceinline__ uint64_t mont64_uniform(uint64_t x, uint64_t y, uint6
   return redc64_uniform(mul63w(x, y), n, ninv);
 }
 
-__device__ __forceinline__ uint64_t msqr64_uniform(uint64_t x, uint64_t n, uint64_t ninv) {
-  return redc64_uniform(sqr63w(x), n, ninv);
+// ---- the width-64 encryption chain ------------------------------------------
+//
+// Products x y 2^{-64} mod n in two rounds of 32 bits, added instead of
+// subtracted: with n' = -n^{-1} mod 2^32, round 1 adds q n (q = lo32(x y) n')
+// and round 2 q' n 2^32, which clear the two low words; the multiply-adds
+// take the running sum as their 64-bit addend, so only three carry-outs and
+// two register moves remain of the word bookkeeping.  Inputs below 2^63 give
+// r = (x y + Q n) 2^{-64} < 2^62 + n < 2^64; between the products of a chain
+// n is subtracted when bit 63 is set, which keeps r below 2^63 (a sign mask:
+// no compare, no carry), and only the last product is reduced below n.  19
+// VALU instructions per product with that step, about 16.1 issue cycles
+// (21 and 18.4 with the 64-bit quotient of redc64_uniform); n, -n and n' are
+// read from scalar registers (the same in every lane of the wave).
+//
+// v0-v7 hold the intermediate register pairs; VCC carries each carry-out
+// (two wait states between its write and its read as a carry).
+struct Mod64 {
+  uint32_t n0, n1;    // n
+  uint32_t np;        // -n^{-1} mod 2^32
+  uint32_t nn0, nn1;  // 2^64 - n
+  uint32_t one;       // 1 in a vector register
+};
+
+#define PHPRNG_ROUND1                                                                         \
+  "v_mul_lo_u32 v7, v0, %[np]\n\t"                                                            \
+  "v_mad_u64_u32 v[0:1], vcc, v7, %[n0], v[0:1]\n\t" /* lo32 = 0, carry in VCC */             \
+  "v_mov_b32 v2, v1\n\t"                                                                      \
+  "s_nop 0\n\t"                                                                               \
+  "v_cndmask_b32 v3, 0, %[one], vcc\n\t"                                                      \
+  "v_mad_u64_u32 v[2:3], vcc, v7, %[n1], v[2:3]\n\t"
+
+// column 1 is in v[2:3] with its carry-out in VCC
+#define PHPRNG_ROUND2                                                                         \
+  "v_mul_lo_u32 v7, v2, %[np]\n\t"                                                            \
+  "s_nop 0\n\t"                                                                               \
+  "v_cndmask_b32 v5, 0, %[one], vcc\n\t"                                                      \
+  "v_mad_u64_u32 v[2:3], vcc, v7, %[n0], v[2:3]\n\t" /* lo32 = 0, carry in VCC */             \
+  "v_mov_b32 v4, v3\n\t"                                                                      \
+  "s_nop 0\n\t"                                                                               \
+  "v_addc_co_u32 v5, vcc, 0, v5, vcc\n\t"                                                     \
+  "v_mad_u64_u32 v[4:5], vcc, v7, %[n1], v[4:5]\n\t"
+
+#define PHPRNG_BELOW_2_63                                                                     \
+  "v_ashrrev_i32 v6, 31, v5\n\t"                                                              \
+  "v_and_b32 v0, %[nn0], v6\n\t"                                                              \
+  "v_and_b32 v1, %[nn1], v6\n\t"                                                              \
+  "v_lshl_add_u64 %[r], v[4:5], 0, v[0:1]"
+
+#define PHPRNG_MOD_OPERANDS                                                                   \
+  [n0] "s"(K.n0), [n1] "s"(K.n1), [np] "s"(K.np), [one] "v"(K.one)
+#define PHPRNG_CLOBBERS "v0", "v1", "v2", "v3", "v4", "v5", "v6", "v7", "vcc"
+
+// x^2 2^{-64} mod n, below 2^63, for x < 2^63.
+__device__ __forceinline__ uint64_t lazy_sqr64(uint64_t x, const Mod64 &K) {
+  uint64_t r;
+  asm("v_mad_u64_u32 v[0:1], vcc, %[x0], %[x0], 0\n\t"
+      "v_add_u32 v6, %[x1], %[x1]\n\t"
+      PHPRNG_ROUND1
+      "v_mad_u64_u32 v[2:3], vcc, %[x0], v6, v[2:3]\n\t"
+      PHPRNG_ROUND2
+      "v_mad_u64_u32 v[4:5], vcc, %[x1], %[x1], v[4:5]\n\t"
+      PHPRNG_BELOW_2_63
+      : [r] "=v"(r)
+      : [x0] "v"((uint32_t)x), [x1] "v"((uint32_t)(x >> 32)), [nn0] "s"(K.nn0), [nn1] "s"(K.nn1),
+        PHPRNG_MOD_OPERANDS
+      : PHPRNG_CLOBBERS);
+  return r;
+}
+
+// x y 2^{-64} mod n, below 2^63, for x, y < 2^63.
+__device__ __forceinline__ uint64_t lazy_mul64(uint64_t x, uint64_t y, const Mod64 &K) {
+  uint64_t r;
+  asm("v_mad_u64_u32 v[0:1], vcc, %[x0], %[y0], 0\n\t"
+      PHPRNG_ROUND1
+      "v_mad_u64_u32 v[2:3], vcc, %[x0], %[y1], v[2:3]\n\t"  // below 2^64: n1, y1 < 2^31
+      "v_mad_u64_u32 v[2:3], vcc, %[x1], %[y0], v[2:3]\n\t"
+      PHPRNG_ROUND2
+      "v_mad_u64_u32 v[4:5], vcc, %[x1], %[y1], v[4:5]\n\t"
+      PHPRNG_BELOW_2_63
+      : [r] "=v"(r)
+      : [x0] "v"((uint32_t)x), [x1] "v"((uint32_t)(x >> 32)), [y0] "v"((uint32_t)y), [y1] "v"((uint32_t)(y >> 32)),
+        [nn0] "s"(K.nn0), [nn1] "s"(K.nn1), PHPRNG_MOD_OPERANDS
+      : PHPRNG_CLOBBERS);
+  return r;
+}
+
+// (x k 2^{-64} mod n) + PLUS for x < 2^63 and a wave-uniform k < n: reduced
+// below n by one compare that selects PLUS or PLUS - n.
+template <int PLUS>
+__device__ __forceinline__ uint64_t last_mul64(uint64_t x, uint64_t k, uint64_t n, const Mod64 &K) {
+  uint64_t r;
+  asm("v_mad_u64_u32 v[0:1], vcc, %[x0], %[y0], 0\n\t"
+      PHPRNG_ROUND1
+      "v_mad_u64_u32 v[2:3], vcc, %[x0], %[y1], v[2:3]\n\t"
+      "v_mad_u64_u32 v[2:3], vcc, %[x1], %[y0], v[2:3]\n\t"
+      PHPRNG_ROUND2
+      "v_mad_u64_u32 %[r], vcc, %[x1], %[y1], v[4:5]"
+      : [r] "=v"(r)
+      : [x0] "v"((uint32_t)x), [x1] "v"((uint32_t)(x >> 32)), [y0] "s"((uint32_t)k), [y1] "s"((uint32_t)(k >> 32)),
+        PHPRNG_MOD_OPERANDS
+      : PHPRNG_CLOBBERS);
+  return r + (r < n ? (uint64_t)PLUS : (uint64_t)PLUS - n);
+}
+
+#undef PHPRNG_ROUND1
+#undef PHPRNG_ROUND2
+#undef PHPRNG_BELOW_2_63
+#undef PHPRNG_MOD_OPERANDS
+#undef PHPRNG_CLOBBERS
+
+// x^e mod n (plus PLUS, 0 or 1) for x <= n, e odd, by a fixed chain for e =
+// 3, 5, 9, 17, else by left-to-right squaring; n, ninv and kc = 2^{64 e} mod
+// n are the same in every lane of the wave (one instance per tile).  With kc
+// = -2^{64 e} mod n and x = n - m it returns m^e.
+template <int EK, int PLUS = 0>
+__device__ __forceinline__ uint64_t encrypt64(uint64_t m, uint64_t n, uint64_t ninv, uint64_t kc, uint64_t e,
+                                              int ebits) {
+  const Mod64 K{(uint32_t)n, (uint32_t)(n >> 32), 0u - (uint32_t)ninv, (uint32_t)(0ull - n),
+                (uint32_t)((0ull - n) >> 32), 1u};
+  uint64_t x = m;
+  if constexpr (EK != 0) {
+    constexpr int kSquarings = EK == 3 ? 1 : (EK == 5 ? 2 : (EK == 9 ? 3 : 4));
+    static_assert(EK == (1 << kSquarings) + 1, "fixed chains are 2^k + 1");
+#pragma unroll
+    for (int i = 0; i < kSquarings; ++i) x = lazy_sqr64(x, K);
+    x = lazy_mul64(x, m, K);
+  } else {
+    for (int b = ebits - 2; b >= 0; --b) {
+      x = lazy_sqr64(x, K);
+      if ((e >> b) & 1) x = lazy_mul64(x, m, K);
+    }
+  }
+  return last_mul64<PLUS>(x, kc, n, K);
 }
 
 // (m + s) mod n for m, s < n < 2^63 (no overflow of the sum).
@@ -297,39 +428,31 @@ __device__ __forceinline__ uint64_t mod_below_4n(uint64_t v, uint64_t n) {
   return v >= n ? v - n : v;
 }
 
-// m^e mod n (algorithm (9)) by a fixed chain for e = 3, 5, 9, 17, else by
-// left-to-right squaring; n, ninv and kc = 2^{64 e} mod n are the same in
-// every lane of the wave (one instance per tile).
-template <int EK>
-__device__ __forceinline__ uint64_t encrypt64(uint64_t m, uint64_t n, uint64_t ninv, uint64_t kc, uint64_t e,
-                                              int ebits) {
-  uint64_t x;
-  if constexpr (EK == 3) {
-    x = msqr64_uniform(m, n, ninv);
-    x = mont64_uniform(x, m, n, ninv);
-  } else if constexpr (EK == 5) {
-    x = msqr64_uniform(m, n, ninv);
-    x = msqr64_uniform(x, n, ninv);
-    x = mont64_uniform(x, m, n, ninv);
-  } else if constexpr (EK == 9) {
-    x = msqr64_uniform(m, n, ninv);
-    x = msqr64_uniform(x, n, ninv);
-    x = msqr64_uniform(x, n, ninv);
-    x = mont64_uniform(x, m, n, ninv);
-  } else if constexpr (EK == 17) {
-    x = msqr64_uniform(m, n, ninv);
-    x = msqr64_uniform(x, n, ninv);
-    x = msqr64_uniform(x, n, ninv);
-    x = msqr64_uniform(x, n, ninv);
-    x = mont64_uniform(x, m, n, ninv);
-  } else {
-    x = m;
-    for (int b = ebits - 2; b >= 0; --b) {
-      x = msqr64_uniform(x, n, ninv);
-      if ((e >> b) & 1) x = mont64_uniform(x, m, n, ninv);
-    }
-  }
-  return mont64_uniform(x, kc, n, ninv);
+// (w - s) mod n for w <= n, s <= n (not w = 0 with s = n).
+__device__ __forceinline__ uint64_t submod64(uint64_t w, uint64_t s, uint64_t n) {
+  unsigned long r;
+  const bool borrow = __builtin_usubl_overflow(w, s, &r);
+  return (uint64_t)r + (borrow ? n : 0ull);
+}
+
+// One skip step a s mod (2^61 - 1) for s in [1, p - 1].  The product with 8 a
+// has (a s) >> 61 as its high 64 bits and 8 ((a s) mod 2^61) as its low 64
+// bits, so the fold takes two shifts instead of a mask and two funnel shifts;
+// 8 a < 0.75 2^64 and s < 2^61 keep the middle column below 2^64.  The sum v
+// is below 2p, never 0 or p, and its bit 61 carries back in.
+__device__ __forceinline__ uint64_t step_p61(uint64_t s) {
+  constexpr uint64_t kA8 = 8 * kA64;
+  static_assert((kA64 >> 61) == 0 && kA8 < 3ull << 62, "the middle column stays below 2^64");
+  constexpr uint32_t a0 = (uint32_t)kA8, a1 = (uint32_t)(kA8 >> 32);
+  const uint32_t s0 = (uint32_t)s, s1 = (uint32_t)(s >> 32);
+  const uint64_t p00 = (uint64_t)s0 * a0;
+  const uint64_t mid = mad_u64_u32(s1, a0, (uint64_t)s0 * a1 + (p00 >> 32));
+  const uint64_t hi = (uint64_t)s1 * a1 + (mid >> 32);
+  const uint64_t v = (((mid << 32) | (uint32_t)p00) >> 3) + hi;
+  const uint32_t top = (uint32_t)(v >> 61);
+  uint64_t r, carry;
+  asm("v_mad_u64_u32 %0, %1, %2, 1, %3" : "=v"(r), "=s"(carry) : "v"(top), "v"(v & kP64));
+  return r;
 }
 
 // Skip generator mod 2^61 - 1 (width 64): fold the 122-bit product.
@@ -366,17 +489,16 @@ __device__ __forceinline__ uint64_t wave_pow_p61(const uint64_t *pow2, uint64_t 
   return f;
 }
 
-// binary64(c + 1) / binary64(n + 1) correctly rounded, with den = RN(n + 1)
-// and rcp = RN(1/den); c + 1 < 2^63 converts with one rounding.  The first
-// correction makes the quotient faithful (within 1 ulp); from a faithful
-// quotient and a correctly rounded reciprocal, one more remainder-and-
-// correct step gives the correctly rounded quotient (Markstein), with five
-// FP64 operations instead of the IEEE divide sequence.
-__device__ __forceinline__ double uniform64(uint64_t c, double den, double rcp) {
-  const double a = (double)(c + 1);
-  const double q0 = a * rcp;
-  const double q1 = __builtin_fma(__builtin_fma(-q0, den, a), rcp, q0);
-  return __builtin_fma(__builtin_fma(-q1, den, a), rcp, q1);
+// binary64(c1) / binary64(n + 1) correctly rounded, c1 = c + 1 < 2^63, with
+// den = RN(n + 1), rcp = RN(1/den) and rcp_lo = RN(1/den - rcp): a rcp +
+// RN(a rcp_lo) rounded once is within one ulp of a/den, and from such a
+// quotient and a correctly rounded reciprocal one remainder-and-correct step
+// gives the correctly rounded quotient (Markstein): four FP64 operations
+// after the conversion, which rounds once (the fma).
+__device__ __forceinline__ double uniform64(uint64_t c1, double den, double rcp, double rcp_lo) {
+  const double a = __builtin_fma((double)(uint32_t)(c1 >> 32), 4294967296.0, (double)(uint32_t)c1);
+  const double q = __builtin_fma(a, rcp, a * rcp_lo);
+  return __builtin_fma(__builtin_fma(-q, den, a), rcp, q);
 }
 
 // ---- instance set-up on the device (seeding) --------------------------------
@@ -526,6 +648,14 @@ __device__ __forceinline__ uint64_t shfl_u64(uint64_t v, int src) {
   return ((uint64_t)hi << 32) | lo;
 }
 
+// The value of lane LANE, in scalar registers.
+template <int LANE>
+__device__ __forceinline__ uint64_t lane_u64(uint64_t v) {
+  const uint32_t lo = __builtin_amdgcn_readlane((int)(uint32_t)v, LANE);
+  const uint32_t hi = __builtin_amdgcn_readlane((int)(uint32_t)(v >> 32), LANE);
+  return ((uint64_t)hi << 32) | lo;
+}
+
 __device__ __forceinline__ uint64_t shfl_xor_u64(uint64_t v, int mask) {
   uint32_t lo = __shfl_xor((int)(uint32_t)v, mask, 64);
   uint32_t hi = __shfl_xor((int)(uint32_t)(v >> 32), mask, 64);
@@ -566,18 +696,17 @@ __device__ __forceinline__ uint64_t wave_sum_mod(uint64_t v, uint64_t n) {
   return v;
 }
 
-// Exclusive prefix sum of v over the lanes of the wave, mod n (v < n < 2^63).
-__device__ __forceinline__ uint64_t wave_exclusive_mod(uint64_t v, uint64_t n, uint32_t lane) {
+// Exclusive prefix sum of v over the lanes of the wave, mod n (v < n < 2^63),
+// all lanes active: the DPP steps of wave_inclusive_sum, reduced at each.
+__device__ __forceinline__ uint64_t wave_exclusive_mod(uint64_t v, uint64_t n) {
   uint64_t incl = v;
-#pragma unroll
-  for (int d = 1; d < 64; d <<= 1) {
-    const uint64_t u = shfl_up_u64(incl, d);
-    if ((int)lane >= d) {
-      const uint64_t t = incl + u;
-      incl = t >= n ? t - n : t;
-    }
-  }
-  return incl >= v ? incl - v : incl + (n - v);
+  incl = addmod64(incl, dpp_u64<0x111, 0xf>(incl), n);
+  incl = addmod64(incl, dpp_u64<0x112, 0xf>(incl), n);
+  incl = addmod64(incl, dpp_u64<0x114, 0xf>(incl), n);
+  incl = addmod64(incl, dpp_u64<0x118, 0xf>(incl), n);
+  incl = addmod64(incl, dpp_u64<0x142, 0xa>(incl), n);
+  incl = addmod64(incl, dpp_u64<0x143, 0xc>(incl), n);
+  return submod64(incl, v, n);
 }
 
 // Orders this wave's LDS accesses across lanes (all lanes of one wave).

@@ -70,7 +70,7 @@ __global__ void __launch_bounds__(256) table_segments64(uint64_t nseg, uint64_t 
   seg_start[i] = s;
   uint64_t lo = 0, hi = 0;
   for (uint64_t j = 0; j < kTab64Stride; ++j) {
-    s = dev::mulmod_p61(kA64, s);
+    s = dev::step_p61(s);
     uint64_t t = lo + s;
     hi += (t < lo) ? 1 : 0;
     lo = t;
@@ -144,7 +144,7 @@ __global__ void __launch_bounds__(256) build_records(const uint64_t *n_arr, cons
     const uint64_t re1 = dev::mpow64(r2, e, one, n, ninv);
     rec.ninv = ninv;
     rec.r2 = r2;
-    rec.kcorr = dev::mont64(re1, 1ull, n, ninv);
+    rec.kcorr = n - dev::mont64(re1, 1ull, n, ninv);
     rec.br2 = 0;
     rec.rcp = 1.0 / rec.den;
   }
@@ -164,7 +164,7 @@ __device__ uint64_t table_prefix64(const uint64_t *u_lo, const uint64_t *u_hi, c
   const uint64_t i = t / kTab64Stride;
   uint64_t lo = u_lo[i], hi = u_hi[i], s = u_s[i];
   for (uint64_t x = i * kTab64Stride; x < t; ++x) {
-    s = dev::mulmod_p61(kA64, s);
+    s = dev::step_p61(s);
     const uint64_t v = lo + s;
     hi += v < lo ? 1 : 0;
     lo = v;
@@ -227,7 +227,7 @@ __device__ __forceinline__ uint64_t tile_skip_sum64(uint64_t s_tile, uint64_t la
   const uint32_t first = lane * kRun64;
 #pragma unroll 4
   for (int i = 0; i < kRun64; ++i) {
-    s = dev::mulmod_p61(kA64, s);
+    s = dev::step_p61(s);
     if (first + (uint32_t)i < len) sum = dev::addmod64(sum, s, n);
   }
   return dev::wave_sum_mod(sum, n);
@@ -281,8 +281,8 @@ __global__ void __launch_bounds__(256) reduce64_kernel(GenArgs A) {
         uint64_t g1 = 0, g2 = 0;
 #pragma unroll
         for (int i = 0; i < kRun64 / 2; ++i) {
-          s = dev::mulmod_p61(kA64, s);
-          s2 = dev::mulmod_p61(kA64, s2);
+          s = dev::step_p61(s);
+          s2 = dev::step_p61(s2);
           g1 += s;
           g2 += s2;
         }
@@ -294,7 +294,7 @@ __global__ void __launch_bounds__(256) reduce64_kernel(GenArgs A) {
         sum = 0;
 #pragma unroll 4
         for (int i = 0; i < kRun64; ++i) {
-          s = dev::mulmod_p61(kA64, s);
+          s = dev::step_p61(s);
           if (first + (uint32_t)i < len) sum = dev::addmod64(sum, s, n);
         }
       }
@@ -337,8 +337,8 @@ __device__ void wave_prefix64_pair(const SkipTables &T, uint64_t x, uint64_t y, 
   const uint32_t first = lane * kRun64;
 #pragma unroll 4
   for (int k = 0; k < kRun64; ++k) {
-    sx = dev::mulmod_p61(kA64, sx);
-    sy = dev::mulmod_p61(kA64, sy);
+    sx = dev::step_p61(sx);
+    sy = dev::step_p61(sy);
     if (first + (uint32_t)k < rx) sumx = dev::addmod64(sumx, sx, n);
     if (first + (uint32_t)k < ry) sumy = dev::addmod64(sumy, sy, n);
   }
@@ -435,7 +435,7 @@ __global__ void __launch_bounds__(kScanThreads) scan64_kernel(GenArgs A) {
       tot = dev::addmod64(tot, v[q], n);
     }
     // exclusive prefix of the thread totals over the workgroup
-    const uint64_t ex = dev::wave_exclusive_mod(tot, n, lane);
+    const uint64_t ex = dev::wave_exclusive_mod(tot, n);
     if (lane == 63) wtot[w] = dev::addmod64(ex, tot, n);
     __syncthreads();
     uint64_t before = carry, all = carry;
@@ -642,8 +642,20 @@ __device__ void run_chunk32(const GenArgs &A, const InstRec &I, const ReqRec &R,
 struct Enc64 {
   uint64_t n, ninv, kc, e;
   int ebits;
-  double den, rcp;
+  double den, rcp, rcp_lo;
 };
+
+// Ciphertext and uniform of one message of a width-64 tile (x = n - m).
+template <int EK, int OUT>
+__device__ __forceinline__ void emit64(uint64_t x, const Enc64 &K, uint64_t *c64, double *rr) {
+  if constexpr (OUT & kOutC) {
+    const uint64_t c = dev::encrypt64<EK>(x, K.n, K.ninv, K.kc, K.e, K.ebits);
+    *c64 = c;
+    if constexpr (OUT & kOutR) *rr = dev::uniform64(c + 1, K.den, K.rcp, K.rcp_lo);
+  } else {
+    *rr = dev::uniform64(dev::encrypt64<EK, 1>(x, K.n, K.ninv, K.kc, K.e, K.ebits), K.den, K.rcp, K.rcp_lo);
+  }
+}
 
 // Pass C, width 64: draw t = i*64 + lane lives at LDS row t / 16, column
 // t % 16, i.e. row 4 i + lane / 16.  MASKED tiles write only t_lo <= t < t_hi.
@@ -654,11 +666,9 @@ __device__ __forceinline__ void passC64(const uint64_t *L, uint32_t lane, const 
   const uint32_t span = t_hi - t_lo;
 #pragma unroll UNROLL
   for (int i = 0; i < kRun64; ++i) {
-    const uint64_t m = src[i * 4 * kRow64];
+    const uint64_t x = src[i * 4 * kRow64];
     if (!MASKED || ((uint32_t)i * 64u + lane - t_lo < span)) {
-      const uint64_t c = dev::encrypt64<EK>(m, K.n, K.ninv, K.kc, K.e, K.ebits);
-      if (OUT & kOutC) c64[i * 64] = c;
-      if (OUT & kOutR) rr[i * 64] = dev::uniform64(c, K.den, K.rcp);
+      emit64<EK, OUT>(x, K, c64 + i * 64, rr + i * 64);
     }
   }
 }
@@ -695,7 +705,6 @@ __device__ void run_chunk64(const GenArgs &A, const InstRec &I, const ReqRec &R,
   const uint64_t n = I.n, ninv = I.ninv, kc = I.kcorr;
   const uint64_t e = I.e;
   const int ebits = (int)I.ebits, ekind = (int)I.ekind;
-  const double den = I.den;
   const uint64_t lane_mul = A.lanemul->m64[lane];
 
   const uint32_t j_begin = (uint32_t)chunk * A.tiles_per_chunk;
@@ -704,7 +713,8 @@ __device__ void run_chunk64(const GenArgs &A, const InstRec &I, const ReqRec &R,
   // draw t of tile j is request draw (first draw of tile j) + t; at table
   // entries the first tile starts x mod 1024 draws before the request
   const uint32_t head = tab ? (uint32_t)(R.x & (kTab64Stride - 1)) : 0u;
-  uint64_t m_t = dev::uniform_u64(dev::const_load(A.t64.m + R.g1 + j_begin));
+  // messages are carried as x = n - m (the encryption takes the sign back)
+  uint64_t x_t = n - dev::uniform_u64(dev::const_load(A.t64.m + R.g1 + j_begin));
   uint64_t s_t = dev::uniform_u64(dev::const_load(A.t64.s + R.g1 + j_begin));
   for (uint32_t j = j_begin; j < j_end; ++j) {
     // ---- pass A
@@ -714,26 +724,26 @@ __device__ void run_chunk64(const GenArgs &A, const InstRec &I, const ReqRec &R,
     uint64_t g1 = 0, g2 = 0;
 #pragma unroll 4
     for (int i = 0; i < kRun64 / 2; ++i) {
-      s = dev::mulmod_p61(kA64, s);
+      s = dev::step_p61(s);
       row[i] = s;
       g1 += s;
     }
 #pragma unroll 4
     for (int i = kRun64 / 2; i < kRun64; ++i) {
-      s = dev::mulmod_p61(kA64, s);
+      s = dev::step_p61(s);
       row[i] = s;
       g2 += s;
     }
     const uint64_t sum = dev::addmod64(dev::mod_below_4n(g1, n), dev::mod_below_4n(g2, n), n);
     // ---- pass B
-    uint64_t m = dev::addmod64(m_t, dev::wave_exclusive_mod(sum, n, lane), n);
+    uint64_t x = dev::submod64(x_t, dev::wave_exclusive_mod(sum, n), n);
 #pragma unroll 4
     for (int i = 0; i < kRun64; ++i) {
-      m = dev::addmod64(m, row[i], n);
-      row[i] = m;
+      x = dev::submod64(x, row[i], n);
+      row[i] = x;
     }
-    m_t = dev::shfl_u64(m, 63);
-    s_t = dev::shfl_u64(s, 63);
+    x_t = dev::lane_u64<63>(x);
+    s_t = dev::lane_u64<63>(s);
     dev::wave_lds_sync();
     // ---- pass C
     const uint32_t t_lo = j == 0 ? head : 0u;
@@ -741,7 +751,7 @@ __device__ void run_chunk64(const GenArgs &A, const InstRec &I, const ReqRec &R,
     const int64_t base = (int64_t)R.out_off + (int64_t)j * kTile64 - (int64_t)head + (int64_t)lane;
     uint64_t *c64 = A.out_c64 ? A.out_c64 + base : nullptr;
     double *rr = A.out_r ? A.out_r + base : nullptr;
-    const Enc64 K{n, ninv, kc, e, ebits, den, I.rcp};
+    const Enc64 K{n, ninv, kc, e, ebits, I.den, I.rcp, I.rcp_lo};
     if (t_lo == 0 && t_hi == (uint32_t)kTile64)
       passC64_e<UNROLL, false>(ekind, L, lane, K, c64, rr, 0u, t_hi);
     else
@@ -819,17 +829,15 @@ __device__ void run_chunk32_cs(const GenArgs &A, const InstRec &I, const ReqRec 
 }
 
 template <int UNROLL, int EK, int OUT, bool MASKED>
-__device__ __forceinline__ void passCS64(uint64_t m, uint64_t step, uint32_t lane, const Enc64 &K, uint64_t *c64,
+__device__ __forceinline__ void passCS64(uint64_t x, uint64_t step, uint32_t lane, const Enc64 &K, uint64_t *c64,
                                          double *rr, uint32_t t_lo, uint32_t t_hi) {
   const uint32_t span = t_hi - t_lo;
 #pragma unroll UNROLL
   for (int i = 0; i < kTileCS / 64; ++i) {
     if (!MASKED || ((uint32_t)i * 64u + lane - t_lo < span)) {
-      const uint64_t c = dev::encrypt64<EK>(m, K.n, K.ninv, K.kc, K.e, K.ebits);
-      if (OUT & kOutC) c64[i * 64] = c;
-      if (OUT & kOutR) rr[i * 64] = dev::uniform64(c, K.den, K.rcp);
+      emit64<EK, OUT>(x, K, c64 + i * 64, rr + i * 64);
     }
-    m = dev::addmod64(m, step, K.n);
+    x = dev::submod64(x, step, K.n);
   }
 }
 
@@ -856,7 +864,7 @@ __device__ __forceinline__ void passCS64_e(int ekind, uint64_t m, uint64_t step,
 template <int UNROLL>
 __device__ void run_chunk64_cs(const GenArgs &A, const InstRec &I, const ReqRec &R, uint64_t chunk, uint32_t lane) {
   const uint64_t n = I.n, ninv = I.ninv;
-  const Enc64 K{n, ninv, I.kcorr, I.e, (int)I.ebits, I.den, I.rcp};
+  const Enc64 K{n, ninv, I.kcorr, I.e, (int)I.ebits, I.den, I.rcp, I.rcp_lo};
   const uint64_t g_begin = R.g1 + chunk * A.tiles_per_chunk;
   const uint64_t g_end = min(g_begin + A.tiles_per_chunk, R.g1 + R.ntiles);
   for (uint64_t g = g_begin; g < g_end; ++g) {
@@ -864,7 +872,7 @@ __device__ void run_chunk64_cs(const GenArgs &A, const InstRec &I, const ReqRec 
     dev::W128 v;
     v.lo = x0 + 1 + lane;  // hi word 0 < n, so REDC applies
     v.hi = 0;
-    const uint64_t m = dev::addmod64(I.mbase, dev::mont64(dev::redc64(v, n, ninv), I.bR2, n, ninv), n);
+    const uint64_t m = n - dev::addmod64(I.mbase, dev::mont64(dev::redc64(v, n, ninv), I.bR2, n, ninv), n);
     const uint64_t req_end = R.x + R.count;
     const uint32_t t_lo = R.x > x0 ? (uint32_t)(R.x - x0) : 0u;
     const uint32_t t_hi = (uint32_t)min(req_end - x0, (uint64_t)kTileCS);

@@ -44,7 +44,7 @@ constexpr uint64_t kTab64Range = 1ull << 34;
 struct alignas(128) InstRec {
   uint64_t n;      // prime modulus
   uint64_t ninv;   // n^{-1} mod 2^W (W = 32 or 64)
-  uint64_t kcorr;  // R^e mod n, R = 2^W; width 32: -R^e mod n (the kernels carry n - m)
+  uint64_t kcorr;  // -R^e mod n, R = 2^W (the kernels carry n - m)
   uint64_t r2;     // R^2 mod n
   uint64_t br2;    // (p(p-1)/2 mod n) * R^2 mod n (width 32)
   uint64_t mbase;  // width 32: m at internal index x is mbase + q b + U(r) mod n; constant skip: m_0

@@ -323,7 +323,7 @@ struct phprng_ctx {
     } else {
       rec.ninv = M.ninv;
       rec.r2 = M.r2;
-      rec.kcorr = M.powmod(M.r1, h.e);
+      rec.kcorr = h.n - M.powmod(M.r1, h.e);
       rec.br2 = 0;
       rec.den = (double)(h.n + 1);
       rec.rcp = 1.0 / rec.den;
