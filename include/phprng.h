@@ -195,7 +195,7 @@ phprng_status phprng_generate(phprng_ctx *ctx, const phprng_request *reqs, uint6
 /* For callers that cannot allocate (code under HIP graph capture, tight
  * serving loops, harnesses that forbid allocation): phprng_generate in
  * persistent mode that calls no hipMalloc, hipFree or other allocating
- * routine.  Its device scratch (the planned requests, the work counter and
+ * routine.  Its device scratch (the planned requests, the work counters and
  * the width-64 tile state) is one fixed array per device, about 7.3 MB, held
  * until the process ends; its host staging buffer is allocated when the
  * context is created.  Limits: at most 16384 requests and 2^18 width-64

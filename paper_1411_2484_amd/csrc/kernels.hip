@@ -908,20 +908,35 @@ __global__ void __launch_bounds__(BLOCK) gen_persistent(GenArgs A) {
   const uint32_t wave = dev::uniform_u32(threadIdx.x / 64);  // wave-uniform: keeps chunk math scalar
   uint64_t *L = lds[wave];
   const uint64_t total = dev::uniform_u64(dev::const_load(&A.hdr->total_chunks));
-  // The first chunk of every wave is its global wave index; later chunks come
-  // from the shared counter, offset by the number of waves.  Small batches
+  // The blocks of group g take the chunks g, g + ngroups, g + 2 ngroups, ...:
+  // chunk k of the group is chunk g + k ngroups of the batch.  The first chunk
+  // of every wave is its index among the group's waves; later chunks come from
+  // the group's counter, offset by the number of its waves.  Small batches
   // therefore need no atomics, and large ones avoid the start-up burst.
-  const uint32_t nwaves = gridDim.x * (BLOCK / 64);
-  uint64_t c = (uint64_t)blockIdx.x * (BLOCK / 64) + wave;
-  // Every wave grabs until a grab fails, so there are total - nwaves
+  // A large batch keeps one group: its chunks are long enough that one
+  // counter keeps up, and it hands them out in the order of their output, which
+  // writes memory 1 to 2.5% faster (2048 ragged streams, c + R: 2623 against
+  // 2690 us; 4096 x 2^18 uniforms: 1615 against 1637 us).  Below kOneGroupChunks
+  // chunks per wave the single counter is the bound (116 M draws of 1024
+  // requests: 402 against 233 us; 200 width-64 streams x 300,007: 411 against
+  // 275 us).
+  const uint32_t ngroups =
+      total >= (uint64_t)kOneGroupChunks * gridDim.x * (BLOCK / 64) ? 1u : min(gridDim.x, kWorkGroups);
+  const uint32_t g = blockIdx.x % ngroups;
+  const uint32_t nwaves = ((gridDim.x - g + ngroups - 1) / ngroups) * (BLOCK / 64);
+  const uint64_t mine = total > g ? (total - g + ngroups - 1) / ngroups : 0;
+  uint64_t k = (uint64_t)(blockIdx.x / ngroups) * (BLOCK / 64) + wave;
+  // Every wave grabs until a grab fails, so there are mine - nwaves
   // successful grabs and one failed grab per wave: the grabs return
-  // 0 .. total - 1, and the one returning total - 1 is the last of all.  Its
-  // wave puts the counter back to zero for the next launch.  A batch with no
-  // more chunks than waves never touches the counter.  (One call site of
+  // 0 .. mine - 1, and the one returning mine - 1 is the last of all.  Its
+  // wave puts the counter back to zero for the next launch.  A group with no
+  // more chunks than waves never touches its counter.  (One call site of
   // run_chunk: a second one gets the whole chunk code outlined into a call.)
-  const bool grab = total > nwaves;
+  const bool grab = mine > nwaves;
+  uint32_t *const counter = &A.ctr->group[g].counter;
   for (;;) {
-    if (c >= total) break;
+    if (k >= mine) break;
+    const uint64_t c = g + k * ngroups;
     const uint64_t r =
         dev::uniform_u64(wave_search(A.nreq, c, lane, [&](uint64_t i) { return A.req[i].chunk_base; }));
     const ReqRec R = dev::const_load(A.req + r);
@@ -929,10 +944,10 @@ __global__ void __launch_bounds__(BLOCK) gen_persistent(GenArgs A) {
     if (!grab) break;
     uint32_t next = 0;
     if (lane == 0) {
-      next = atomicAdd(&A.ctr->counter, 1u);
-      if ((uint64_t)next == total - 1) __hip_atomic_store(&A.ctr->counter, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      next = atomicAdd(counter, 1u);
+      if ((uint64_t)next == mine - 1) __hip_atomic_store(counter, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
-    c = (uint64_t)nwaves + dev::uniform_u32((uint32_t)__shfl((int)next, 0, 64));
+    k = (uint64_t)nwaves + dev::uniform_u32((uint32_t)__shfl((int)next, 0, 64));
   }
 }
 

@@ -8,13 +8,13 @@
 namespace phprng {
 
 // Fixed device scratch of the allocation-free entry point (one per device):
-// the work counter, the batch header, the planned requests and the width-64
+// the work counters, the batch header, the planned requests and the width-64
 // tile state, at these byte offsets.
 constexpr int kMaxDevices = 64;
 constexpr uint64_t kNoAllocMaxRequests = 16384;
 constexpr uint64_t kNoAllocMaxTiles64 = 1ull << 18;
 constexpr uint64_t kScratchCtrOff = 0;
-constexpr uint64_t kScratchReqOff = 256;
+constexpr uint64_t kScratchReqOff = sizeof(WorkCtr) + 256;
 constexpr uint64_t kScratchHdrOff = kScratchReqOff - sizeof(BatchHdr);  // header right before the requests
 constexpr uint64_t kScratchTileOff = kScratchReqOff + kNoAllocMaxRequests * sizeof(ReqRec);
 constexpr uint64_t kScratchBytes = kScratchTileOff + 3 * kNoAllocMaxTiles64 * sizeof(uint64_t);

@@ -106,12 +106,22 @@ struct alignas(64) BatchHdr {
 };
 static_assert(sizeof(BatchHdr) == 64, "BatchHdr must be 64 bytes");
 
-// Work-stealing counter of the generation kernel: zero when a launch starts;
-// the wave that makes the launch's last grab sets it back to zero.
+// Work counters of the generation kernel.  One address serves about 9e7 grabs
+// a second, so a batch of many short chunks is cut into kWorkGroups groups:
+// the blocks b with the same b mod kWorkGroups share one counter (its own
+// 64-byte line) and the chunks c with the same c mod kWorkGroups, so that the
+// interleaved shares hold every request in equal parts.  Batches of at least
+// kOneGroupChunks chunks per wave keep one group.  Each counter is zero when a
+// launch starts; the wave that makes its last grab sets it back.
+constexpr uint32_t kOneGroupChunks = 10;
+constexpr uint32_t kWorkGroups = 64;  // a multiple of the 8 XCDs: a group's blocks share an L2
 struct alignas(64) WorkCtr {
-  uint32_t counter;
-  uint32_t pad[15];
+  struct alignas(64) {
+    uint32_t counter;
+    uint32_t pad[15];
+  } group[kWorkGroups];
 };
+static_assert(sizeof(WorkCtr) == 64 * kWorkGroups, "one line per counter");
 
 // Width-64 tile state of a batch: skip and message before each tile, and
 // the sum of the tile's skips mod n.
