@@ -90,6 +90,21 @@ void fourier_law(double *p) {
   p[kFourierCats - 1] = p[0];
 }
 
+// chi^2 of `total` samples over `cells` equally likely cells from the exact
+// sum of squared counts: (cells sum O^2 - total^2) / total.  The integer
+// numerator is exact while it fits 128 bits (any histogram of fewer than 2^53
+// samples); beyond, long double.
+double equal_cells_chi2(uint64_t total, unsigned __int128 sq, uint32_t cells) {
+  if (total == 0) return 0;
+  if (total < (1ull << 53)) {
+    const unsigned __int128 num = sq * cells - (unsigned __int128)total * total;
+    return (double)((long double)num / (long double)total);
+  }
+  return (double)((long double)sq / (long double)total * cells - (long double)total);
+}
+
+constexpr uint32_t kReportMoments = kPartTests * kMomentSlices;
+
 struct Pending {
   int cls;
   hipEvent_t a, b;
@@ -110,10 +125,12 @@ struct phprng_battery {
   uint64_t *d_bits = nullptr;
   double2 *d_y = nullptr;
   double2 *d_tw = nullptr;  // w1024 | fineN | fineM
-  double *d_probs = nullptr;  // poker | collision | runs | fourier
-  Chi2Job *d_jobs = nullptr;
-  double *d_chi2 = nullptr;
-  unsigned long long *d_total = nullptr;
+  std::vector<double> probs;  // poker | collision | runs | fourier
+  // report: per-slice moments of the large histograms, then the small
+  // histograms, written by the device into mapped host memory
+  void *h_report = nullptr;
+  Moments *report_moments = nullptr;            // device addresses of the two parts
+  unsigned long long *report_small = nullptr;
   unsigned long long *d_discard = nullptr;  // Fourier category replicas of phprng_battery_fourier calls
   // per-workgroup replicas [kRep][categories] of the small histograms
   unsigned long long *d_rep = nullptr;
@@ -215,20 +232,22 @@ phprng_status phprng_battery_create(phprng_battery **out, int device) {
   uint64_t total = 0;
   for (int t = 0; t < PHPRNG_TEST_COUNT; ++t) total += kCats[t];
   const uint64_t nprob = kPokerCats + kCollCats + kRunsCats + kFourierCats;
+  void *report_dev = nullptr;
   bool ok = hipMalloc(&b->d_hist, total * sizeof(unsigned long long)) == hipSuccess &&
             hipMalloc(&b->d_bits, kChunkBlocks * kWordsPerBlock * sizeof(uint64_t)) == hipSuccess &&
             hipMalloc(&b->d_y, kChunkBlocks * (uint64_t)kFftN * sizeof(double2)) == hipSuccess &&
             hipMalloc(&b->d_tw, 3 * 1024 * sizeof(double2)) == hipSuccess &&
-            hipMalloc(&b->d_probs, nprob * sizeof(double)) == hipSuccess &&
-            hipMalloc(&b->d_jobs, PHPRNG_TEST_COUNT * sizeof(Chi2Job)) == hipSuccess &&
-            hipMalloc(&b->d_chi2, PHPRNG_TEST_COUNT * sizeof(double)) == hipSuccess &&
-            hipMalloc(&b->d_total, PHPRNG_TEST_COUNT * sizeof(unsigned long long)) == hipSuccess &&
+            hipHostMalloc(&b->h_report, kReportMoments * sizeof(Moments) + nprob * sizeof(uint64_t),
+                          hipHostMallocMapped | hipHostMallocCoherent) == hipSuccess &&
+            hipHostGetDevicePointer(&report_dev, b->h_report, 0) == hipSuccess &&
             hipMalloc(&b->d_discard, kRep * kFourierCats * sizeof(unsigned long long)) == hipSuccess &&
             hipMalloc(&b->d_rep, kRep * nprob * sizeof(unsigned long long)) == hipSuccess;
   if (!ok) {
     phprng_battery_destroy(b);
     return PHPRNG_E_NOMEM;
   }
+  b->report_moments = static_cast<Moments *>(report_dev);
+  b->report_small = reinterpret_cast<unsigned long long *>(b->report_moments + kReportMoments);
   uint64_t off = 0;
   for (int t = 0; t < PHPRNG_TEST_COUNT; ++t) {
     b->d_cat[t] = b->d_hist + off;
@@ -285,20 +304,12 @@ phprng_status phprng_battery_create(phprng_battery **out, int device) {
     tw[1024 + t] = make_double2((double)cosl(a1), (double)sinl(a1));
     tw[2048 + t] = make_double2((double)cosl(a2), (double)sinl(a2));
   }
-  std::vector<double> probs(nprob);
-  poker_law(probs.data());
-  collision_law(probs.data() + kPokerCats);
-  runs_law(probs.data() + kPokerCats + kCollCats);
-  fourier_law(probs.data() + kPokerCats + kCollCats + kRunsCats);
-  Chi2Job jobs[PHPRNG_TEST_COUNT];
-  for (int t = 0; t < PHPRNG_TEST_COUNT; ++t) jobs[t] = Chi2Job{b->d_cat[t], nullptr, kCats[t], 0};
-  jobs[PHPRNG_TEST_POKER].probs = b->d_probs;
-  jobs[PHPRNG_TEST_COLLISION].probs = b->d_probs + kPokerCats;
-  jobs[PHPRNG_TEST_RUNS].probs = b->d_probs + kPokerCats + kCollCats;
-  jobs[PHPRNG_TEST_FOURIER].probs = b->d_probs + kPokerCats + kCollCats + kRunsCats;
+  b->probs.resize(nprob);
+  poker_law(b->probs.data());
+  collision_law(b->probs.data() + kPokerCats);
+  runs_law(b->probs.data() + kPokerCats + kCollCats);
+  fourier_law(b->probs.data() + kPokerCats + kCollCats + kRunsCats);
   if (hipMemcpy(b->d_tw, tw.data(), tw.size() * sizeof(double2), hipMemcpyHostToDevice) != hipSuccess ||
-      hipMemcpy(b->d_probs, probs.data(), nprob * sizeof(double), hipMemcpyHostToDevice) != hipSuccess ||
-      hipMemcpy(b->d_jobs, jobs, sizeof jobs, hipMemcpyHostToDevice) != hipSuccess ||
       hipMemset(b->d_hist, 0, total * sizeof(unsigned long long)) != hipSuccess ||
       hipMemset(b->d_rep, 0, kRep * nprob * sizeof(unsigned long long)) != hipSuccess ||
       hipMemset(b->d_discard, 0, kRep * kFourierCats * sizeof(unsigned long long)) != hipSuccess) {
@@ -316,11 +327,12 @@ phprng_status phprng_battery_destroy(phprng_battery *b) {
   (void)hipSetDevice(b->device);
   resolve(b, true);
   for (hipEvent_t e : b->free_events) (void)hipEventDestroy(e);
-  void *bufs[] = {b->d_hist,  b->d_bits,  b->d_y,      b->d_tw,     b->d_probs,   b->d_jobs,   b->d_chi2,
-                  b->d_total, b->d_discard, b->d_pdata, b->d_pfill, b->d_pncell, b->d_pslices, b->d_phist,
+  void *bufs[] = {b->d_hist,   b->d_bits,  b->d_y,      b->d_tw,      b->d_discard,
+                  b->d_pdata,  b->d_pfill, b->d_pncell, b->d_pslices, b->d_phist,
                   b->d_rep};
   for (void *p : bufs)
     if (p) (void)hipFree(p);
+  if (b->h_report) (void)hipHostFree(b->h_report);
   delete b;
   return PHPRNG_OK;
 }
@@ -373,10 +385,15 @@ phprng_status phprng_battery_accumulate(phprng_battery *b, const double *r, uint
   }
   // the small histograms' replicas into their histograms
   if (nblocks) {
-    for (int t : {PHPRNG_TEST_POKER, PHPRNG_TEST_COLLISION, PHPRNG_TEST_RUNS, PHPRNG_TEST_FOURIER}) {
-      hipError_t e = launch_fold(b->rep[t], b->d_cat[t], kCats[t], st);
-      if (e != hipSuccess) return hip_fail(b, e, "fold");
+    SmallHists S{};
+    const int tests[kSmallTests] = {PHPRNG_TEST_POKER, PHPRNG_TEST_COLLISION, PHPRNG_TEST_RUNS, PHPRNG_TEST_FOURIER};
+    for (int i = 0; i < kSmallTests; ++i) {
+      S.rep[i] = b->rep[tests[i]];
+      S.dst[i] = b->d_cat[tests[i]];
+      S.ncat[i] = kCats[tests[i]];
     }
+    const hipError_t e = launch_fold(S, st);
+    if (e != hipSuccess) return hip_fail(b, e, "fold");
   }
   return PHPRNG_OK;
 }
@@ -402,20 +419,47 @@ phprng_status phprng_battery_report(phprng_battery *b, phprng_test_result *out, 
   if (!b || !out) return PHPRNG_E_INVALID;
   (void)hipSetDevice(b->device);
   hipStream_t st = (hipStream_t)stream;
-  hipError_t e = launch_chi2(b->d_jobs, PHPRNG_TEST_COUNT, b->d_chi2, b->d_total, st);
-  double chi2[PHPRNG_TEST_COUNT];
-  unsigned long long tot[PHPRNG_TEST_COUNT];
-  if (e == hipSuccess) e = hipMemcpyAsync(chi2, b->d_chi2, sizeof chi2, hipMemcpyDeviceToHost, st);
-  if (e == hipSuccess) e = hipMemcpyAsync(tot, b->d_total, sizeof tot, hipMemcpyDeviceToHost, st);
+  MomentJobs J{};
+  for (int t = 0; t < kPartTests; ++t) {
+    J.counts[t] = b->d_cat[PHPRNG_TEST_FREQUENCY + t];
+    J.ncat[t] = kCats[PHPRNG_TEST_FREQUENCY + t];
+  }
+  J.small = b->d_cat[PHPRNG_TEST_POKER];
+  J.nsmall = (uint32_t)b->probs.size();
+  hipError_t e = launch_moments(J, b->report_moments, b->report_small, st);
   if (e == hipSuccess) e = hipStreamSynchronize(st);
   if (e != hipSuccess) return hip_fail(b, e, "report");
+  const Moments *mom = static_cast<const Moments *>(b->h_report);
+  const uint64_t *small = reinterpret_cast<const uint64_t *>(mom + kReportMoments);
+  const double *probs = b->probs.data();
   for (int t = 0; t < PHPRNG_TEST_COUNT; ++t) {
-    out[t].chi2 = chi2[t];
-    out[t].samples = tot[t];
+    uint64_t tot = 0;
+    double chi2 = 0;
+    if (t < kPartTests) {
+      unsigned __int128 sq = 0;
+      for (uint32_t i = 0; i < kMomentSlices; ++i) {
+        const Moments &m = mom[(uint32_t)t * kMomentSlices + i];
+        tot += m.sum;
+        sq += ((unsigned __int128)m.sq_hi << 64) | m.sq_lo;
+      }
+      chi2 = equal_cells_chi2(tot, sq, kCats[t]);
+    } else {
+      const uint32_t n = kCats[t];
+      for (uint32_t i = 0; i < n; ++i) tot += small[i];
+      for (uint32_t i = 0; i < n; ++i) {
+        const double ex = (double)tot * probs[i];
+        const double d = (double)small[i] - ex;
+        chi2 += d * d / ex;
+      }
+      small += n;
+      probs += n;
+    }
+    out[t].samples = tot;
     out[t].dof = kCats[t] - 1;
     double P = 0, Q = 0;
-    if (tot[t]) {
-      phprng::gamma_pq(0.5 * (double)out[t].dof, 0.5 * chi2[t], &P, &Q);
+    if (tot) {
+      out[t].chi2 = chi2;
+      phprng::gamma_pq(0.5 * (double)out[t].dof, 0.5 * chi2, &P, &Q);
       out[t].p_value = P < Q ? P : Q;
     } else {
       out[t].p_value = 0;

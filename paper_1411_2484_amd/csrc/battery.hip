@@ -193,69 +193,77 @@ __global__ __launch_bounds__(1024) void collision_kernel(const double *__restric
   }
 }
 
-// One thread per 64-bit word of run bits: every run that starts in the word
-// (a position whose bit differs from its predecessor's) is measured up to the
-// next change, scanning later words of the block if needed; runs that reach
-// the end of the block, and the block's first run, are not interior and are
-// not counted.
-__global__ __launch_bounds__(256) void runs_kernel(const uint64_t *__restrict__ bits, uint64_t nwords,
-                                                   unsigned long long *hist) {
+// Sum of v over the wave, in lane 63 (all lanes active).
+__device__ __forceinline__ uint32_t wave_total(uint32_t v) {
+  v += __builtin_amdgcn_update_dpp(0, (int)v, 0x111, 0xf, 0xf, false);  // row_shr:1
+  v += __builtin_amdgcn_update_dpp(0, (int)v, 0x112, 0xf, 0xf, false);  // row_shr:2
+  v += __builtin_amdgcn_update_dpp(0, (int)v, 0x114, 0xf, 0xf, false);  // row_shr:4
+  v += __builtin_amdgcn_update_dpp(0, (int)v, 0x118, 0xf, 0xf, false);  // row_shr:8
+  v += __builtin_amdgcn_update_dpp(0, (int)v, 0x142, 0xa, 0xf, false);  // row_bcast:15
+  v += __builtin_amdgcn_update_dpp(0, (int)v, 0x143, 0xc, 0xf, false);  // row_bcast:31
+  return v;
+}
+
+// Interior runs: kRunsWords 64-bit words of run bits per thread, 256 words
+// apart.  Position i of the block changes when its bit differs from the one
+// before; a run starts at a change and ends at the next one, so the starts
+// whose next L positions do not change are t & ~(ch >> 1) & ... & ~(ch >> L),
+// counted with two population counts per L for all 64 positions at once
+// (measuring run by run took 65 us per 2^26 uniforms, this 13).  The block's
+// first position never changes, and its last change starts a run that the
+// block's end cuts: neither is counted.
+constexpr uint32_t kRunsWords = 4;
+__global__ __launch_bounds__(256) void runs_kernel(const uint64_t *__restrict__ bits, unsigned long long *hist) {
+  static_assert(kRunsMax < 32, "the look-ahead is the low half of the next word's changes");
+  static_assert(kWordsPerBlock % (256 * kRunsWords) == 0, "a workgroup's words lie in one block");
   __shared__ uint32_t h[kRunsCats];
   if (threadIdx.x < kRunsCats) h[threadIdx.x] = 0;
   __syncthreads();
-  const uint64_t w = (uint64_t)blockIdx.x * 256 + threadIdx.x;
-  // Runs of length 1..8 (all but 0.4% of them) are counted in registers, four
-  // 16-bit fields per word (lengths 1-4 in lo4, 5-8 in hi4; at most 64 runs
-  // start in a word, and a wave's sums stay below 2^16); longer runs go to the
-  // LDS histogram.  An LDS atomic per run queued on the few short-run bins.
-  uint64_t lo4 = 0, hi4 = 0;
-  if (w < nwords) {
-    const uint32_t wi = (uint32_t)(w & (kWordsPerBlock - 1));
-    const uint64_t word = bits[w];
-    const uint64_t prev = wi ? (bits[w - 1] >> 63) : (word & 1);
-    uint64_t ch = word ^ ((word << 1) | prev);
-    while (ch) {
-      const uint32_t i = __builtin_ctzll(ch);
-      ch &= ch - 1;
-      uint32_t len = 0;
-      if (ch) {
-        len = __builtin_ctzll(ch) - i;
-      } else {
-        uint32_t run = 64 - i;
-        uint64_t pw = word;
-        bool found = false;
-        for (uint32_t wj = wi + 1; wj < kWordsPerBlock; ++wj) {
-          const uint64_t nw = bits[w + (wj - wi)];
-          const uint64_t c2 = nw ^ ((nw << 1) | (pw >> 63));
-          if (c2) {
-            len = run + __builtin_ctzll(c2);
-            found = true;
-            break;
-          }
-          run += 64;
-          pw = nw;
-        }
-        if (!found) break;
+  uint64_t word[kRunsWords], next[kRunsWords];
+  uint32_t prev[kRunsWords], wi[kRunsWords];
+  const uint64_t w0 = (uint64_t)blockIdx.x * (256 * kRunsWords) + threadIdx.x;
+#pragma unroll
+  for (uint32_t k = 0; k < kRunsWords; ++k) {
+    const uint64_t w = w0 + 256 * k;
+    wi[k] = (uint32_t)(w & (kWordsPerBlock - 1));
+    word[k] = bits[w];
+    prev[k] = wi[k] ? (uint32_t)(bits[w - 1] >> 63) : (uint32_t)word[k] & 1;
+    next[k] = wi[k] + 1 < kWordsPerBlock ? bits[w + 1] : 0;
+  }
+  uint32_t cnt[kRunsMax + 1] = {};  // cnt[L]: starts whose next L positions do not change
+#pragma unroll
+  for (uint32_t k = 0; k < kRunsWords; ++k) {
+    uint64_t ch = word[k] ^ ((word[k] << 1) | prev[k]);
+    uint64_t ahead = wi[k] + 1 < kWordsPerBlock ? next[k] ^ ((next[k] << 1) | (word[k] >> 63)) : 0;
+    uint64_t t = ch;
+    if (ch && !ahead) {
+      // no change in the next word: is there any later one in the block?
+      bool later = false;
+      uint64_t pw = next[k];
+      for (uint32_t wj = wi[k] + 2; wj < kWordsPerBlock && !later; ++wj) {
+        const uint64_t nw = bits[w0 + 256 * k + (wj - wi[k])];
+        later = (nw ^ ((nw << 1) | (pw >> 63))) != 0;
+        pw = nw;
       }
-      if (len <= 4)
-        lo4 += 1ull << (16 * (len - 1));
-      else if (len <= 8)
-        hi4 += 1ull << (16 * (len - 5));
-      else
-        atomicAdd(&h[(len < kRunsCats ? len : kRunsCats) - 1], 1u);
+      if (!later) t &= ~(1ull << (63 - __builtin_clzll(ch)));
+    }
+    uint32_t look = (uint32_t)ahead;
+    cnt[0] += (uint32_t)__popcll(t);
+#pragma unroll
+    for (uint32_t L = 1; L <= kRunsMax; ++L) {
+      ch = (ch >> 1) | ((uint64_t)look << 63);
+      look >>= 1;
+      t &= ~ch;
+      cnt[L] += (uint32_t)__popcll(t);
     }
   }
 #pragma unroll
-  for (int d = 32; d > 0; d >>= 1) {
-    lo4 += shfl_xor_u64(lo4, d);
-    hi4 += shfl_xor_u64(hi4, d);
-  }
-  if ((threadIdx.x & 63) == 0) {
-#pragma unroll
-    for (int b = 0; b < 4; ++b) {
-      const uint32_t a = (uint32_t)(lo4 >> (16 * b)) & 0xffffu, c = (uint32_t)(hi4 >> (16 * b)) & 0xffffu;
-      if (a) atomicAdd(&h[b], a);
-      if (c) atomicAdd(&h[4 + b], c);
+  for (uint32_t L = 0; L <= kRunsMax; ++L) {
+    const uint32_t tot = wave_total(cnt[L]);
+    // cnt[L - 1] - cnt[L] runs have length L; the last category holds the rest
+    if ((threadIdx.x & 63) == 63 && tot) {
+      atomicAdd(&h[L], tot);
+      if (L > 0) atomicSub(&h[L - 1], tot);
     }
   }
   __syncthreads();
@@ -462,49 +470,69 @@ __global__ __launch_bounds__(128) void fft_pass2_self_kernel(const double2 *__re
     atomicAdd(&hist[(blockIdx.x % kRep) * kFourierCats + threadIdx.x], (unsigned long long)h[threadIdx.x]);
 }
 
-// dst[c] += sum of the kRep replicas of bin c, which are cleared.
-__global__ __launch_bounds__(256) void fold_kernel(unsigned long long *rep, unsigned long long *dst, uint32_t ncat) {
-  const uint32_t c = blockIdx.x * 256 + threadIdx.x;
-  if (c >= ncat) return;
-  unsigned long long s = 0;
-  for (uint32_t r = 0; r < kRep; ++r) {
-    s += rep[(uint64_t)r * ncat + c];
-    rep[(uint64_t)r * ncat + c] = 0;
+// One workgroup per category of the four small histograms: dst[c] += sum of
+// its kRep replicas, which are cleared, one replica per thread (a thread that
+// walked the replicas of its category took 30 us per histogram).
+__global__ __launch_bounds__(kRep) void fold_kernel(SmallHists S) {
+  __shared__ unsigned long long part[kRep / 64];
+  uint32_t c = blockIdx.x, t = 0;
+  while (c >= S.ncat[t]) c -= S.ncat[t++];
+  unsigned long long *const src = S.rep[t] + (uint64_t)threadIdx.x * S.ncat[t] + c;
+  unsigned long long v = *src;
+  *src = 0;
+#pragma unroll
+  for (int d = 1; d < 64; d <<= 1) v += shfl_xor_u64(v, d);
+  if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = v;
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    for (uint32_t i = 1; i < kRep / 64; ++i) v += part[i];
+    if (v) S.dst[t][c] += v;
   }
-  if (s) dst[c] += s;
 }
 
-// One workgroup per test: the total count, then sum (O - E)^2 / E with
-// E = total * probability, in a fixed reduction order.
-__global__ __launch_bounds__(1024) void chi2_kernel(const Chi2Job *jobs, double *chi2, unsigned long long *total) {
-  __shared__ unsigned long long su[1024];
-  __shared__ double sd[1024];
-  const Chi2Job J = jobs[blockIdx.x];
-  unsigned long long s = 0;
-  for (uint32_t i = threadIdx.x; i < J.ncat; i += 1024) s += J.counts[i];
-  su[threadIdx.x] = s;
+// Exact sums of the counts and of their squares over slice blockIdx.x of
+// large histogram blockIdx.y (its cells are equally likely, so these two
+// integers give its chi^2); the workgroups of row kPartTests copy the small
+// histograms.  The results go to host memory.  64 workgroups per histogram
+// read the 42 MB in parallel (one per histogram, which read it twice, took
+// 671 us).
+__global__ __launch_bounds__(256) void moments_kernel(MomentJobs J, Moments *out, unsigned long long *small_out) {
+  if (blockIdx.y == kPartTests) {
+    for (uint32_t i = blockIdx.x * 256 + threadIdx.x; i < J.nsmall; i += kMomentSlices * 256) small_out[i] = J.small[i];
+    return;
+  }
+  const unsigned long long *counts = J.counts[blockIdx.y];
+  const uint32_t n = J.ncat[blockIdx.y];
+  const uint32_t lo = (uint32_t)((uint64_t)n * blockIdx.x / kMomentSlices);
+  const uint32_t hi = (uint32_t)((uint64_t)n * (blockIdx.x + 1) / kMomentSlices);
+  unsigned long long sum = 0;
+  unsigned __int128 sq = 0;
+  constexpr uint32_t kU = 8;  // loads in flight per thread
+  for (uint32_t i0 = lo + threadIdx.x; i0 < hi; i0 += 256 * kU) {
+    unsigned long long o[kU];
+#pragma unroll
+    for (uint32_t u = 0; u < kU; ++u) o[u] = i0 + 256 * u < hi ? counts[i0 + 256 * u] : 0;
+#pragma unroll
+    for (uint32_t u = 0; u < kU; ++u) {
+      sum += o[u];
+      sq += (unsigned __int128)o[u] * o[u];
+    }
+  }
+#pragma unroll
+  for (int d = 1; d < 64; d <<= 1) {
+    sum += shfl_xor_u64(sum, d);
+    const uint64_t l = shfl_xor_u64((uint64_t)sq, d), h = shfl_xor_u64((uint64_t)(sq >> 64), d);
+    sq += ((unsigned __int128)h << 64) | l;
+  }
+  __shared__ Moments part[4];
+  if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = {sum, (uint64_t)sq, (uint64_t)(sq >> 64)};
   __syncthreads();
-  for (int w = 512; w > 0; w >>= 1) {
-    if ((int)threadIdx.x < w) su[threadIdx.x] += su[threadIdx.x + w];
-    __syncthreads();
-  }
-  const double tot = (double)su[0];
-  const double eq = 1.0 / (double)J.ncat;
-  double acc = 0.0;
-  for (uint32_t i = threadIdx.x; i < J.ncat; i += 1024) {
-    const double ex = tot * (J.probs ? J.probs[i] : eq);
-    const double d = (double)J.counts[i] - ex;
-    acc += d * d / ex;
-  }
-  sd[threadIdx.x] = acc;
-  __syncthreads();
-  for (int w = 512; w > 0; w >>= 1) {
-    if ((int)threadIdx.x < w) sd[threadIdx.x] += sd[threadIdx.x + w];
-    __syncthreads();
-  }
   if (threadIdx.x == 0) {
-    chi2[blockIdx.x] = sd[0];
-    total[blockIdx.x] = su[0];
+    for (int w = 1; w < 4; ++w) {
+      sum += part[w].sum;
+      sq += ((unsigned __int128)part[w].sq_hi << 64) | part[w].sq_lo;
+    }
+    out[blockIdx.y * kMomentSlices + blockIdx.x] = {sum, (uint64_t)sq, (uint64_t)(sq >> 64)};
   }
 }
 
@@ -542,7 +570,7 @@ hipError_t launch_collision(const double *r, uint64_t nblocks, unsigned long lon
 hipError_t launch_runs(const uint64_t *bits, uint64_t nblocks, unsigned long long *runs, hipStream_t st) {
   clear_launch_error();
   const uint64_t nwords = nblocks * kWordsPerBlock;
-  runs_kernel<<<dim3((unsigned)((nwords + 255) / 256)), dim3(256), 0, st>>>(bits, nwords, runs);
+  runs_kernel<<<dim3((unsigned)(nwords / (256 * kRunsWords))), dim3(256), 0, st>>>(bits, runs);
   return hipGetLastError();
 }
 
@@ -560,15 +588,17 @@ hipError_t launch_fft_pass2(const double2 *y, uint64_t nblocks, unsigned long lo
   return hipGetLastError();
 }
 
-hipError_t launch_fold(unsigned long long *rep, unsigned long long *dst, uint32_t ncat, hipStream_t st) {
+hipError_t launch_fold(const SmallHists &S, hipStream_t st) {
   clear_launch_error();
-  fold_kernel<<<dim3((ncat + 255) / 256), dim3(256), 0, st>>>(rep, dst, ncat);
+  uint32_t cats = 0;
+  for (uint32_t n : S.ncat) cats += n;
+  fold_kernel<<<dim3(cats), dim3(kRep), 0, st>>>(S);
   return hipGetLastError();
 }
 
-hipError_t launch_chi2(const Chi2Job *jobs, int njobs, double *chi2, unsigned long long *total, hipStream_t st) {
+hipError_t launch_moments(const MomentJobs &J, Moments *out, unsigned long long *small_out, hipStream_t st) {
   clear_launch_error();
-  chi2_kernel<<<dim3(njobs), dim3(1024), 0, st>>>(jobs, chi2, total);
+  moments_kernel<<<dim3(kMomentSlices, kPartTests + 1), dim3(256), 0, st>>>(J, out, small_out);
   return hipGetLastError();
 }
 

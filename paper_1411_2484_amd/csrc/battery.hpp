@@ -58,12 +58,20 @@ struct Twiddles {
   const double2 *w1024, *fineN, *fineM;
 };
 
-struct Chi2Job {
-  const unsigned long long *counts;
-  const double *probs;  // null: equal probabilities 1 / ncat
-  uint32_t ncat;
-  uint32_t pad;
+// The large histograms (equally likely cells) and the small ones, which lie
+// one after the other.
+struct MomentJobs {
+  const unsigned long long *counts[kPartTests];
+  uint32_t ncat[kPartTests];
+  const unsigned long long *small;
+  uint32_t nsmall;
 };
+
+// Sum of counts and of their squares (128 bits).
+struct Moments {
+  uint64_t sum, sq_lo, sq_hi;
+};
+constexpr uint32_t kMomentSlices = 64;
 
 // The small histograms (poker, collision, runs, Fourier categories) take a
 // count from every workgroup.  Global atomics on the same address serialise
@@ -71,6 +79,11 @@ struct Chi2Job {
 // replica blockIdx.x % kRep of the histogram, an array [kRep][categories]
 // that launch_fold sums into the histogram (and clears).
 constexpr uint32_t kRep = 256;
+constexpr int kSmallTests = 4;
+struct SmallHists {
+  unsigned long long *rep[kSmallTests], *dst[kSmallTests];
+  uint32_t ncat[kSmallTests];
+};
 
 hipError_t launch_hist(const double *r, uint64_t nblocks, const ph::PartSet &P, const BatteryParts &bp,
                        unsigned long long *poker_rep, uint64_t *bits, hipStream_t st);
@@ -80,8 +93,9 @@ hipError_t launch_fft_pass1(const double *r, uint64_t nblocks, double2 *y, Twidd
 // coef (may be null): per block, M doubles = (Re, Im) of coefficients 0 .. M/2 - 1.
 hipError_t launch_fft_pass2(const double2 *y, uint64_t nblocks, unsigned long long *fourier_rep, double *coef,
                             Twiddles tw, double scale, hipStream_t st);
-hipError_t launch_fold(unsigned long long *rep, unsigned long long *dst, uint32_t ncat, hipStream_t st);
-hipError_t launch_chi2(const Chi2Job *jobs, int njobs, double *chi2, unsigned long long *total, hipStream_t st);
+hipError_t launch_fold(const SmallHists &S, hipStream_t st);
+// out: [kPartTests][kMomentSlices], small_out: J.nsmall counts, both host memory mapped for the device.
+hipError_t launch_moments(const MomentJobs &J, Moments *out, unsigned long long *small_out, hipStream_t st);
 hipError_t launch_interleave(const double *in, double *out, uint64_t nstreams, uint64_t length, hipStream_t st);
 
 }  // namespace bat
