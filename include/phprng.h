@@ -528,6 +528,16 @@ typedef struct {
  * up to 2^30 keys (at most about 2.8 GB). */
 phprng_status phprng_pattern_histogram(const phprng_pattern *pat, uint64_t *hist, void *stream);
 
+/* The same with caller-owned scratch, for programs that call it often (the
+ * allocation and release of that much memory takes longer than a short
+ * pattern): *bytes receives what phprng_pattern_histogram_ws needs for `pat`;
+ * workspace is device memory of at least that size, 256-byte aligned, free
+ * for use on `stream` until the call returns.  PHPRNG_E_RANGE if it is too
+ * small. */
+phprng_status phprng_pattern_workspace(const phprng_pattern *pat, uint64_t *bytes);
+phprng_status phprng_pattern_histogram_ws(const phprng_pattern *pat, uint64_t *hist, void *workspace, uint64_t bytes,
+                                          void *stream);
+
 /* chi^2 of a histogram of `pat` (device) against the uniform model: each
  * following point uniform over [0, n), so a cell expects
  * T prod_j (w_{b_j} / n) with T = l0 (s_hi - s_lo) and w_b the number of

@@ -155,6 +155,8 @@ SIGNATURES = {
     "phprng_chi2_pvalue": (ctypes.c_int, [ctypes.c_double, ctypes.c_double, ctypes.POINTER(ctypes.c_double)]),
     "phprng_interleave": (ctypes.c_int, [_vp, _vp, _u64, _u64, _vp]),
     "phprng_pattern_histogram": (ctypes.c_int, [ctypes.POINTER(phprng_pattern), _vp, _vp]),
+    "phprng_pattern_workspace": (ctypes.c_int, [ctypes.POINTER(phprng_pattern), _pu64]),
+    "phprng_pattern_histogram_ws": (ctypes.c_int, [ctypes.POINTER(phprng_pattern), _vp, _vp, _u64, _vp]),
     "phprng_pattern_chi2": (ctypes.c_int, [ctypes.POINTER(phprng_pattern), _vp, ctypes.POINTER(ctypes.c_double),
                                            ctypes.POINTER(ctypes.c_double), _pu64, _vp]),
 }
@@ -679,7 +681,32 @@ def pattern_histogram(spec, hist, stream=None):
     dim, bins = int(spec.dim), int(spec.bins)
     if 2 <= dim <= 5 and bins >= 1 and bins ** (dim - 1) <= (1 << 24) and hist.numel() < bins ** (dim - 1):
         raise ValueError("hist must hold bins^(dim-1) counts")
-    _check(lib().phprng_pattern_histogram(ctypes.byref(spec), ph, _stream_handle(stream)))
+    st = _stream_handle(stream)
+    ws = _torch_scratch(spec, hist, st)
+    if ws is not None:
+        _check(lib().phprng_pattern_histogram_ws(ctypes.byref(spec), ph, ws.data_ptr(), ws.numel(), st))
+    else:
+        _check(lib().phprng_pattern_histogram(ctypes.byref(spec), ph, st))
+
+
+def _torch_scratch(spec, hist, raw_stream):
+    """Scratch of a pattern histogram from torch's caching allocator (freeing
+    and mapping gigabytes anew took 38 ms of a 41 ms call), or None where that
+    memory might be in use elsewhere: the allocator orders a block's reuse on
+    torch's current stream only, so the call must run on that stream of the
+    histogram's device.  The call waits for its stream, so the block is free
+    again on return."""
+    import torch
+    dev = getattr(hist.device, "index", None)
+    if dev is None or dev != torch.cuda.current_device() or raw_stream != _stream_handle(None, dev):
+        return None
+    n = _u64()
+    if lib().phprng_pattern_workspace(ctypes.byref(spec), ctypes.byref(n)) != PHPRNG_OK:
+        return None  # the call itself reports what is wrong with the shape
+    try:
+        return torch.empty(n.value, dtype=torch.uint8, device=hist.device)
+    except torch.cuda.OutOfMemoryError:
+        return None
 
 
 def pattern_chi2(spec, hist, stream=None):

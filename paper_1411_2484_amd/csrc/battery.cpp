@@ -377,10 +377,7 @@ phprng_status phprng_battery_accumulate(phprng_battery *b, const double *r, uint
         (s = timed(b, 4, st, "fft pass 2", [&] {
            return launch_fft_pass2(b->d_y, nb, b->rep[PHPRNG_TEST_FOURIER], nullptr, b->tw, b->fourier_scale, st);
          })) != PHPRNG_OK ||
-        (s = timed(b, 5, st, "histogram count", [&] {
-           hipError_t e = ph::launch_count(b->parts, st);
-           return e == hipSuccess ? ph::launch_add(b->parts, st) : e;
-         })) != PHPRNG_OK)
+        (s = timed(b, 5, st, "histogram count", [&] { return ph::launch_count(b->parts, st); })) != PHPRNG_OK)
       return s;
   }
   // the small histograms' replicas into their histograms

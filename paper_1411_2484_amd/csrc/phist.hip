@@ -9,7 +9,10 @@ namespace ph {
 namespace {
 
 // One workgroup per (partition, slice): count slice s of every sub-bucket
-// of the partition in LDS and store the partition's counts for the slice.
+// of the partition in LDS and store the partition's counts for the slice,
+// or, with one slice, add them to the histogram and clear the partition's
+// fill counters (no other workgroup reads them).
+template <bool DIRECT>
 __global__ __launch_bounds__(1024) void count_kernel(PartSet P) {
   __shared__ uint32_t c[kPartCells];
   const uint32_t p = blockIdx.x / P.nslice, s = blockIdx.x % P.nslice;
@@ -48,9 +51,23 @@ __global__ __launch_bounds__(1024) void count_kernel(PartSet P) {
     for (uint32_t i = (hi & ~7u) + threadIdx.x; i < hi; i += 1024) atomicAdd(&c[d[i]], 1u);
   }
   __syncthreads();
-  uint32_t *out = P.slices + ((uint64_t)p * P.nslice + s) * kPartCells;
   const uint32_t nc = P.ncell[p];
-  for (uint32_t i = threadIdx.x; i < nc; i += 1024) out[i] = c[i];
+  if constexpr (DIRECT) {
+    unsigned long long *h = P.hist[p];
+    constexpr uint32_t kU = 8;  // histogram cells in flight per thread
+    for (uint32_t i0 = threadIdx.x; i0 < nc; i0 += 1024 * kU) {
+      unsigned long long v[kU];
+#pragma unroll
+      for (uint32_t u = 0; u < kU; ++u) v[u] = i0 + 1024 * u < nc ? h[i0 + 1024 * u] : 0;
+#pragma unroll
+      for (uint32_t u = 0; u < kU; ++u)
+        if (i0 + 1024 * u < nc) h[i0 + 1024 * u] = v[u] + c[i0 + 1024 * u];
+    }
+    if (threadIdx.x < P.nsub) P.fill[p * P.nsub + threadIdx.x] = 0;
+  } else {
+    uint32_t *out = P.slices + ((uint64_t)p * P.nslice + s) * kPartCells;
+    for (uint32_t i = threadIdx.x; i < nc; i += 1024) out[i] = c[i];
+  }
 }
 
 // hist[p][j] += sum over slices; the first nsub threads of each partition
@@ -70,12 +87,13 @@ __global__ __launch_bounds__(256) void add_kernel(PartSet P) {
 
 hipError_t launch_count(const PartSet &P, hipStream_t st) {
   clear_launch_error();
-  count_kernel<<<dim3(P.npart * P.nslice), dim3(1024), 0, st>>>(P);
-  return hipGetLastError();
-}
-
-hipError_t launch_add(const PartSet &P, hipStream_t st) {
-  clear_launch_error();
+  if (P.nslice == 1) {
+    count_kernel<true><<<dim3(P.npart), dim3(1024), 0, st>>>(P);
+    return hipGetLastError();
+  }
+  count_kernel<false><<<dim3(P.npart * P.nslice), dim3(1024), 0, st>>>(P);
+  const hipError_t e = hipGetLastError();
+  if (e != hipSuccess) return e;
   add_kernel<<<dim3(P.npart * (kPartCells / 256)), dim3(256), 0, st>>>(P);
   return hipGetLastError();
 }

@@ -8,7 +8,8 @@
 //   2. count: one workgroup per (partition, slice of its bucket) counts the
 //      offsets in a 128 KB LDS histogram and stores the counts;
 //   3. add: the per-slice counts are summed into the uint64 histogram and the
-//      bucket fill counters are cleared for the next round.
+//      bucket fill counters are cleared for the next round (stage 2 does both
+//      when a partition has one slice).
 // Atomics on one address serialise (about 5e7 per second), and every
 // workgroup reserves in every partition, so each partition's bucket is split
 // into nsub sub-buckets with fill counters of their own, and a workgroup
@@ -113,8 +114,8 @@ __device__ __forceinline__ void scatter_staged(const uint32_t (&key)[K], const P
   __syncthreads();
 }
 
+// Stages 2 and 3.
 hipError_t launch_count(const PartSet &P, hipStream_t st);
-hipError_t launch_add(const PartSet &P, hipStream_t st);
 
 }  // namespace ph
 }  // namespace phprng
