@@ -40,9 +40,14 @@ constexpr int kRow64 = kRun64 + 1;
 static_assert((kTilesPerPeriod32 & (kTilesPerPeriod32 - 1)) == 0, "tiles per period is a power of two");
 constexpr int kTileShift32 = 20;
 static_assert((1ull << kTileShift32) == kTilesPerPeriod32, "tile shift");
-// LDS words (64-bit) per wave: the width-32 block, or the larger width-64 one.
-constexpr int kLdsWords32 = (64 * kRow32 + 1) / 2;  // 1056
-constexpr int kLdsWords64 = 64 * kRow64;            // 1088
+// LDS words (64-bit) per wave: 64 rows of the tile and, before them, the last
+// row of the tile before it; the width-32 block, or the larger width-64 one.
+constexpr int kLdsWords32 = (65 * kRow32 + 1) / 2;  // 1073
+constexpr int kLdsWords64 = 65 * kRow64;            // 1105
+// Draws by which the rows of a tile are shifted back so that they start at
+// whole 128-byte lines of the outputs (32 4-byte or 16 8-byte elements).
+constexpr uint32_t kAlign32 = 32, kAlign64 = 16;
+static_assert(kAlign32 <= kRun32 && kAlign64 <= kRun64, "one row of the tile before holds the shifted draws");
 
 // ---------------------------------------------------------------------------
 // skip-prefix table segments
@@ -513,51 +518,89 @@ struct Enc32 {
   double rcp, rcp_lo;
 };
 
-// Ciphertext and uniform of one message of a width-32 tile (x = n - m).
+// What a draw stores: its ciphertext and its uniform.
+template <class C>
+struct Draw {
+  C c;
+  double r;
+};
+
+// The draw of one message of a width-32 tile (x = n - m).
 template <int EK, int OUT>
-__device__ __forceinline__ void emit32(uint32_t x, const Enc32 &K, uint32_t *c32, double *rr) {
+__device__ __forceinline__ Draw<uint32_t> draw32(uint32_t x, const Enc32 &K) {
+  Draw<uint32_t> d{};
   if constexpr (OUT & kOutC) {
-    const uint32_t c = dev::encrypt32<EK>(x, K.n, K.ninv, K.kc, K.e, K.ebits);
-    *c32 = c;
-    if constexpr (OUT & kOutR) *rr = dev::uniform32(c + 1u, K.rcp, K.rcp_lo);
+    d.c = dev::encrypt32<EK>(x, K.n, K.ninv, K.kc, K.e, K.ebits);
+    if constexpr (OUT & kOutR) d.r = dev::uniform32(d.c + 1u, K.rcp, K.rcp_lo);
   } else {
-    *rr = dev::uniform32(dev::encrypt32<EK, 1>(x, K.n, K.ninv, K.kc, K.e, K.ebits), K.rcp, K.rcp_lo);
+    d.r = dev::uniform32(dev::encrypt32<EK, 1>(x, K.n, K.ninv, K.kc, K.e, K.ebits), K.rcp, K.rcp_lo);
   }
+  return d;
 }
 
-// Pass C, width 32: draw t = i*64 + lane of the tile lives at LDS row t / 32,
-// column t % 32.  MASKED tiles write only t in [t_lo, t_hi).
-template <int UNROLL, int EK, int OUT, bool MASKED>
-__device__ __forceinline__ void passC32(const uint32_t *L, uint32_t lane, const Enc32 &K, uint32_t *c32, double *rr,
-                                        uint32_t t_lo, uint32_t t_hi) {
-  const uint32_t *src = L + (lane >> 5) * kRow32 + (lane & 31);
-  const uint32_t span = t_hi - t_lo;
-#pragma unroll UNROLL
-  for (int i = 0; i < kRun32; ++i) {
-    const uint32_t x = src[i * 2 * kRow32];
-    if (!MASKED || ((uint32_t)i * 64u + lane - t_lo < span)) {
-      emit32<EK, OUT>(x, K, c32 + i * 64, rr + i * 64);
+template <int OUT, class C>
+__device__ __forceinline__ void put_draw(const Draw<C> &d, C *c, double *r) {
+  if constexpr (OUT & kOutC) *c = d.c;
+  if constexpr (OUT & kOutR) *r = d.r;
+}
+
+// Pass C works on rows of 64 consecutive draws, one per lane.  The rows of a
+// tile are shifted back by `shift` draws, so that row r holds the draws
+// t = 64 r + lane - shift and its stores cover whole 128-byte lines whatever
+// the request's output offset (rows that straddle lines cost 6% of the store
+// rate for uniforms and 10% with ciphertexts).  u = t + shift counts from the
+// first row; the pass writes u in [u_lo, u_hi): whole rows in groups of UNROLL
+// (all messages, then all encryptions, then all stores of a group), the rows
+// at either end masked one at a time.  get(k) gives this lane's message of the
+// k-th row from the current one, calc(x) what is stored for it, put(k, v)
+// stores it, and next(n) makes the n-th row from here the current one (the
+// first is row u_lo / 64).
+template <int UNROLL, class Get, class Calc, class Put, class Next>
+__device__ __forceinline__ void row_loop(uint32_t u_lo, uint32_t u_hi, uint32_t lane, Get get, Calc calc, Put put,
+                                         Next next) {
+  const uint32_t whole_end = u_hi >> 6, end = (u_hi + 63) >> 6;
+  uint32_t r = u_lo >> 6;
+  for (;;) {
+    // masked rows: the first when u_lo cuts it, and what is left at the end
+    while (r < end && ((r << 6) < u_lo || r + UNROLL > whole_end)) {
+      if ((r << 6) + lane - u_lo < u_hi - u_lo) put(0, calc(get(0)));
+      next(1);
+      ++r;
+    }
+    if (r >= end) break;
+    for (; r + UNROLL <= whole_end; r += UNROLL) {
+      decltype(get(0)) x[UNROLL];
+      decltype(calc(get(0))) v[UNROLL];
+#pragma unroll
+      for (int k = 0; k < UNROLL; ++k) x[k] = get(k);
+#pragma unroll
+      for (int k = 0; k < UNROLL; ++k) v[k] = calc(x[k]);
+#pragma unroll
+      for (int k = 0; k < UNROLL; ++k) put(k, v[k]);
+      next(UNROLL);
     }
   }
 }
 
-template <int UNROLL, int EK, bool MASKED>
-__device__ __forceinline__ void passC32_out(const uint32_t *L, uint32_t lane, const Enc32 &K, uint32_t *c32,
-                                            double *rr, uint32_t t_lo, uint32_t t_hi) {
-  if (c32 && rr) passC32<UNROLL, EK, kOutC | kOutR, MASKED>(L, lane, K, c32, rr, t_lo, t_hi);
-  else if (rr) passC32<UNROLL, EK, kOutR, MASKED>(L, lane, K, c32, rr, t_lo, t_hi);
-  else if (c32) passC32<UNROLL, EK, kOutC, MASKED>(L, lane, K, c32, rr, t_lo, t_hi);
+// Calls f with the exponent chain and the outputs as compile-time constants.
+template <int V>
+struct Const {
+  static constexpr int value = V;
+};
+template <int EK, class F>
+__device__ __forceinline__ void with_outputs(bool c, bool r, F f) {
+  if (c && r) f(Const<EK>(), Const<kOutC | kOutR>());
+  else if (r) f(Const<EK>(), Const<kOutR>());
+  else if (c) f(Const<EK>(), Const<kOutC>());
 }
-
-template <int UNROLL, bool MASKED>
-__device__ __forceinline__ void passC32_e(int ekind, const uint32_t *L, uint32_t lane, const Enc32 &K, uint32_t *c32,
-                                          double *rr, uint32_t t_lo, uint32_t t_hi) {
+template <class F>
+__device__ __forceinline__ void with_chain(int ekind, bool c, bool r, F f) {
   switch (ekind) {
-    case 9: passC32_out<UNROLL, 9, MASKED>(L, lane, K, c32, rr, t_lo, t_hi); break;
-    case 17: passC32_out<UNROLL, 17, MASKED>(L, lane, K, c32, rr, t_lo, t_hi); break;
-    case 3: passC32_out<UNROLL, 3, MASKED>(L, lane, K, c32, rr, t_lo, t_hi); break;
-    case 5: passC32_out<UNROLL, 5, MASKED>(L, lane, K, c32, rr, t_lo, t_hi); break;
-    default: passC32_out<UNROLL, 0, MASKED>(L, lane, K, c32, rr, t_lo, t_hi); break;
+    case 9: with_outputs<9>(c, r, f); break;
+    case 17: with_outputs<17>(c, r, f); break;
+    case 3: with_outputs<3>(c, r, f); break;
+    case 5: with_outputs<5>(c, r, f); break;
+    default: with_outputs<0>(c, r, f); break;
   }
 }
 
@@ -575,8 +618,11 @@ __device__ void run_chunk32(const GenArgs &A, const InstRec &I, const ReqRec &R,
 
   const uint64_t g_begin = R.g1 + chunk * A.tiles_per_chunk;
   const uint64_t g_end = min(g_begin + A.tiles_per_chunk, R.g1 + R.ntiles);
+  uint32_t *const T = L + kRow32;  // the tile's rows; the row before holds the last 32 messages of the tile before
   uint32_t m_t = 0, s_t = 0;
   bool carried = false;
+  bool deferred = false;  // the tile before left its last `shift` draws to this one
+  uint32_t u_next = 0;    // and this is where the request begins among its rows
   for (uint64_t g = g_begin; g < g_end; ++g) {
     const uint64_t q = g >> kTileShift32;
     const uint32_t j = (uint32_t)(g & (kTilesPerPeriod32 - 1));
@@ -592,7 +638,7 @@ __device__ void run_chunk32(const GenArgs &A, const InstRec &I, const ReqRec &R,
     }
     // ---- pass A: skips of this lane's run, their sum (two skips < 2^31 add
     // below 2^32 before they enter the 64-bit sum)
-    uint32_t *row = L + lane * kRow32;
+    uint32_t *row = T + lane * kRow32;
     uint32_t s = dev::mulmod_p31(s_t, lane_mul);
     uint64_t sum = 0;
 #pragma unroll 4
@@ -620,21 +666,36 @@ __device__ void run_chunk32(const GenArgs &A, const InstRec &I, const ReqRec &R,
     s_t = (uint32_t)__builtin_amdgcn_readlane((int)s, 63);
     carried = true;
     dev::wave_lds_sync();
-    // ---- pass C: encrypt in draw order
-    const uint64_t tile_first = x0;  // draw t of this tile comes from state index x0 + t
-    const uint64_t req_end = R.x + R.count;  // one past the last state index used
-    uint32_t t_lo = R.x > tile_first ? (uint32_t)(R.x - tile_first) : 0u;
-    uint64_t hi1 = req_end - tile_first;
-    uint64_t hi2 = pm1 - (uint64_t)j * kTile32;
-    uint64_t hi = min(min(hi1, hi2), (uint64_t)kTile32);
-    uint32_t t_hi = (uint32_t)hi;
-    const int64_t base = (int64_t)R.out_off + (int64_t)(tile_first - R.x) + (int64_t)lane;
-    uint32_t *c32 = A.out_c32 ? A.out_c32 + base : nullptr;
-    double *rr = A.out_r ? A.out_r + base : nullptr;
-    if (t_lo == 0 && t_hi == (uint32_t)kTile32)
-      passC32_e<UNROLL, false>(ekind, L, lane, K, c32, rr, t_lo, t_hi);
-    else
-      passC32_e<1, true>(ekind, L, lane, K, c32, rr, t_lo, t_hi);
+    // ---- pass C: encrypt in draw order.  Draw t of this tile comes from
+    // state index x0 + t; a tile before another one of its chunk and period
+    // leaves its last `shift` draws to that tile's first row.
+    const uint64_t last = j + 1 == kTilesPerPeriod32 ? pm1 - (uint64_t)j * kTile32 : (uint64_t)kTile32;
+    const bool flush = g + 1 == g_end || j + 1 == kTilesPerPeriod32;
+    const int64_t base = (int64_t)R.out_off + (int64_t)(x0 - R.x);  // output element of draw 0
+    const uint32_t shift = (uint32_t)base & (kAlign32 - 1);
+    const uint32_t u_lo = deferred ? u_next : shift + (R.x > x0 ? (uint32_t)(R.x - x0) : 0u);
+    const uint32_t u_hi = flush ? shift + (uint32_t)min(R.x + R.count - x0, last) : (uint32_t)kTile32;
+    const int t0 = (int)lane - (int)shift;
+    const uint32_t *src = T + (t0 >> 5) * kRow32 + (t0 & 31);
+    const int64_t at = base - (int64_t)shift + (int64_t)(u_lo & ~63u) + (int64_t)lane;
+    uint32_t *cp = A.out_c32 + at;
+    double *rp = A.out_r + at;
+    const uint32_t *sp = src + (u_lo >> 6) * (2 * kRow32);
+    with_chain(ekind, A.out_c32 != nullptr, A.out_r != nullptr, [&](auto ek, auto out) {
+      constexpr int EK = decltype(ek)::value, OUT = decltype(out)::value;
+      row_loop<UNROLL>(
+          u_lo, u_hi, lane, [&](int k) { return sp[k * (2 * kRow32)]; },
+          [&](uint32_t v) { return draw32<EK, OUT>(v, K); },
+          [&](int k, const Draw<uint32_t> &d) { put_draw<OUT>(d, cp + k * 64, rp + k * 64); },
+          [&](int k) {
+            sp += k * (2 * kRow32);
+            cp += k * 64;
+            rp += k * 64;
+          });
+    });
+    deferred = !flush;
+    u_next = u_lo > (uint32_t)kTile32 ? u_lo - (uint32_t)kTile32 : 0u;  // all of this tile's draws deferred
+    if (deferred && lane < 32) L[lane] = T[63 * kRow32 + lane];
     dev::wave_lds_sync();
   }
 }
@@ -645,52 +706,17 @@ struct Enc64 {
   double den, rcp, rcp_lo;
 };
 
-// Ciphertext and uniform of one message of a width-64 tile (x = n - m).
+// The draw of one message of a width-64 tile (x = n - m).
 template <int EK, int OUT>
-__device__ __forceinline__ void emit64(uint64_t x, const Enc64 &K, uint64_t *c64, double *rr) {
+__device__ __forceinline__ Draw<uint64_t> draw64(uint64_t x, const Enc64 &K) {
+  Draw<uint64_t> d{};
   if constexpr (OUT & kOutC) {
-    const uint64_t c = dev::encrypt64<EK>(x, K.n, K.ninv, K.kc, K.e, K.ebits);
-    *c64 = c;
-    if constexpr (OUT & kOutR) *rr = dev::uniform64(c + 1, K.den, K.rcp, K.rcp_lo);
+    d.c = dev::encrypt64<EK>(x, K.n, K.ninv, K.kc, K.e, K.ebits);
+    if constexpr (OUT & kOutR) d.r = dev::uniform64(d.c + 1, K.den, K.rcp, K.rcp_lo);
   } else {
-    *rr = dev::uniform64(dev::encrypt64<EK, 1>(x, K.n, K.ninv, K.kc, K.e, K.ebits), K.den, K.rcp, K.rcp_lo);
+    d.r = dev::uniform64(dev::encrypt64<EK, 1>(x, K.n, K.ninv, K.kc, K.e, K.ebits), K.den, K.rcp, K.rcp_lo);
   }
-}
-
-// Pass C, width 64: draw t = i*64 + lane lives at LDS row t / 16, column
-// t % 16, i.e. row 4 i + lane / 16.  MASKED tiles write only t_lo <= t < t_hi.
-template <int UNROLL, int EK, int OUT, bool MASKED>
-__device__ __forceinline__ void passC64(const uint64_t *L, uint32_t lane, const Enc64 &K, uint64_t *c64, double *rr,
-                                        uint32_t t_lo, uint32_t t_hi) {
-  const uint64_t *src = L + (lane >> 4) * kRow64 + (lane & 15);
-  const uint32_t span = t_hi - t_lo;
-#pragma unroll UNROLL
-  for (int i = 0; i < kRun64; ++i) {
-    const uint64_t x = src[i * 4 * kRow64];
-    if (!MASKED || ((uint32_t)i * 64u + lane - t_lo < span)) {
-      emit64<EK, OUT>(x, K, c64 + i * 64, rr + i * 64);
-    }
-  }
-}
-
-template <int UNROLL, int EK, bool MASKED>
-__device__ __forceinline__ void passC64_out(const uint64_t *L, uint32_t lane, const Enc64 &K, uint64_t *c64,
-                                            double *rr, uint32_t t_lo, uint32_t t_hi) {
-  if (c64 && rr) passC64<UNROLL, EK, kOutC | kOutR, MASKED>(L, lane, K, c64, rr, t_lo, t_hi);
-  else if (rr) passC64<UNROLL, EK, kOutR, MASKED>(L, lane, K, c64, rr, t_lo, t_hi);
-  else if (c64) passC64<UNROLL, EK, kOutC, MASKED>(L, lane, K, c64, rr, t_lo, t_hi);
-}
-
-template <int UNROLL, bool MASKED>
-__device__ __forceinline__ void passC64_e(int ekind, const uint64_t *L, uint32_t lane, const Enc64 &K, uint64_t *c64,
-                                          double *rr, uint32_t t_lo, uint32_t t_hi) {
-  switch (ekind) {
-    case 9: passC64_out<UNROLL, 9, MASKED>(L, lane, K, c64, rr, t_lo, t_hi); break;
-    case 17: passC64_out<UNROLL, 17, MASKED>(L, lane, K, c64, rr, t_lo, t_hi); break;
-    case 3: passC64_out<UNROLL, 3, MASKED>(L, lane, K, c64, rr, t_lo, t_hi); break;
-    case 5: passC64_out<UNROLL, 5, MASKED>(L, lane, K, c64, rr, t_lo, t_hi); break;
-    default: passC64_out<UNROLL, 0, MASKED>(L, lane, K, c64, rr, t_lo, t_hi); break;
-  }
+  return d;
 }
 
 // Width 64: tile j of the request covers its draws [1024 j, 1024 (j + 1)),
@@ -716,9 +742,21 @@ __device__ void run_chunk64(const GenArgs &A, const InstRec &I, const ReqRec &R,
   // messages are carried as x = n - m (the encryption takes the sign back)
   uint64_t x_t = n - dev::uniform_u64(dev::const_load(A.t64.m + R.g1 + j_begin));
   uint64_t s_t = dev::uniform_u64(dev::const_load(A.t64.s + R.g1 + j_begin));
+  uint64_t *const T = L + kRow64;  // the tile's rows; the row before holds the last 16 messages of the tile before
+  const Enc64 K{n, ninv, kc, e, ebits, I.den, I.rcp, I.rcp_lo};
+  // draw 0 of tile j is output element base + 1024 j, so the shift that
+  // aligns its rows is the same for all tiles of the request.  Uniforms alone
+  // (8 bytes for some 110 VALU cycles) are far from the store rate, and the
+  // one more row that a shifted chunk takes is not won back: 283 against
+  // 286 us for 200 streams x 300,007.
+  const int64_t base = (int64_t)R.out_off - (int64_t)head;
+  const uint32_t shift = A.out_c64 ? (uint32_t)base & (kAlign64 - 1) : 0u;
+  const int t0 = (int)lane - (int)shift;
+  const uint64_t *src = T + (t0 >> 4) * kRow64 + (t0 & 15);
+  uint32_t u_lo = shift + (j_begin == 0 ? head : 0u);
   for (uint32_t j = j_begin; j < j_end; ++j) {
     // ---- pass A
-    uint64_t *row = L + lane * kRow64;
+    uint64_t *row = T + lane * kRow64;
     uint64_t s = dev::mulmod_p61(s_t, lane_mul);
     // eight skips below 2^61 sum below 2^64 < 4n: plain adds, one reduction per half run
     uint64_t g1 = 0, g2 = 0;
@@ -745,58 +783,68 @@ __device__ void run_chunk64(const GenArgs &A, const InstRec &I, const ReqRec &R,
     x_t = dev::lane_u64<63>(x);
     s_t = dev::lane_u64<63>(s);
     dev::wave_lds_sync();
-    // ---- pass C
-    const uint32_t t_lo = j == 0 ? head : 0u;
-    const uint32_t t_hi = tile_len64(R, j, head);
-    const int64_t base = (int64_t)R.out_off + (int64_t)j * kTile64 - (int64_t)head + (int64_t)lane;
-    uint64_t *c64 = A.out_c64 ? A.out_c64 + base : nullptr;
-    double *rr = A.out_r ? A.out_r + base : nullptr;
-    const Enc64 K{n, ninv, kc, e, ebits, I.den, I.rcp, I.rcp_lo};
-    if (t_lo == 0 && t_hi == (uint32_t)kTile64)
-      passC64_e<UNROLL, false>(ekind, L, lane, K, c64, rr, 0u, t_hi);
-    else
-      passC64_e<1, true>(ekind, L, lane, K, c64, rr, t_lo, t_hi);
+    // ---- pass C: a tile before another one of its chunk leaves its last
+    // `shift` draws to that tile's first row
+    const bool flush = j + 1 == j_end;
+    const uint32_t u_hi = flush ? shift + tile_len64(R, j, head) : (uint32_t)kTile64;
+    const int64_t first = base + (int64_t)j * kTile64 - (int64_t)shift;
+    const int64_t at = first + (int64_t)(u_lo & ~63u) + (int64_t)lane;
+    uint64_t *cp = A.out_c64 + at;
+    double *rp = A.out_r + at;
+    const uint64_t *sp = src + (u_lo >> 6) * (4 * kRow64);
+    with_chain(ekind, A.out_c64 != nullptr, A.out_r != nullptr, [&](auto ek, auto out) {
+      constexpr int EK = decltype(ek)::value, OUT = decltype(out)::value;
+      row_loop<UNROLL>(
+          u_lo, u_hi, lane, [&](int k) { return sp[k * (4 * kRow64)]; },
+          [&](uint64_t v) { return draw64<EK, OUT>(v, K); },
+          [&](int k, const Draw<uint64_t> &d) { put_draw<OUT>(d, cp + k * 64, rp + k * 64); },
+          [&](int k) {
+            sp += k * (4 * kRow64);
+            cp += k * 64;
+            rp += k * 64;
+          });
+    });
+    if (!flush && lane < 16) L[lane] = T[63 * kRow64 + lane];
+    u_lo = u_lo > (uint32_t)kTile64 ? u_lo - (uint32_t)kTile64 : 0u;  // where the request begins in the next tile's rows
     dev::wave_lds_sync();
   }
 }
 
 // ---------------------------------------------------------------------------
 // constant / unit skip (Sec. II): m at state index x is mbase + x b mod n, so
-// lane l of a tile starts at state x0 + 1 + l and steps by 64 b mod n; no
-// skip generator, no prefix, no LDS.
+// the lanes of a row start at consecutive states and step by 64 b mod n from
+// row to row; no skip generator, no prefix, no LDS.  Every tile is shifted
+// back to the outputs' lines as a whole (its states follow from the index
+// alone), and a request's last tile takes the draws that the shift leaves.
 // ---------------------------------------------------------------------------
 
-template <int UNROLL, int EK, int OUT, bool MASKED>
-__device__ __forceinline__ void passCS32(uint32_t x, uint32_t step, uint32_t lane, const Enc32 &K, uint32_t *c32,
-                                         double *rr, uint32_t t_lo, uint32_t t_hi) {
-  const uint32_t span = t_hi - t_lo;
-#pragma unroll UNROLL
-  for (int i = 0; i < kTileCS / 64; ++i) {
-    if (!MASKED || ((uint32_t)i * 64u + lane - t_lo < span)) {
-      emit32<EK, OUT>(x, K, c32 + i * 64, rr + i * 64);
-    }
-    x = dev::submod32(x, step, K.n);
-  }
-}
+// Rows of tile g of a constant-skip request: the pass writes u in
+// [u_lo, u_hi), and row u_lo / 64 starts at state index `state` + lane (one
+// row later, `state` + 64 + lane, when the tile's first row would start
+// before state 0).
+struct RowsCS {
+  uint32_t u_lo, u_hi;
+  uint64_t state;
+  bool later;
+  int64_t first;  // output element of row 0
+};
 
-template <int UNROLL, int EK, bool MASKED>
-__device__ __forceinline__ void passCS32_out(uint32_t m, uint32_t step, uint32_t lane, const Enc32 &K,
-                                             uint32_t *c32, double *rr, uint32_t t_lo, uint32_t t_hi) {
-  if (c32 && rr) passCS32<UNROLL, EK, kOutC | kOutR, MASKED>(m, step, lane, K, c32, rr, t_lo, t_hi);
-  else if (rr) passCS32<UNROLL, EK, kOutR, MASKED>(m, step, lane, K, c32, rr, t_lo, t_hi);
-  else if (c32) passCS32<UNROLL, EK, kOutC, MASKED>(m, step, lane, K, c32, rr, t_lo, t_hi);
-}
-
-template <int UNROLL, bool MASKED>
-__device__ __forceinline__ void passCS32_e(int ekind, uint32_t m, uint32_t step, uint32_t lane, const Enc32 &K,
-                                           uint32_t *c32, double *rr, uint32_t t_lo, uint32_t t_hi) {
-  switch (ekind) {
-    case 9: passCS32_out<UNROLL, 9, MASKED>(m, step, lane, K, c32, rr, t_lo, t_hi); break;
-    case 17: passCS32_out<UNROLL, 17, MASKED>(m, step, lane, K, c32, rr, t_lo, t_hi); break;
-    case 3: passCS32_out<UNROLL, 3, MASKED>(m, step, lane, K, c32, rr, t_lo, t_hi); break;
-    case 5: passCS32_out<UNROLL, 5, MASKED>(m, step, lane, K, c32, rr, t_lo, t_hi); break;
-    default: passCS32_out<UNROLL, 0, MASKED>(m, step, lane, K, c32, rr, t_lo, t_hi); break;
-  }
+__device__ __forceinline__ RowsCS rows_cs(const ReqRec &R, uint64_t g, uint32_t align) {
+  const uint64_t x0 = g * kTileCS;
+  const int64_t base = (int64_t)R.out_off + (int64_t)(x0 - R.x);  // output element of draw 0
+  const uint32_t shift = (uint32_t)base & (align - 1);
+  RowsCS W;
+  const bool last = g + 1 == R.g1 + R.ntiles;
+  // the request begins in its first tile's rows, or, when the shift moves all
+  // of that tile's draws on, in those of its second
+  const int64_t begin = (int64_t)(R.x - x0) + shift;
+  W.u_lo = begin > 0 ? (uint32_t)begin : 0u;
+  W.u_hi = last ? shift + (uint32_t)(R.x + R.count - x0) : (uint32_t)kTileCS;
+  const uint64_t r0 = W.u_lo & ~63u;
+  W.later = x0 + r0 < shift;
+  W.state = x0 + r0 + 1 - shift;  // wraps below 0 only when `later`
+  W.first = base - (int64_t)shift;
+  return W;
 }
 
 template <int UNROLL>
@@ -807,57 +855,34 @@ __device__ void run_chunk32_cs(const GenArgs &A, const InstRec &I, const ReqRec 
   const uint64_t g_begin = R.g1 + chunk * A.tiles_per_chunk;
   const uint64_t g_end = min(g_begin + A.tiles_per_chunk, R.g1 + R.ntiles);
   for (uint64_t g = g_begin; g < g_end; ++g) {
-    const uint64_t x0 = g * kTileCS;
-    // lane's first state index v = x0 + 1 + lane; v b mod n by Montgomery:
-    // bring hi(v) below n, then REDC(v) times b R^2
-    const uint64_t v = x0 + 1 + lane;
+    const RowsCS W = rows_cs(R, g, kAlign32);
+    // v b mod n by Montgomery: bring hi(v) below n, then REDC(v) times b R^2
+    const uint64_t v = W.state + lane + (W.later ? 64 : 0);
     uint32_t vh = (uint32_t)(v >> 32);
     vh = vh >= n ? vh - n : vh;
     const uint64_t vr = ((uint64_t)vh << 32) | (uint32_t)v;
-    const uint32_t m = n - dev::addmod32(mbase, dev::mont32(dev::redc32(vr, n, ninv), bR2, n, ninv), n);
-    const uint64_t req_end = R.x + R.count;
-    const uint32_t t_lo = R.x > x0 ? (uint32_t)(R.x - x0) : 0u;
-    const uint32_t t_hi = (uint32_t)min(req_end - x0, (uint64_t)kTileCS);
-    const int64_t base = (int64_t)R.out_off + (int64_t)(x0 - R.x) + (int64_t)lane;
-    uint32_t *c32 = A.out_c32 ? A.out_c32 + base : nullptr;
-    double *rr = A.out_r ? A.out_r + base : nullptr;
-    if (t_lo == 0 && t_hi == (uint32_t)kTileCS)
-      passCS32_e<UNROLL, false>((int)I.ekind, m, step, lane, K, c32, rr, t_lo, t_hi);
-    else
-      passCS32_e<1, true>((int)I.ekind, m, step, lane, K, c32, rr, t_lo, t_hi);
-  }
-}
-
-template <int UNROLL, int EK, int OUT, bool MASKED>
-__device__ __forceinline__ void passCS64(uint64_t x, uint64_t step, uint32_t lane, const Enc64 &K, uint64_t *c64,
-                                         double *rr, uint32_t t_lo, uint32_t t_hi) {
-  const uint32_t span = t_hi - t_lo;
-#pragma unroll UNROLL
-  for (int i = 0; i < kTileCS / 64; ++i) {
-    if (!MASKED || ((uint32_t)i * 64u + lane - t_lo < span)) {
-      emit64<EK, OUT>(x, K, c64 + i * 64, rr + i * 64);
-    }
-    x = dev::submod64(x, step, K.n);
-  }
-}
-
-template <int UNROLL, int EK, bool MASKED>
-__device__ __forceinline__ void passCS64_out(uint64_t m, uint64_t step, uint32_t lane, const Enc64 &K,
-                                             uint64_t *c64, double *rr, uint32_t t_lo, uint32_t t_hi) {
-  if (c64 && rr) passCS64<UNROLL, EK, kOutC | kOutR, MASKED>(m, step, lane, K, c64, rr, t_lo, t_hi);
-  else if (rr) passCS64<UNROLL, EK, kOutR, MASKED>(m, step, lane, K, c64, rr, t_lo, t_hi);
-  else if (c64) passCS64<UNROLL, EK, kOutC, MASKED>(m, step, lane, K, c64, rr, t_lo, t_hi);
-}
-
-template <int UNROLL, bool MASKED>
-__device__ __forceinline__ void passCS64_e(int ekind, uint64_t m, uint64_t step, uint32_t lane, const Enc64 &K,
-                                           uint64_t *c64, double *rr, uint32_t t_lo, uint32_t t_hi) {
-  switch (ekind) {
-    case 9: passCS64_out<UNROLL, 9, MASKED>(m, step, lane, K, c64, rr, t_lo, t_hi); break;
-    case 17: passCS64_out<UNROLL, 17, MASKED>(m, step, lane, K, c64, rr, t_lo, t_hi); break;
-    case 3: passCS64_out<UNROLL, 3, MASKED>(m, step, lane, K, c64, rr, t_lo, t_hi); break;
-    case 5: passCS64_out<UNROLL, 5, MASKED>(m, step, lane, K, c64, rr, t_lo, t_hi); break;
-    default: passCS64_out<UNROLL, 0, MASKED>(m, step, lane, K, c64, rr, t_lo, t_hi); break;
+    uint32_t x = n - dev::addmod32(mbase, dev::mont32(dev::redc32(vr, n, ninv), bR2, n, ninv), n);
+    if (W.later) x = dev::addmod32(x, step, n);
+    uint32_t y = x;  // message of the row last taken
+    const int64_t at = W.first + (int64_t)(W.u_lo & ~63u) + (int64_t)lane;
+    uint32_t *cp = A.out_c32 + at;
+    double *rp = A.out_r + at;
+    with_chain((int)I.ekind, A.out_c32 != nullptr, A.out_r != nullptr, [&](auto ek, auto out) {
+      constexpr int EK = decltype(ek)::value, OUT = decltype(out)::value;
+      row_loop<UNROLL>(
+          W.u_lo, W.u_hi, lane, 
+          [&](int k) {  // called in row order
+            y = k == 0 ? x : dev::submod32(y, step, n);
+            return y;
+          },
+          [&](uint32_t v) { return draw32<EK, OUT>(v, K); },
+          [&](int k, const Draw<uint32_t> &d) { put_draw<OUT>(d, cp + k * 64, rp + k * 64); },
+          [&](int k) {
+            x = dev::submod32(k == 1 ? x : y, step, n);
+            cp += k * 64;
+            rp += k * 64;
+          });
+    });
   }
 }
 
@@ -868,21 +893,32 @@ __device__ void run_chunk64_cs(const GenArgs &A, const InstRec &I, const ReqRec 
   const uint64_t g_begin = R.g1 + chunk * A.tiles_per_chunk;
   const uint64_t g_end = min(g_begin + A.tiles_per_chunk, R.g1 + R.ntiles);
   for (uint64_t g = g_begin; g < g_end; ++g) {
-    const uint64_t x0 = g * kTileCS;
+    const RowsCS W = rows_cs(R, g, kAlign64);
     dev::W128 v;
-    v.lo = x0 + 1 + lane;  // hi word 0 < n, so REDC applies
+    v.lo = W.state + lane + (W.later ? 64 : 0);  // hi word 0 < n, so REDC applies
     v.hi = 0;
-    const uint64_t m = n - dev::addmod64(I.mbase, dev::mont64(dev::redc64(v, n, ninv), I.bR2, n, ninv), n);
-    const uint64_t req_end = R.x + R.count;
-    const uint32_t t_lo = R.x > x0 ? (uint32_t)(R.x - x0) : 0u;
-    const uint32_t t_hi = (uint32_t)min(req_end - x0, (uint64_t)kTileCS);
-    const int64_t base = (int64_t)R.out_off + (int64_t)(x0 - R.x) + (int64_t)lane;
-    uint64_t *c64 = A.out_c64 ? A.out_c64 + base : nullptr;
-    double *rr = A.out_r ? A.out_r + base : nullptr;
-    if (t_lo == 0 && t_hi == (uint32_t)kTileCS)
-      passCS64_e<UNROLL, false>((int)I.ekind, m, I.b64, lane, K, c64, rr, t_lo, t_hi);
-    else
-      passCS64_e<1, true>((int)I.ekind, m, I.b64, lane, K, c64, rr, t_lo, t_hi);
+    uint64_t x = n - dev::addmod64(I.mbase, dev::mont64(dev::redc64(v, n, ninv), I.bR2, n, ninv), n);
+    if (W.later) x = dev::addmod64(x, I.b64, n);
+    uint64_t y = x;  // message of the row last taken
+    const int64_t at = W.first + (int64_t)(W.u_lo & ~63u) + (int64_t)lane;
+    uint64_t *cp = A.out_c64 + at;
+    double *rp = A.out_r + at;
+    with_chain((int)I.ekind, A.out_c64 != nullptr, A.out_r != nullptr, [&](auto ek, auto out) {
+      constexpr int EK = decltype(ek)::value, OUT = decltype(out)::value;
+      row_loop<UNROLL>(
+          W.u_lo, W.u_hi, lane, 
+          [&](int k) {  // called in row order
+            y = k == 0 ? x : dev::submod64(y, I.b64, n);
+            return y;
+          },
+          [&](uint64_t v) { return draw64<EK, OUT>(v, K); },
+          [&](int k, const Draw<uint64_t> &d) { put_draw<OUT>(d, cp + k * 64, rp + k * 64); },
+          [&](int k) {
+            x = dev::submod64(k == 1 ? x : y, I.b64, n);
+            cp += k * 64;
+            rp += k * 64;
+          });
+    });
   }
 }
 
