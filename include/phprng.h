@@ -262,16 +262,18 @@ phprng_status phprng_get_tuning_class(phprng_ctx *ctx, int cls, phprng_tuning *t
  * and width-64 messages are restored afterwards. */
 phprng_status phprng_autotune(phprng_ctx *ctx, uint64_t draws, phprng_tuning *best);
 
-/* ---- captured repeat draws -------------------------------------------------*/
+/* ---- prepared repeat draws -------------------------------------------------*/
 
 typedef struct phprng_graph phprng_graph;
 
-/* Capture one persistent generation of `reqs` into a HIP graph.  Each
+/* Prepare one persistent generation of `reqs` for repeated launches.  Each
  * phprng_graph_launch draws every request's count from its instance's
  * current position (whatever moved it since the last launch: generate,
  * jump, set_state), advances the positions and overwrites the same output
- * ranges; the planned requests are copied to the device before each
- * replay.  Requests must name distinct instances. */
+ * ranges; it plans the list again and launches the kernels directly (a HIP
+ * graph of so few kernels costs the host more than they do).  Each launch
+ * follows the one before, also on another stream.  Requests must name
+ * distinct instances. */
 phprng_status phprng_graph_create(phprng_ctx *ctx, const phprng_request *reqs, uint64_t nreq, uint32_t *out_c32,
                                   uint64_t *out_c64, double *out_r, uint64_t capacity, void *stream,
                                   phprng_graph **graph);
@@ -279,24 +281,26 @@ phprng_status phprng_graph_launch(phprng_graph *graph, void *stream);
 phprng_status phprng_graph_destroy(phprng_graph *graph);
 
 /* Kernel time of the last phprng_generate / phprng_graph_launch call on the
- * context, in milliseconds, measured with HIP events recorded on its stream
- * right before and after the call's kernels (for width-64 requests the
- * tile-start reduce and scan, then the generation kernel or kernels); waits
- * for that stream.  PLAIN mode reports the span of all its launches. */
+ * context, in milliseconds: from the beginning of the call's first kernel to
+ * the end of its last wave (for width-64 requests the tile-start kernels,
+ * then the generation kernel), read by the kernels from the device's
+ * constant-rate clock; waits for that stream.  HIP events around the call's
+ * kernels measure it instead in PLAIN mode (the span of all its launches),
+ * without draws, with launch shapes of more than 8192 waves and on a stream
+ * that is being captured. */
 phprng_status phprng_last_kernel_ms(phprng_ctx *ctx, double *ms);
 
-/* Cumulative generation-kernel time (same events as above) and number of
+/* Cumulative generation-kernel time (as above) and number of
  * timed calls since the last phprng_timing_reset, without stalling the host
- * between calls: each call's events are read when its staging slot is
+ * between calls: each call's times are read when its staging slot is
  * recycled, and this function waits for the calls still in flight. */
 phprng_status phprng_timing_reset(phprng_ctx *ctx);
 phprng_status phprng_timing_read(phprng_ctx *ctx, double *total_ms, uint64_t *calls);
 
-/* Per-call kernel timing on (on != 0, the default) or off.  Off, a call
- * records only the event that ends its kernels (the staging slot's
- * completion), not the one before them: one HIP event record fewer per
- * call, about 5 microseconds of host time on MI355X with ROCm 7, for
- * latency-bound callers such as a serving loop.  Calls made with timing off
+/* Per-call kernel timing on (on != 0, the default) or off.  Off, the kernels
+ * write no time stamps and a call that is timed by events leaves out the one
+ * before its kernels (about 5 microseconds of host time on MI355X with ROCm
+ * 7).  Calls made with timing off
  * are not counted by phprng_timing_read, and phprng_last_kernel_ms fails
  * after one.  phprng_autotune times its candidates either way. */
 phprng_status phprng_set_timing(phprng_ctx *ctx, int on);

@@ -471,7 +471,7 @@ class Context:
 
 
 class Graph:
-    """Captured repeat draws (phprng_graph_*)."""
+    """Prepared repeat draws (phprng_graph_*)."""
 
     def __init__(self, ctx, requests, out_c32, out_c64, out_r, capacity, stream):
         reqs = np.ascontiguousarray(requests, dtype=REQUEST_DTYPE)

@@ -24,8 +24,10 @@
 // A chunk is a run of consecutive tiles of one request; a wave carries the
 // state from one tile to the next within a chunk.
 #include <hip/hip_runtime.h>
+#include <hip/hip_ext.h>
 
 #include <algorithm>
+#include <cstddef>
 #include <mutex>
 #include <type_traits>
 
@@ -222,6 +224,34 @@ __device__ __forceinline__ uint64_t wave_search(uint64_t nreq, uint64_t c, uint3
   return lo;
 }
 
+// The batch's planned requests: the kernel's own arguments for a small batch.
+// (GenArgs is every kernel's first parameter.)
+using ArgPtr = const __attribute__((address_space(4))) char *;
+__device__ __forceinline__ const ReqRec *requests(const GenArgs &A) {
+  const ArgPtr args = (ArgPtr)__builtin_amdgcn_kernarg_segment_ptr();
+  return A.nreq <= kInlineReqs ? (const ReqRec *)(args + offsetof(GenArgs, inline_req)) : A.req;
+}
+
+// The kernel arguments, read again from the scalar cache: for a loop whose
+// body would otherwise hold all of them in scalar registers (and spill them).
+__device__ __forceinline__ const GenArgs &args_again() {
+  ArgPtr args = (ArgPtr)__builtin_amdgcn_kernarg_segment_ptr();
+  asm volatile("" : "+s"(args));
+  return *(const GenArgs *)args;
+}
+
+// Start of the call, from the kernel that is its first.
+__device__ __forceinline__ void stamp_begin(const GenArgs &A) {
+  if (A.stamp && A.stamp_start && blockIdx.x == 0 && threadIdx.x == 0) A.stamp[0] = (uint64_t)wall_clock64();
+}
+
+// End of wave w of the generation kernel, its stores included.
+__device__ __forceinline__ void stamp_end(const GenArgs &A, uint32_t w, uint32_t lane) {
+  if (!A.stamp) return;
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+  if (lane == 0) A.stamp[1 + w] = (uint64_t)wall_clock64();
+}
+
 // Sum, mod n, of the skips of lane `lane`'s run of kRun64 draws in a tile
 // that starts with skip s_tile and holds `len` draws; every lane gets the
 // tile total.
@@ -249,7 +279,7 @@ __device__ __forceinline__ uint32_t tile_len64(const ReqRec &R, uint32_t j, uint
   return j + 1 == R.ntiles ? last : (uint32_t)kTile64;
 }
 
-// One wave per reduce unit (grid-stride): up to hdr->reduce_tiles consecutive
+// One wave per reduce unit (grid-stride): up to A.reduce_tiles consecutive
 // tiles of one width-64 request.  For each tile j of a request starting at
 // skip log t it writes the skip before the tile, a^{t + 1024 j} mod p (a
 // power for the unit's first tile, then carried from tile to tile), and the
@@ -257,16 +287,17 @@ __device__ __forceinline__ uint32_t tile_len64(const ReqRec &R, uint32_t j, uint
 __global__ void __launch_bounds__(256) reduce64_kernel(GenArgs A) {
   const uint32_t lane = dev::lane_id();
   const uint32_t wave = dev::uniform_u32(threadIdx.x / 64);
-  const uint64_t units = dev::uniform_u64(dev::const_load(&A.hdr->units64));
-  const uint64_t nreq64 = dev::uniform_u64(dev::const_load(&A.hdr->nreq64));
-  const uint32_t rt = dev::uniform_u32((uint32_t)dev::const_load(&A.hdr->reduce_tiles));
+  stamp_begin(A);
+  const ReqRec *const req = requests(A);
+  const uint64_t units = A.units64, nreq64 = A.nreq64;
+  const uint32_t rt = A.reduce_tiles;
   const uint64_t nwaves = (uint64_t)gridDim.x * (blockDim.x / 64);
   const uint64_t lane_mul = A.lanemul->m64[lane];
   const uint64_t pm1 = kP64 - 1;
   for (uint64_t u = (uint64_t)blockIdx.x * (blockDim.x / 64) + wave; u < units; u += nwaves) {
     const uint64_t r =
-        dev::uniform_u64(wave_search(nreq64, u, lane, [&](uint64_t i) { return A.req[i].rbase; }));
-    const ReqRec R = dev::const_load(A.req + r);
+        dev::uniform_u64(wave_search(nreq64, u, lane, [&](uint64_t i) { return req[i].rbase; }));
+    const ReqRec R = dev::const_load(req + r);
     const uint64_t n = dev::const_load(&A.inst[R.inst].n);
     const uint32_t j0 = (uint32_t)(u - R.rbase) * rt;
     const uint32_t j1 = R.ntiles - j0 > rt ? j0 + rt : R.ntiles;
@@ -361,7 +392,9 @@ __device__ void wave_prefix64_pair(const SkipTables &T, uint64_t x, uint64_t y, 
 // wave then commits the message after the instance's last draw in the batch.
 __global__ void __launch_bounds__(64) tab64_kernel(GenArgs A) {
   const uint32_t lane = dev::lane_id();
-  const ReqRec R0 = dev::const_load(A.req + blockIdx.x);
+  stamp_begin(A);
+  const ReqRec *const req = requests(A);
+  const ReqRec R0 = dev::const_load(req + blockIdx.x);
   const uint32_t seg = R0.seg & kSegCount;
   if (seg == 0 || !(R0.seg & kSegTable)) return;
   const InstRec &I = A.inst[R0.inst];
@@ -369,12 +402,12 @@ __global__ void __launch_bounds__(64) tab64_kernel(GenArgs A) {
   const uint64_t lane_mul = A.lanemul->m64[lane];
   const uint64_t m0 = dev::uniform_u64(A.m64[R0.inst]);
   // U at the instance's first and last positions in the batch
-  const ReqRec RL = dev::const_load(A.req + blockIdx.x + seg - 1);
+  const ReqRec RL = dev::const_load(req + blockIdx.x + seg - 1);
   uint64_t u0, ue;
   wave_prefix64_pair(A.tab, R0.x, RL.x + RL.count, n, ninv, r2, lane_mul, lane, &u0, &ue);
   const uint64_t mbase = m0 >= u0 ? m0 - u0 : m0 + (n - u0);
   for (uint32_t q = 0; q < seg; ++q) {
-    const ReqRec R = dev::const_load(A.req + blockIdx.x + q);
+    const ReqRec R = dev::const_load(req + blockIdx.x + q);
     const uint64_t e0 = R.x / kTab64Stride;
     // the table reads of kTabGroup tiles per lane are issued before any of
     // them is used, so their latencies overlap (a long request has up to
@@ -422,10 +455,12 @@ constexpr int kScanPer = 4;
 __global__ void __launch_bounds__(kScanThreads) scan64_kernel(GenArgs A) {
   __shared__ uint64_t wtot[kScanThreads / 64];
   const uint64_t r = blockIdx.x;
-  const ReqRec R = dev::const_load(A.req + r);
+  stamp_begin(A);
+  const ReqRec *const req = requests(A);
+  const ReqRec R = dev::const_load(req + r);
   const uint32_t seg = R.seg & kSegCount;
   if (seg == 0 || (R.seg & kSegTable)) return;
-  const ReqRec L = dev::const_load(A.req + r + seg - 1);
+  const ReqRec L = dev::const_load(req + r + seg - 1);
   const uint64_t n = dev::const_load(&A.inst[R.inst].n);
   const uint64_t t0 = R.g1, t1 = L.g1 + L.ntiles;
   const uint32_t tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
@@ -582,6 +617,16 @@ __device__ __forceinline__ void row_loop(uint32_t u_lo, uint32_t u_hi, uint32_t 
   }
 }
 
+// The part of a tile's rows that wave `part` of the 2^split waves which share
+// the tile writes (each computes the whole tile's messages).
+__device__ __forceinline__ void part_of_rows(uint32_t split, uint32_t part, uint32_t tile, uint32_t *u_lo,
+                                             uint32_t *u_hi) {
+  const uint32_t span = tile >> split;
+  const uint32_t lo = max(*u_lo, part * span);
+  *u_hi = max(lo, (part + 1) >> split ? *u_hi : min(*u_hi, (part + 1) * span));
+  *u_lo = lo;
+}
+
 // Calls f with the exponent chain and the outputs as compile-time constants.
 template <int V>
 struct Const {
@@ -605,8 +650,8 @@ __device__ __forceinline__ void with_chain(int ekind, bool c, bool r, F f) {
 }
 
 template <int UNROLL>
-__device__ void run_chunk32(const GenArgs &A, const InstRec &I, const ReqRec &R, uint64_t chunk, uint32_t *L,
-                            uint32_t lane) {
+__device__ void run_chunk32(const GenArgs &A, const InstRec &I, const ReqRec &R, uint64_t chunk, uint32_t part,
+                            uint32_t *L, uint32_t lane) {
   const uint32_t n = (uint32_t)I.n, ninv = (uint32_t)I.ninv, kc = (uint32_t)I.kcorr, r2 = (uint32_t)I.r2;
   const uint32_t br2 = (uint32_t)I.br2;
   const uint64_t e = I.e;
@@ -673,8 +718,9 @@ __device__ void run_chunk32(const GenArgs &A, const InstRec &I, const ReqRec &R,
     const bool flush = g + 1 == g_end || j + 1 == kTilesPerPeriod32;
     const int64_t base = (int64_t)R.out_off + (int64_t)(x0 - R.x);  // output element of draw 0
     const uint32_t shift = (uint32_t)base & (kAlign32 - 1);
-    const uint32_t u_lo = deferred ? u_next : shift + (R.x > x0 ? (uint32_t)(R.x - x0) : 0u);
-    const uint32_t u_hi = flush ? shift + (uint32_t)min(R.x + R.count - x0, last) : (uint32_t)kTile32;
+    uint32_t u_lo = deferred ? u_next : shift + (R.x > x0 ? (uint32_t)(R.x - x0) : 0u);
+    uint32_t u_hi = flush ? shift + (uint32_t)min(R.x + R.count - x0, last) : (uint32_t)kTile32;
+    if (A.split) part_of_rows(A.split, part, kTile32, &u_lo, &u_hi);
     const int t0 = (int)lane - (int)shift;
     const uint32_t *src = T + (t0 >> 5) * kRow32 + (t0 & 31);
     const int64_t at = base - (int64_t)shift + (int64_t)(u_lo & ~63u) + (int64_t)lane;
@@ -726,8 +772,8 @@ __device__ __forceinline__ Draw<uint64_t> draw64(uint64_t x, const Enc64 &K) {
 // first tile comes from the scan or the table kernel; later tiles continue
 // from lane 63's last state.
 template <int UNROLL>
-__device__ void run_chunk64(const GenArgs &A, const InstRec &I, const ReqRec &R, uint64_t chunk, uint64_t *L,
-                            uint32_t lane) {
+__device__ void run_chunk64(const GenArgs &A, const InstRec &I, const ReqRec &R, uint64_t chunk, uint32_t part,
+                            uint64_t *L, uint32_t lane) {
   const uint64_t n = I.n, ninv = I.ninv, kc = I.kcorr;
   const uint64_t e = I.e;
   const int ebits = (int)I.ebits, ekind = (int)I.ekind;
@@ -786,7 +832,8 @@ __device__ void run_chunk64(const GenArgs &A, const InstRec &I, const ReqRec &R,
     // ---- pass C: a tile before another one of its chunk leaves its last
     // `shift` draws to that tile's first row
     const bool flush = j + 1 == j_end;
-    const uint32_t u_hi = flush ? shift + tile_len64(R, j, head) : (uint32_t)kTile64;
+    uint32_t u_hi = flush ? shift + tile_len64(R, j, head) : (uint32_t)kTile64;
+    if (A.split) part_of_rows(A.split, part, kTile64, &u_lo, &u_hi);
     const int64_t first = base + (int64_t)j * kTile64 - (int64_t)shift;
     const int64_t at = first + (int64_t)(u_lo & ~63u) + (int64_t)lane;
     uint64_t *cp = A.out_c64 + at;
@@ -829,7 +876,7 @@ struct RowsCS {
   int64_t first;  // output element of row 0
 };
 
-__device__ __forceinline__ RowsCS rows_cs(const ReqRec &R, uint64_t g, uint32_t align) {
+__device__ __forceinline__ RowsCS rows_cs(const ReqRec &R, uint64_t g, uint32_t align, uint32_t split, uint32_t part) {
   const uint64_t x0 = g * kTileCS;
   const int64_t base = (int64_t)R.out_off + (int64_t)(x0 - R.x);  // output element of draw 0
   const uint32_t shift = (uint32_t)base & (align - 1);
@@ -840,6 +887,7 @@ __device__ __forceinline__ RowsCS rows_cs(const ReqRec &R, uint64_t g, uint32_t 
   const int64_t begin = (int64_t)(R.x - x0) + shift;
   W.u_lo = begin > 0 ? (uint32_t)begin : 0u;
   W.u_hi = last ? shift + (uint32_t)(R.x + R.count - x0) : (uint32_t)kTileCS;
+  if (split) part_of_rows(split, part, kTileCS, &W.u_lo, &W.u_hi);
   const uint64_t r0 = W.u_lo & ~63u;
   W.later = x0 + r0 < shift;
   W.state = x0 + r0 + 1 - shift;  // wraps below 0 only when `later`
@@ -848,14 +896,15 @@ __device__ __forceinline__ RowsCS rows_cs(const ReqRec &R, uint64_t g, uint32_t 
 }
 
 template <int UNROLL>
-__device__ void run_chunk32_cs(const GenArgs &A, const InstRec &I, const ReqRec &R, uint64_t chunk, uint32_t lane) {
+__device__ void run_chunk32_cs(const GenArgs &A, const InstRec &I, const ReqRec &R, uint64_t chunk, uint32_t part,
+                               uint32_t lane) {
   const uint32_t n = (uint32_t)I.n, ninv = (uint32_t)I.ninv;
   const Enc32 K{n, ninv, (uint32_t)I.kcorr, I.e, (int)I.ebits, I.rcp, I.rcp_lo};
   const uint32_t bR2 = (uint32_t)I.bR2, step = (uint32_t)I.b64, mbase = (uint32_t)I.mbase;
   const uint64_t g_begin = R.g1 + chunk * A.tiles_per_chunk;
   const uint64_t g_end = min(g_begin + A.tiles_per_chunk, R.g1 + R.ntiles);
   for (uint64_t g = g_begin; g < g_end; ++g) {
-    const RowsCS W = rows_cs(R, g, kAlign32);
+    const RowsCS W = rows_cs(R, g, kAlign32, A.split, part);
     // v b mod n by Montgomery: bring hi(v) below n, then REDC(v) times b R^2
     const uint64_t v = W.state + lane + (W.later ? 64 : 0);
     uint32_t vh = (uint32_t)(v >> 32);
@@ -887,13 +936,14 @@ __device__ void run_chunk32_cs(const GenArgs &A, const InstRec &I, const ReqRec 
 }
 
 template <int UNROLL>
-__device__ void run_chunk64_cs(const GenArgs &A, const InstRec &I, const ReqRec &R, uint64_t chunk, uint32_t lane) {
+__device__ void run_chunk64_cs(const GenArgs &A, const InstRec &I, const ReqRec &R, uint64_t chunk, uint32_t part,
+                               uint32_t lane) {
   const uint64_t n = I.n, ninv = I.ninv;
   const Enc64 K{n, ninv, I.kcorr, I.e, (int)I.ebits, I.den, I.rcp, I.rcp_lo};
   const uint64_t g_begin = R.g1 + chunk * A.tiles_per_chunk;
   const uint64_t g_end = min(g_begin + A.tiles_per_chunk, R.g1 + R.ntiles);
   for (uint64_t g = g_begin; g < g_end; ++g) {
-    const RowsCS W = rows_cs(R, g, kAlign64);
+    const RowsCS W = rows_cs(R, g, kAlign64, A.split, part);
     dev::W128 v;
     v.lo = W.state + lane + (W.later ? 64 : 0);  // hi word 0 < n, so REDC applies
     v.hi = 0;
@@ -926,14 +976,16 @@ __device__ void run_chunk64_cs(const GenArgs &A, const InstRec &I, const ReqRec 
 template <int UNROLL, bool HAS64>
 __device__ __forceinline__ void run_chunk(const GenArgs &A, const ReqRec &R, uint64_t chunk, uint64_t *L,
                                           uint32_t lane) {
+  const uint32_t part = (uint32_t)chunk & ((1u << A.split) - 1);
+  chunk >>= A.split;
   const InstRec I = dev::const_load(A.inst + R.inst);
   if (I.sched == kSchedConstant) {
-    if (HAS64 && I.width == 64) run_chunk64_cs<UNROLL>(A, I, R, chunk, lane);
-    else run_chunk32_cs<UNROLL>(A, I, R, chunk, lane);
+    if (HAS64 && I.width == 64) run_chunk64_cs<UNROLL>(A, I, R, chunk, part, lane);
+    else run_chunk32_cs<UNROLL>(A, I, R, chunk, part, lane);
   } else if (HAS64 && I.width == 64) {
-    run_chunk64<UNROLL>(A, I, R, chunk, L, lane);
+    run_chunk64<UNROLL>(A, I, R, chunk, part, L, lane);
   } else {
-    run_chunk32<UNROLL>(A, I, R, chunk, reinterpret_cast<uint32_t *>(L), lane);
+    run_chunk32<UNROLL>(A, I, R, chunk, part, reinterpret_cast<uint32_t *>(L), lane);
   }
 }
 
@@ -943,7 +995,8 @@ __global__ void __launch_bounds__(BLOCK) gen_persistent(GenArgs A) {
   const uint32_t lane = dev::lane_id();
   const uint32_t wave = dev::uniform_u32(threadIdx.x / 64);  // wave-uniform: keeps chunk math scalar
   uint64_t *L = lds[wave];
-  const uint64_t total = dev::uniform_u64(dev::const_load(&A.hdr->total_chunks));
+  stamp_begin(A);
+  const uint64_t total = A.total_chunks;
   // The blocks of group g take the chunks g, g + ngroups, g + 2 ngroups, ...:
   // chunk k of the group is chunk g + k ngroups of the batch.  The first chunk
   // of every wave is its index among the group's waves; later chunks come from
@@ -969,22 +1022,26 @@ __global__ void __launch_bounds__(BLOCK) gen_persistent(GenArgs A) {
   // more chunks than waves never touches its counter.  (One call site of
   // run_chunk: a second one gets the whole chunk code outlined into a call.)
   const bool grab = mine > nwaves;
-  uint32_t *const counter = &A.ctr->group[g].counter;
   for (;;) {
     if (k >= mine) break;
+    const GenArgs &B = args_again();
     const uint64_t c = g + k * ngroups;
+    const ReqRec *const req = requests(B);
     const uint64_t r =
-        dev::uniform_u64(wave_search(A.nreq, c, lane, [&](uint64_t i) { return A.req[i].chunk_base; }));
-    const ReqRec R = dev::const_load(A.req + r);
-    run_chunk<UNROLL, HAS64>(A, R, c - R.chunk_base, L, lane);
+        B.nreq == 1 ? 0
+                    : dev::uniform_u64(wave_search(B.nreq, c, lane, [&](uint64_t i) { return req[i].chunk_base; }));
+    const ReqRec R = dev::const_load(req + r);
+    run_chunk<UNROLL, HAS64>(B, R, c - R.chunk_base, L, lane);
     if (!grab) break;
     uint32_t next = 0;
     if (lane == 0) {
+      uint32_t *const counter = &args_again().ctr->group[g].counter;
       next = atomicAdd(counter, 1u);
       if ((uint64_t)next == mine - 1) __hip_atomic_store(counter, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
     k = (uint64_t)nwaves + dev::uniform_u32((uint32_t)__shfl((int)next, 0, 64));
   }
+  stamp_end(args_again(), blockIdx.x * (BLOCK / 64) + wave, lane);
 }
 
 // One grid per request: block b (one wave) takes chunk b of request `r`.
@@ -992,7 +1049,7 @@ template <int UNROLL, bool HAS64>
 __global__ void __launch_bounds__(64) gen_plain(GenArgs A, uint64_t r) {
   __shared__ uint64_t lds[HAS64 ? kLdsWords64 : kLdsWords32];
   const uint32_t lane = dev::lane_id();
-  const ReqRec R = dev::const_load(A.req + r);
+  const ReqRec R = dev::const_load(requests(A) + r);
   if ((uint64_t)blockIdx.x >= R.nchunks) return;
   run_chunk<UNROLL, HAS64>(A, R, blockIdx.x, lds, lane);
 }
@@ -1082,29 +1139,35 @@ hipError_t launch_position64(const InstRec *inst, const uint32_t *ids, const uin
   return hipGetLastError();
 }
 
-hipError_t launch_tiles64_reduce(const GenArgs &A, uint64_t units64, unsigned max_blocks, hipStream_t st) {
+// A launch that completes the given events, or a plain one without any.
+template <class K, class... Args>
+static hipError_t launch_with(LaunchEvents ev, K kernel, unsigned grid, unsigned block, hipStream_t st, Args... args) {
+  if (ev.start || ev.stop)
+    hipExtLaunchKernelGGL(kernel, dim3(grid), dim3(block), 0, st, ev.start, ev.stop, 0, args...);
+  else
+    hipLaunchKernelGGL(kernel, dim3(grid), dim3(block), 0, st, args...);
+  return hipGetLastError();
+}
+
+hipError_t launch_tiles64_reduce(const GenArgs &A, uint64_t units64, unsigned max_blocks, hipStream_t st,
+                                 LaunchEvents ev) {
   clear_launch_error();
-  if (units64 == 0) return hipSuccess;
+  if (units64 == 0) return hipErrorInvalidValue;
   const uint64_t want = (units64 + 3) / 4;
   const unsigned blocks = (unsigned)std::max<uint64_t>(1, std::min<uint64_t>(want, max_blocks));
-  hipLaunchKernelGGL(reduce64_kernel, dim3(blocks), dim3(256), 0, st, A);
-  return hipGetLastError();
+  return launch_with(ev, reduce64_kernel, blocks, 256, st, A);
 }
 
-hipError_t launch_tiles64_table(const GenArgs &A, uint64_t nreq64, hipStream_t st) {
+hipError_t launch_tiles64_table(const GenArgs &A, uint64_t nreq64, hipStream_t st, LaunchEvents ev) {
   clear_launch_error();
-  if (nreq64 == 0) return hipSuccess;
-  if (nreq64 > 0x7fffffffull) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(tab64_kernel, dim3((unsigned)nreq64), dim3(64), 0, st, A);
-  return hipGetLastError();
+  if (nreq64 == 0 || nreq64 > 0x7fffffffull) return hipErrorInvalidValue;
+  return launch_with(ev, tab64_kernel, (unsigned)nreq64, 64, st, A);
 }
 
-hipError_t launch_tiles64_scan(const GenArgs &A, uint64_t nreq64, hipStream_t st) {
+hipError_t launch_tiles64_scan(const GenArgs &A, uint64_t nreq64, hipStream_t st, LaunchEvents ev) {
   clear_launch_error();
-  if (nreq64 == 0) return hipSuccess;
-  if (nreq64 > 0x7fffffffull) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(scan64_kernel, dim3((unsigned)nreq64), dim3(kScanThreads), 0, st, A);
-  return hipGetLastError();
+  if (nreq64 == 0 || nreq64 > 0x7fffffffull) return hipErrorInvalidValue;
+  return launch_with(ev, scan64_kernel, (unsigned)nreq64, kScanThreads, st, A);
 }
 
 hipError_t launch_skip_total64(uint64_t t, uint64_t count, uint64_t n, const LaneMul *lm, uint64_t *partial,
@@ -1121,52 +1184,48 @@ hipError_t launch_skip_total64(uint64_t t, uint64_t count, uint64_t n, const Lan
   return hipGetLastError();
 }
 
-template <int BLOCK, int UNROLL, bool HAS64>
-static void launch_p(const GenArgs &A, unsigned grid, hipStream_t st) {
-  hipLaunchKernelGGL((gen_persistent<BLOCK, UNROLL, HAS64>), dim3(grid), dim3(BLOCK), 0, st, A);
-}
-
 template <int BLOCK, bool HAS64>
-static bool launch_pu(const GenArgs &A, unsigned grid, int unroll, hipStream_t st) {
+static hipError_t launch_pu(const GenArgs &A, unsigned grid, int unroll, hipStream_t st, LaunchEvents ev) {
   switch (unroll) {
-    case 1: launch_p<BLOCK, 1, HAS64>(A, grid, st); return true;
-    case 2: launch_p<BLOCK, 2, HAS64>(A, grid, st); return true;
-    case 4: launch_p<BLOCK, 4, HAS64>(A, grid, st); return true;
-    default: return false;
+    case 1: return launch_with(ev, gen_persistent<BLOCK, 1, HAS64>, grid, BLOCK, st, A);
+    case 2: return launch_with(ev, gen_persistent<BLOCK, 2, HAS64>, grid, BLOCK, st, A);
+    case 4: return launch_with(ev, gen_persistent<BLOCK, 4, HAS64>, grid, BLOCK, st, A);
+    default: return hipErrorInvalidValue;
   }
 }
 
 template <bool HAS64>
-static bool launch_pb(const GenArgs &A, unsigned grid, int block, int unroll, hipStream_t st) {
+static hipError_t launch_pb(const GenArgs &A, unsigned grid, int block, int unroll, hipStream_t st, LaunchEvents ev) {
   switch (block) {
-    case 64: return launch_pu<64, HAS64>(A, grid, unroll, st);
-    case 128: return launch_pu<128, HAS64>(A, grid, unroll, st);
-    case 256: return launch_pu<256, HAS64>(A, grid, unroll, st);
-    case 512: return launch_pu<512, HAS64>(A, grid, unroll, st);
-    default: return false;
+    case 64: return launch_pu<64, HAS64>(A, grid, unroll, st, ev);
+    case 128: return launch_pu<128, HAS64>(A, grid, unroll, st, ev);
+    case 256: return launch_pu<256, HAS64>(A, grid, unroll, st, ev);
+    case 512: return launch_pu<512, HAS64>(A, grid, unroll, st, ev);
+    default: return hipErrorInvalidValue;
   }
 }
 
-hipError_t launch_persistent(const GenArgs &A, unsigned grid, int block, int unroll, bool has64, hipStream_t st) {
+hipError_t launch_persistent(const GenArgs &A, unsigned grid, int block, int unroll, bool has64, hipStream_t st,
+                             LaunchEvents ev) {
   clear_launch_error();
-  bool ok = has64 ? launch_pb<true>(A, grid, block, unroll, st) : launch_pb<false>(A, grid, block, unroll, st);
-  if (!ok) return hipErrorInvalidValue;
-  return hipGetLastError();
+  return has64 ? launch_pb<true>(A, grid, block, unroll, st, ev) : launch_pb<false>(A, grid, block, unroll, st, ev);
 }
 
-hipError_t launch_plain(const GenArgs &A, uint64_t r, unsigned grid, int unroll, bool has64, hipStream_t st) {
-  clear_launch_error();
-  if (grid == 0) return hipSuccess;
-  if (has64) {
-    if (unroll == 4) hipLaunchKernelGGL((gen_plain<4, true>), dim3(grid), dim3(64), 0, st, A, r);
-    else if (unroll == 2) hipLaunchKernelGGL((gen_plain<2, true>), dim3(grid), dim3(64), 0, st, A, r);
-    else hipLaunchKernelGGL((gen_plain<1, true>), dim3(grid), dim3(64), 0, st, A, r);
-  } else {
-    if (unroll == 4) hipLaunchKernelGGL((gen_plain<4, false>), dim3(grid), dim3(64), 0, st, A, r);
-    else if (unroll == 2) hipLaunchKernelGGL((gen_plain<2, false>), dim3(grid), dim3(64), 0, st, A, r);
-    else hipLaunchKernelGGL((gen_plain<1, false>), dim3(grid), dim3(64), 0, st, A, r);
+template <bool HAS64>
+static hipError_t launch_plain_u(const GenArgs &A, uint64_t r, unsigned grid, int unroll, hipStream_t st,
+                                 LaunchEvents ev) {
+  switch (unroll) {
+    case 4: return launch_with(ev, gen_plain<4, HAS64>, grid, 64, st, A, r);
+    case 2: return launch_with(ev, gen_plain<2, HAS64>, grid, 64, st, A, r);
+    default: return launch_with(ev, gen_plain<1, HAS64>, grid, 64, st, A, r);
   }
-  return hipGetLastError();
+}
+
+hipError_t launch_plain(const GenArgs &A, uint64_t r, unsigned grid, int unroll, bool has64, hipStream_t st,
+                        LaunchEvents ev) {
+  clear_launch_error();
+  if (grid == 0) return hipErrorInvalidValue;
+  return has64 ? launch_plain_u<true>(A, r, grid, unroll, st, ev) : launch_plain_u<false>(A, r, grid, unroll, st, ev);
 }
 
 }  // namespace phprng

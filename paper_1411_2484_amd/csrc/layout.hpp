@@ -93,19 +93,6 @@ static_assert(sizeof(ReqRec) == 64, "ReqRec must be 64 bytes");
 constexpr uint32_t kSegTable = 1u << 31;
 constexpr uint32_t kSegCount = kSegTable - 1;
 
-// Per-call totals, copied with the requests (kernels read them from device
-// memory, so that captured graphs take new values at every launch).
-struct alignas(64) BatchHdr {
-  uint64_t total_chunks;  // chunks of the whole batch
-  uint64_t nreq;          // requests
-  uint64_t nreq64;        // width-64 pseudorandom-skip requests (the first nreq64)
-  uint64_t tiles64;       // their tiles (entries of the tile-state arrays)
-  uint64_t units64;       // their reduce units
-  uint64_t reduce_tiles;  // tiles per reduce unit (1 .. kReduceTiles)
-  uint64_t pad[2];
-};
-static_assert(sizeof(BatchHdr) == 64, "BatchHdr must be 64 bytes");
-
 // Work counters of the generation kernel.  One address serves about 9e7 grabs
 // a second, so a batch of many short chunks is cut into kWorkGroups groups:
 // the blocks b with the same b mod kWorkGroups share one counter (its own
@@ -149,11 +136,21 @@ struct LaneMul {
   uint64_t pow64[64];   // a^{2^b} mod (2^61 - 1), b = 0..60
 };
 
+// Batches of at most kInlineReqs requests travel in the kernel arguments: a
+// kernel that reads its totals and its request from pinned host memory waits
+// for two more round trips over the bus (1.5 to 2 us each) before it starts.
+// With time stamps instead of a start event and the completion event on the
+// kernel's launch, calls of 1,000 draws in a row went from 17 to 6.7 us each,
+// sixteen requests (read from pinned memory) from 18 to 7.2 us.
+constexpr uint32_t kInlineReqs = 8;
+
 struct GenArgs {
   const InstRec *inst;
-  const ReqRec *req;
-  const BatchHdr *hdr;
+  const ReqRec *req;      // planned requests, when there are more than kInlineReqs
   uint64_t nreq;
+  uint64_t total_chunks;  // chunks of the whole batch
+  uint64_t nreq64;        // width-64 pseudorandom-skip requests (the first nreq64)
+  uint64_t units64;       // their reduce units
   WorkCtr *ctr;
   SkipTables tab;
   const LaneMul *lanemul;
@@ -162,7 +159,16 @@ struct GenArgs {
   uint32_t *out_c32;
   uint64_t *out_c64;
   double *out_r;
+  // Call timing (null: off): the device's constant-rate clock when the call's
+  // first kernel begins (stamp[0], written by that kernel: stamp_start), and
+  // when wave w of the generation kernel ends (stamp[1 + w]).
+  uint64_t *stamp;
+  uint32_t stamp_start;
   uint32_t tiles_per_chunk;
+  uint32_t reduce_tiles;  // tiles per reduce unit (1 .. kReduceTiles)
+  uint32_t split;         // log2 of the waves that share a tile (tiles_per_chunk is then 1)
+  ReqRec inline_req[kInlineReqs];
 };
+static_assert(sizeof(GenArgs) <= 1024, "kernel arguments stay small");
 
 }  // namespace phprng

@@ -1,6 +1,6 @@
 // Host runtime behind include/phprng.h: instance tables, seeding, the skip
 // tables, request planning and kernel launches, jumps and state restore,
-// captured repeat draws and the allocation-free entry point.
+// prepared repeat draws and the allocation-free entry point.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -71,6 +71,16 @@ int bit_length(uint64_t v) {
 // Batches of at most this many requests are read by the kernels from pinned
 // host memory instead of a device copy.
 constexpr uint64_t kDirectRequests = 1024;
+// Waves that share a tile in a small batch: up to 2^kMaxSplit, as long as the
+// batch then has at most kSplitWavesPerCu waves per compute unit (two: half
+// of the SIMDs).  A wave alone on its SIMD waits out every latency of its tile,
+// so rows divided among idle SIMDs end sooner: kernel time of 16,384 width-32
+// draws 5.8 us unsplit, 4.7 by two, 4.1 by four, 3.9 by eight (whole calls
+// 7.4, 6.8, 6.7 and 6.9); 65,536 width-64 draws 16.6, 14.3, 13.4, 13.2.  With
+// every SIMD taken (10^6 draws) a split only repeats the messages: 8.5 us a
+// call unsplit, 8.6 by four.
+constexpr uint32_t kMaxSplit = 2;
+constexpr uint32_t kSplitWavesPerCu = 2;
 // Planning vectors reserved at context creation.
 constexpr uint64_t kPlanReserve = 16384;
 static_assert(kNoAllocMaxRequests <= kPlanReserve, "allocation-free calls plan without growing a vector");
@@ -109,27 +119,26 @@ uint64_t add_u64_mod(uint64_t x, uint64_t y, uint64_t m) {  // (x + y) mod m, x,
 
 }  // namespace
 
+// Prepared repeat draws: the request list, its outputs and a launch shape.
+// A replay plans the list from the current positions and launches its one to
+// three kernels directly: a HIP graph of one kernel takes the host 16 us to
+// launch (and a copy of the planned requests to the address that was captured
+// 8 us more), the kernel itself 4 us.
 struct phprng_graph {
   phprng_ctx *ctx = nullptr;
-  hipGraph_t graph = nullptr;
-  hipGraphExec_t exec = nullptr;
-  uint8_t *d_blk = nullptr;  // batch header + requests, refreshed before every launch
-  WorkCtr *d_ctr = nullptr;
+  uint32_t *out_c32 = nullptr;
+  uint64_t *out_c64 = nullptr;
+  double *out_r = nullptr;
   uint64_t *d_t64 = nullptr;  // width-64 tile state
-  hipEvent_t done = nullptr;  // after the previous launch
-  bool launched = false;
+  // after the previous replay: the completion event of its staging slot (a
+  // slot that has been taken again since had waited for it)
+  hipEvent_t done = nullptr;
   std::vector<phprng_request> reqs;
   uint64_t nreq64 = 0;
   uint64_t cap64 = 0;  // width-64 tile-state entries: enough for either way of finding tile starts
   uint32_t tpc = 1;
-  bool has64 = false;
   ~phprng_graph() {
-    if (exec) (void)hipGraphExecDestroy(exec);
-    if (graph) (void)hipGraphDestroy(graph);
-    if (d_blk) (void)hipFree(d_blk);
-    if (d_ctr) (void)hipFree(d_ctr);
     if (d_t64) (void)hipFree(d_t64);
-    if (done) (void)hipEventDestroy(done);
   }
 };
 
@@ -145,6 +154,7 @@ struct Plan {
   uint64_t tiles = 0;    // all tiles
   uint64_t total_chunks = 0;
   uint32_t tpc = 1;
+  uint32_t split = 0;  // log2 of the waves that share a tile
   bool has32 = false, has64 = false;
   int cls = kMix32;
 };
@@ -176,23 +186,31 @@ struct phprng_ctx {
   // different streams) never overwrite a request block still in use.  A slot
   // is reused only after the event recorded behind its last kernel.
   struct Slot {
-    uint8_t *h_blk = nullptr;            // pinned, mapped: BatchHdr + ReqRec[cap]
+    uint8_t *h_blk = nullptr;            // pinned, mapped: ReqRec[cap]
     const uint8_t *h_blk_dev = nullptr;  // h_blk's address for kernels
     uint8_t *d_blk = nullptr;            // device copy
     uint64_t cap = 0;
     WorkCtr *d_ctr = nullptr;
     uint64_t *d_t64 = nullptr;  // 3 * cap64 words
     uint64_t cap64 = 0;
-    hipEvent_t ev0 = nullptr, ev1 = nullptr;  // around the call's kernels; ev1 also marks the slot free
+    // Call timing: the device's clock at the start of the call and at the end
+    // of each wave (pinned, mapped: GenArgs::stamp), or, where a call has more
+    // waves than that holds, ev0 and ev1 around its kernels.  ev1 also marks
+    // the slot free.
+    uint64_t *h_stamp = nullptr, *h_stamp_dev = nullptr;
+    uint32_t stamps = 0;  // waves of the last call
+    hipEvent_t ev0 = nullptr, ev1 = nullptr;
     bool busy = false;
-    bool timed = false;  // ev0 was recorded before the call's kernels
+    enum { kUntimed, kStamps, kEvents } timed = kUntimed;
   };
+  static constexpr uint32_t kStampWaves = 8192;
   static constexpr int kSlots = 8;
   static constexpr uint64_t kMinSlotRequests = 8192;
   Slot slots[kSlots];
   int cur_slot = 0;
   int last_timed = -1;
-  bool timing_on = true;  // record ev0 before each call's kernels (phprng_set_timing)
+  bool timing_on = true;  // time each call's kernels (phprng_set_timing)
+  double wall_khz = 1e5;  // rate of the device's constant clock
   double acc_ms = 0;  // cumulative kernel time of recycled slots
   uint64_t acc_calls = 0;
   // Planning scratch kept across calls, so that a batch costs O(requests)
@@ -232,6 +250,7 @@ struct phprng_ctx {
     for (auto &s : slots) {
       (void)hipFree(s.d_blk);
       if (s.h_blk) (void)hipHostFree(s.h_blk);
+      if (s.h_stamp) (void)hipHostFree(s.h_stamp);
       (void)hipFree(s.d_ctr);
       (void)hipFree(s.d_t64);
       if (s.ev0) (void)hipEventDestroy(s.ev0);
@@ -336,13 +355,27 @@ struct phprng_ctx {
   hipError_t retire(Slot &s) {
     hipError_t e = hipEventSynchronize(s.ev1);
     if (e != hipSuccess) return e;
-    float f = 0;
-    if (s.timed && hipEventElapsedTime(&f, s.ev0, s.ev1) == hipSuccess) {
-      acc_ms += f;
+    double ms = 0;
+    if (s.timed != Slot::kUntimed && slot_ms(s, &ms) == hipSuccess) {
+      acc_ms += ms;
       acc_calls += 1;
     }
     s.busy = false;
     return hipSuccess;
+  }
+
+  // Kernel time of a slot's finished call.
+  hipError_t slot_ms(const Slot &s, double *ms) const {
+    if (s.timed == Slot::kStamps) {
+      uint64_t end = s.h_stamp[0];
+      for (uint32_t w = 1; w <= s.stamps; ++w) end = std::max(end, s.h_stamp[w]);
+      *ms = (double)(end - s.h_stamp[0]) / wall_khz;
+      return hipSuccess;
+    }
+    float f = 0;
+    const hipError_t e = hipEventElapsedTime(&f, s.ev0, s.ev1);
+    if (e == hipSuccess) *ms = f;
+    return e;
   }
 
   // Take the next staging slot with room for nreq requests; waits for the
@@ -368,6 +401,14 @@ struct phprng_ctx {
     if (!s.ev0) {
       if ((e = hipEventCreate(&s.ev0)) != hipSuccess) return hip_fail(e, "event");
       if ((e = hipEventCreate(&s.ev1)) != hipSuccess) return hip_fail(e, "event");
+      if ((e = hipHostMalloc(&s.h_stamp, (kStampWaves + 1) * sizeof(uint64_t),
+                             hipHostMallocMapped | hipHostMallocCoherent)) != hipSuccess) {
+        s.h_stamp = nullptr;
+        return fail(PHPRNG_E_NOMEM, "timing buffer: %s", hipGetErrorString(e));
+      }
+      void *dp = nullptr;
+      if ((e = hipHostGetDevicePointer(&dp, s.h_stamp, 0)) != hipSuccess) return hip_fail(e, "timing buffer address");
+      s.h_stamp_dev = static_cast<uint64_t *>(dp);
       if ((e = hipMalloc(&s.d_ctr, sizeof(WorkCtr))) != hipSuccess) return fail(PHPRNG_E_NOMEM, "work counter");
       // the generation kernel expects a zero counter and leaves it so
       if ((e = hipMemset(s.d_ctr, 0, sizeof(WorkCtr))) != hipSuccess) return hip_fail(e, "work counter");
@@ -382,7 +423,7 @@ struct phprng_ctx {
       s.h_blk = nullptr;
       s.h_blk_dev = nullptr;
       s.cap = 0;
-      const uint64_t bytes = sizeof(BatchHdr) + cap * sizeof(ReqRec);
+      const uint64_t bytes = cap * sizeof(ReqRec);
       if ((e = hipMalloc(&s.d_blk, bytes)) != hipSuccess)
         return fail(PHPRNG_E_NOMEM, "request buffer: %s", hipGetErrorString(e));
       // coherent: kernels may read the planned requests straight from it
@@ -396,6 +437,20 @@ struct phprng_ctx {
       s.h_blk_dev = static_cast<const uint8_t *>(dp);
       s.cap = cap;
     }
+    return PHPRNG_OK;
+  }
+
+  // Where the kernels read a slot's planned requests.  The smallest batches
+  // travel in the kernel arguments; up to kDirectRequests are read straight
+  // from the pinned block (a few reads over the bus per chunk, no copy ahead
+  // of them); larger batches are copied to device memory first, where the
+  // chunk searches run locally.
+  phprng_status stage(Slot &s, uint64_t nreq, hipStream_t st, const uint8_t **blk) {
+    *blk = s.h_blk_dev;
+    if (nreq <= kDirectRequests) return PHPRNG_OK;
+    const hipError_t e = hipMemcpyAsync(s.d_blk, s.h_blk, nreq * sizeof(ReqRec), hipMemcpyHostToDevice, st);
+    if (e != hipSuccess) return hip_fail(e, "request copy");
+    *blk = s.d_blk;
     return PHPRNG_OK;
   }
 
@@ -416,9 +471,9 @@ struct phprng_ctx {
   phprng_status plan(const phprng_request *reqs, uint64_t nreq, uint64_t capacity, int mode, const uint32_t *tpc_fix,
                      uint64_t stage_cap, uint8_t *stage, Plan *P);
   void commit_plan();
-  GenArgs args(const uint8_t *d_blk, WorkCtr *ctr, uint64_t *t64, uint64_t t64cap, uint64_t nreq, uint32_t *c32,
-               uint64_t *c64, double *r, uint32_t tpc) const;
-  phprng_status launch(const Plan &P, const GenArgs &A, const ReqRec *hreq, hipStream_t s, int mode);
+  GenArgs args(const Plan &P, const uint8_t *blk, const uint8_t *stage, WorkCtr *ctr, uint64_t *t64, uint64_t t64cap,
+               uint32_t *c32, uint64_t *c64, double *r) const;
+  phprng_status launch(const Plan &P, GenArgs A, const ReqRec *hreq, hipStream_t s, int mode, Slot *slot);
   phprng_status sync_chain();
   phprng_status read_m64(uint32_t id, uint64_t *m);
   phprng_status write_m64(uint32_t id, uint64_t m);
@@ -534,7 +589,7 @@ static inline uint64_t tile_of32(uint64_t x) {
 }
 
 // Validate a request list, reserve positions (in request order) and write
-// the planned batch into `stage` (BatchHdr followed by nreq ReqRec): the
+// the planned batch into `stage` (nreq ReqRec): the
 // width-64 pseudorandom-skip requests first, grouped by instance in call
 // order, then the other width-64 requests, then the width-32 ones.  The new
 // positions are kept in cur_x / cur_k for commit_plan once every launch has
@@ -621,8 +676,7 @@ phprng_status phprng_ctx::plan(const phprng_request *reqs, uint64_t nreq, uint64
   order.resize(nreq);
   for (uint64_t i = 0; i < nreq; ++i) order[req_pos[i]] = (uint32_t)i;
   // records
-  BatchHdr *H = reinterpret_cast<BatchHdr *>(stage);
-  ReqRec *R = reinterpret_cast<ReqRec *>(stage + sizeof(BatchHdr));
+  ReqRec *R = reinterpret_cast<ReqRec *>(stage);
   // A width-64 instance's tile starts come from the table when all of its
   // draws in the batch lie below the table's range (its tiles then start at
   // table entries), else from the reduce and scan of its requests' skips.
@@ -704,10 +758,14 @@ phprng_status phprng_ctx::plan(const phprng_request *reqs, uint64_t nreq, uint64
     while (tpc > 1 && tiles < 4 * waves * tpc) tpc >>= 1;
   }
   out.tpc = tpc;
+  // Batches that leave most SIMDs idle share a tile between waves: each
+  // computes the tile's messages and encrypts a part of its rows.
+  if (mode == PHPRNG_MODE_PERSISTENT && tpc == 1)
+    while (out.split < kMaxSplit && (tiles << (out.split + 1)) <= (uint64_t)num_cus * kSplitWavesPerCu) ++out.split;
   uint64_t chunks = 0;
   for (uint64_t p = 0; p < nreq; ++p) {
     ReqRec &rr = R[p];
-    const uint64_t nc = ((uint64_t)rr.ntiles + tpc - 1) / tpc;
+    const uint64_t nc = (((uint64_t)rr.ntiles + tpc - 1) / tpc) << out.split;
     rr.chunk_base = chunks;
     rr.nchunks = (uint32_t)nc;
     chunks += nc;
@@ -715,13 +773,6 @@ phprng_status phprng_ctx::plan(const phprng_request *reqs, uint64_t nreq, uint64
   // the work counter hands out chunk numbers in 32 bits
   if (chunks >= (1ull << 31)) return fail(PHPRNG_E_RANGE, "batch too large: %llu chunks", (unsigned long long)chunks);
   out.total_chunks = chunks;
-  memset(H, 0, sizeof *H);
-  H->total_chunks = chunks;
-  H->nreq = nreq;
-  H->nreq64 = c64l;
-  H->tiles64 = tiles64;
-  H->units64 = units64;
-  H->reduce_tiles = rt;
   *P = out;
   return PHPRNG_OK;
 }
@@ -734,14 +785,22 @@ void phprng_ctx::commit_plan() {
   }
 }
 
-GenArgs phprng_ctx::args(const uint8_t *d_blk, WorkCtr *ctr, uint64_t *t64, uint64_t t64cap, uint64_t nreq,
-                         uint32_t *c32, uint64_t *c64, double *r, uint32_t tpc) const {
+// Kernel arguments of a planned batch; `stage` is the host's copy of its
+// requests and `blk` where the kernels find them (unless the arguments hold
+// them).
+GenArgs phprng_ctx::args(const Plan &P, const uint8_t *blk, const uint8_t *stage, WorkCtr *ctr, uint64_t *t64,
+                         uint64_t t64cap, uint32_t *c32, uint64_t *c64, double *r) const {
   GenArgs A;
   memset(&A, 0, sizeof A);
   A.inst = d_inst;
-  A.hdr = reinterpret_cast<const BatchHdr *>(d_blk);
-  A.req = reinterpret_cast<const ReqRec *>(d_blk + sizeof(BatchHdr));
-  A.nreq = nreq;
+  A.req = reinterpret_cast<const ReqRec *>(blk);
+  if (P.nreq <= kInlineReqs) memcpy(A.inline_req, stage, P.nreq * sizeof(ReqRec));
+  A.nreq = P.nreq;
+  A.total_chunks = P.total_chunks;
+  A.nreq64 = P.nreq64;
+  A.units64 = P.units64;
+  A.reduce_tiles = P.reduce_tiles;
+  A.split = P.split;
   A.ctr = ctr;
   A.tab = SkipTables{d_u32, d_s32, (uint64_t)u32.size(), d_u64lo, d_u64hi, d_s64};
   A.lanemul = d_lanemul;
@@ -752,42 +811,101 @@ GenArgs phprng_ctx::args(const uint8_t *d_blk, WorkCtr *ctr, uint64_t *t64, uint
   A.out_c32 = c32;
   A.out_c64 = c64;
   A.out_r = r;
-  A.tiles_per_chunk = tpc;
+  A.tiles_per_chunk = P.tpc;
   return A;
 }
 
 // Width-64 tile starts (ordered after the previous call's scan), then the
-// generation kernel(s).  The batch block must already be on the device.
-phprng_status phprng_ctx::launch(const Plan &P, const GenArgs &A, const ReqRec *hreq, hipStream_t s, int mode) {
+// generation kernel(s).  The batch's requests must already be where the
+// kernels read them.  `slot` (may be null: neither timing nor completion is
+// recorded) gets the call's time as set by timing_on and its completion event;
+// events ride on the kernels' launches, except that a capturing stream gets
+// plain launches and records.
+phprng_status phprng_ctx::launch(const Plan &P, GenArgs A, const ReqRec *hreq, hipStream_t s, int mode, Slot *slot) {
   hipError_t e;
+  hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+  const bool plain_events =
+      !slot || hipStreamIsCapturing(s, &cap) != hipSuccess || cap != hipStreamCaptureStatusNone;
+  const phprng_tuning &T = tuning[P.cls];
+  // A batch with fewer chunks than the tuned grid has waves runs one wave per
+  // chunk in one-wave blocks, so that its waves spread over every compute
+  // unit instead of filling a few with whole blocks.
+  const uint64_t full = (uint64_t)num_cus * T.blocks_per_cu * (T.block_threads / 64);
+  const int block = P.total_chunks < full ? 64 : T.block_threads;
+  const unsigned grid = (unsigned)(P.total_chunks < full ? P.total_chunks : (uint64_t)num_cus * T.blocks_per_cu);
+  uint64_t gens = 0;  // generation launches still to come
+  if (mode == PHPRNG_MODE_PERSISTENT) {
+    gens = P.total_chunks ? 1 : 0;
+  } else {
+    for (uint64_t p = 0; p < P.nreq; ++p) gens += hreq[p].nchunks != 0;
+  }
+  hipEvent_t start = nullptr;
+  const hipEvent_t stop = slot ? slot->ev1 : nullptr;
+  if (slot) {
+    // Timing by the kernels themselves (a start event beside or on a launch
+    // costs about 5 us of every call), by events where that does not apply.
+    const uint64_t waves = (uint64_t)grid * (block / 64);
+    slot->timed = Slot::kUntimed;
+    if (timing_on && mode == PHPRNG_MODE_PERSISTENT && gens && waves <= kStampWaves && !plain_events) {
+      slot->timed = Slot::kStamps;
+      slot->stamps = (uint32_t)waves;
+      A.stamp = slot->h_stamp_dev;
+      A.stamp_start = 1;
+    } else if (timing_on) {
+      slot->timed = Slot::kEvents;
+      start = slot->ev0;
+    }
+  }
+  if (plain_events && start && (e = hipEventRecord(start, s)) != hipSuccess) return hip_fail(e, "event");
+  // The launches: `start` and the start stamp go to the first, an event to
+  // complete to the one that is given it.
+  LaunchEvents next;
+  if (!plain_events) next.start = start;
+  auto ev = [&](hipEvent_t x) {
+    LaunchEvents v = next;
+    v.stop = plain_events ? nullptr : x;
+    next.start = nullptr;
+    return v;
+  };
   if (P.nreq64 > 0) {
-    if (P.any_reduce && (e = launch_tiles64_reduce(A, P.units64, (unsigned)num_cus * 8, s)) != hipSuccess)
-      return hip_fail(e, "tile reduce");
+    if (P.any_reduce && P.units64 > 0) {
+      if ((e = launch_tiles64_reduce(A, P.units64, (unsigned)num_cus * 8, s, ev(nullptr))) != hipSuccess)
+        return hip_fail(e, "tile reduce");
+      A.stamp_start = 0;
+    }
     if (chain_pending && (e = hipStreamWaitEvent(s, chain_ev, 0)) != hipSuccess) return hip_fail(e, "chain wait");
-    if (P.any_tab && (e = launch_tiles64_table(A, P.nreq64, s)) != hipSuccess) return hip_fail(e, "table tile starts");
-    if (P.any_reduce && (e = launch_tiles64_scan(A, P.nreq64, s)) != hipSuccess) return hip_fail(e, "tile scan");
-    if ((e = hipEventRecord(chain_ev, s)) != hipSuccess) return hip_fail(e, "chain record");
+    // the last of these kernels completes chain_ev
+    if (P.any_tab) {
+      if ((e = launch_tiles64_table(A, P.nreq64, s, ev(P.any_reduce ? nullptr : chain_ev))) != hipSuccess)
+        return hip_fail(e, "table tile starts");
+      A.stamp_start = 0;
+    }
+    if (P.any_reduce) {
+      if ((e = launch_tiles64_scan(A, P.nreq64, s, ev(chain_ev))) != hipSuccess) return hip_fail(e, "tile scan");
+      A.stamp_start = 0;
+    }
+    if (plain_events && (e = hipEventRecord(chain_ev, s)) != hipSuccess) return hip_fail(e, "chain record");
     chain_pending = true;
   }
-  const phprng_tuning &T = tuning[P.cls];
+  if (gens == 0) {
+    // no generation kernel: the events beside what ran
+    if (next.start && (e = hipEventRecord(next.start, s)) != hipSuccess) return hip_fail(e, "event");
+    if (stop && (e = hipEventRecord(stop, s)) != hipSuccess) return hip_fail(e, "event");
+    return PHPRNG_OK;
+  }
   if (mode == PHPRNG_MODE_PERSISTENT) {
-    if (P.total_chunks == 0) return PHPRNG_OK;
-    // A batch with fewer chunks than the tuned grid has waves runs one wave
-    // per chunk in one-wave blocks, so that its waves spread over every
-    // compute unit instead of filling a few with whole blocks.
-    const uint64_t wpb = (uint64_t)T.block_threads / 64;
-    const uint64_t full = (uint64_t)num_cus * T.blocks_per_cu * wpb;
-    const int block = P.total_chunks < full ? 64 : T.block_threads;
-    const unsigned grid = (unsigned)(P.total_chunks < full ? P.total_chunks : (uint64_t)num_cus * T.blocks_per_cu);
-    if ((e = launch_persistent(A, grid, block, T.unroll, P.has64, s)) != hipSuccess)
+    if ((e = launch_persistent(A, grid, block, T.unroll, P.has64, s, ev(stop))) != hipSuccess)
       return hip_fail(e, "persistent launch");
   } else {
     // one grid per request, from the host copy of the planned requests
     for (uint64_t p = 0; p < P.nreq; ++p) {
-      if ((e = launch_plain(A, p, hreq[p].nchunks, T.unroll, P.has64, s)) != hipSuccess)
+      if (hreq[p].nchunks == 0) continue;
+      const hipEvent_t last = --gens == 0 ? stop : nullptr;
+      if ((e = launch_plain(A, p, hreq[p].nchunks, T.unroll, P.has64, s, ev(last))) != hipSuccess)
         return hip_fail(e, "plain launch");
     }
   }
+  if (plain_events && stop && (e = hipEventRecord(stop, s)) != hipSuccess) return hip_fail(e, "event");
   return PHPRNG_OK;
 }
 
@@ -979,6 +1097,8 @@ extern "C" phprng_status phprng_create(phprng_ctx **out, int device, uint64_t ma
   hipDeviceProp_t prop;
   if (hipGetDeviceProperties(&prop, device) != hipSuccess) return PHPRNG_E_DEVICE;
   c->num_cus = prop.multiProcessorCount;
+  int khz = 0;
+  if (hipDeviceGetAttribute(&khz, hipDeviceAttributeWallClockRate, device) == hipSuccess && khz > 0) c->wall_khz = khz;
   c->arch = prop.gcnArchName;
   c->max_instances = max_instances;
   try {
@@ -1013,8 +1133,7 @@ extern "C" phprng_status phprng_create(phprng_ctx **out, int device, uint64_t ma
   void *sp = nullptr;
   if (scratch_address(device, &sp) != hipSuccess || !sp) return PHPRNG_E_DEVICE;
   c->scratch = static_cast<uint8_t *>(sp);
-  if (hipHostMalloc(&c->h_noalloc, sizeof(BatchHdr) + kNoAllocMaxRequests * sizeof(ReqRec), hipHostMallocDefault) !=
-      hipSuccess) {
+  if (hipHostMalloc(&c->h_noalloc, kNoAllocMaxRequests * sizeof(ReqRec), hipHostMallocDefault) != hipSuccess) {
     c->h_noalloc = nullptr;
     return PHPRNG_E_NOMEM;
   }
@@ -1345,24 +1464,12 @@ extern "C" phprng_status phprng_generate(phprng_ctx *c, const phprng_request *re
   if (st != PHPRNG_OK) return st;
   if ((st = c->ensure_tiles(*slot, P.tiles64)) != PHPRNG_OK) return st;
   hipStream_t s = (hipStream_t)stream;
-  hipError_t e;
-  // Small batches are read by the kernels straight from the pinned block (a
-  // few reads over the bus per chunk, no copy ahead of them); larger ones are
-  // copied to device memory first, where the chunk searches run locally.
-  const bool direct = nreq <= kDirectRequests;
-  if (!direct) {
-    const uint64_t bytes = sizeof(BatchHdr) + nreq * sizeof(ReqRec);
-    if ((e = hipMemcpyAsync(slot->d_blk, slot->h_blk, bytes, hipMemcpyHostToDevice, s)) != hipSuccess)
-      return c->hip_fail(e, "request copy");
-  }
-  GenArgs A = c->args(direct ? slot->h_blk_dev : slot->d_blk, slot->d_ctr, slot->d_t64, slot->cap64, nreq, out_c32,
-                      out_c64, out_r, P.tpc);
-  if (c->timing_on && (e = hipEventRecord(slot->ev0, s)) != hipSuccess) return c->hip_fail(e, "event");
-  st = c->launch(P, A, reinterpret_cast<const ReqRec *>(slot->h_blk + sizeof(BatchHdr)), s, mode);
+  const uint8_t *blk = nullptr;
+  if ((st = c->stage(*slot, nreq, s, &blk)) != PHPRNG_OK) return st;
+  const GenArgs A = c->args(P, blk, slot->h_blk, slot->d_ctr, slot->d_t64, slot->cap64, out_c32, out_c64, out_r);
+  st = c->launch(P, A, reinterpret_cast<const ReqRec *>(slot->h_blk), s, mode, slot);
   if (st != PHPRNG_OK) return st;
-  if ((e = hipEventRecord(slot->ev1, s)) != hipSuccess) return c->hip_fail(e, "event");
   slot->busy = true;
-  slot->timed = c->timing_on;
   c->last_timed = c->timing_on ? c->cur_slot : -1;
   c->commit_plan();
   return PHPRNG_OK;
@@ -1391,16 +1498,17 @@ extern "C" phprng_status phprng_generate_noalloc(phprng_ctx *c, const phprng_req
   if (P.tiles64 > kNoAllocMaxTiles64)
     return c->fail(PHPRNG_E_RANGE, "allocation-free generation takes at most %llu width-64 tiles (%llu draws) per call",
                    (unsigned long long)kNoAllocMaxTiles64, (unsigned long long)(kNoAllocMaxTiles64 * kTile64));
-  uint8_t *blk = c->scratch + kScratchHdrOff;
-  const uint64_t bytes = sizeof(BatchHdr) + nreq * sizeof(ReqRec);
-  if ((e = hipMemcpyAsync(blk, c->h_noalloc, bytes, hipMemcpyHostToDevice, s)) != hipSuccess)
-    return c->hip_fail(e, "request copy");
-  if ((e = hipEventRecord(c->noalloc_copied, s)) != hipSuccess) return c->hip_fail(e, "event");
-  c->noalloc_pending = true;
-  GenArgs A = c->args(blk, reinterpret_cast<WorkCtr *>(c->scratch + kScratchCtrOff),
-                      reinterpret_cast<uint64_t *>(c->scratch + kScratchTileOff), kNoAllocMaxTiles64, nreq, out_c32,
-                      out_c64, out_r, P.tpc);
-  st = c->launch(P, A, reinterpret_cast<const ReqRec *>(c->h_noalloc + sizeof(BatchHdr)), s, PHPRNG_MODE_PERSISTENT);
+  uint8_t *blk = c->scratch + kScratchReqOff;
+  if (nreq > kInlineReqs) {
+    if ((e = hipMemcpyAsync(blk, c->h_noalloc, nreq * sizeof(ReqRec), hipMemcpyHostToDevice, s)) != hipSuccess)
+      return c->hip_fail(e, "request copy");
+    if ((e = hipEventRecord(c->noalloc_copied, s)) != hipSuccess) return c->hip_fail(e, "event");
+    c->noalloc_pending = true;
+  }
+  const GenArgs A = c->args(P, blk, c->h_noalloc, reinterpret_cast<WorkCtr *>(c->scratch + kScratchCtrOff),
+                            reinterpret_cast<uint64_t *>(c->scratch + kScratchTileOff), kNoAllocMaxTiles64, out_c32,
+                            out_c64, out_r);
+  st = c->launch(P, A, reinterpret_cast<const ReqRec *>(c->h_noalloc), s, PHPRNG_MODE_PERSISTENT, nullptr);
   if (st != PHPRNG_OK) return st;
   c->commit_plan();
   return PHPRNG_OK;
@@ -1413,9 +1521,7 @@ extern "C" phprng_status phprng_last_kernel_ms(phprng_ctx *c, double *ms) {
   phprng_ctx::Slot &s = c->slots[c->last_timed];
   hipError_t e = hipEventSynchronize(s.ev1);
   if (e != hipSuccess) return c->hip_fail(e, "event sync");
-  float f = 0;
-  if ((e = hipEventElapsedTime(&f, s.ev0, s.ev1)) != hipSuccess) return c->hip_fail(e, "event time");
-  *ms = f;
+  if ((e = c->slot_ms(s, ms)) != hipSuccess) return c->hip_fail(e, "event time");
   return PHPRNG_OK;
 }
 
@@ -1704,7 +1810,7 @@ extern "C" phprng_status phprng_autotune(phprng_ctx *c, uint64_t draws, phprng_t
 }
 
 // ---------------------------------------------------------------------------
-// captured repeat draws
+// prepared repeat draws
 // ---------------------------------------------------------------------------
 
 extern "C" phprng_status phprng_graph_create(phprng_ctx *c, const phprng_request *reqs, uint64_t nreq,
@@ -1736,39 +1842,20 @@ extern "C" phprng_status phprng_graph_create(phprng_ctx *c, const phprng_request
   g->reqs.assign(reqs, reqs + nreq);
   g->nreq64 = P.nreq64;
   g->tpc = P.tpc;
-  g->has64 = P.has64;
+  g->out_c32 = out_c32;
+  g->out_c64 = out_c64;
+  g->out_r = out_r;
   // Each replay finds every instance's tile starts in whichever way its
   // position allows (the table, or the reduce and scan): a request takes
   // ceil(count / 1024) tiles the second way and at most one more the first.
-  uint64_t cap64 = 1;
+  uint64_t cap64 = 0;
   for (uint64_t i = 0; i < nreq; ++i)
     if (lcg64(c->inst[reqs[i].instance])) cap64 += (reqs[i].count + kTile64 - 1) / kTile64 + 1;
   g->cap64 = cap64;
-  hipError_t e;
-  const uint64_t bytes = sizeof(BatchHdr) + nreq * sizeof(ReqRec);
-  if ((e = hipMalloc(&g->d_blk, bytes)) != hipSuccess) return c->hip_fail(e, "graph alloc");
-  if ((e = hipMalloc(&g->d_ctr, sizeof(WorkCtr))) != hipSuccess) return c->hip_fail(e, "graph alloc");
-  if ((e = hipMemset(g->d_ctr, 0, sizeof(WorkCtr))) != hipSuccess) return c->hip_fail(e, "graph alloc");
-  if ((e = hipMalloc(&g->d_t64, 3 * cap64 * sizeof(uint64_t))) != hipSuccess) return c->hip_fail(e, "graph alloc");
-  if ((e = hipEventCreateWithFlags(&g->done, hipEventDisableTiming)) != hipSuccess) return c->hip_fail(e, "event");
-  const phprng_tuning &T = c->tuning[P.cls];
-  GenArgs A = c->args(g->d_blk, g->d_ctr, g->d_t64, cap64, nreq, out_c32, out_c64, out_r, P.tpc);
-  hipStream_t cap_stream;
-  if ((e = hipStreamCreateWithFlags(&cap_stream, hipStreamNonBlocking)) != hipSuccess) return c->hip_fail(e, "stream");
-  e = hipStreamBeginCapture(cap_stream, hipStreamCaptureModeThreadLocal);
-  // all three tile-start kernels, on grids that fit any replay: each reads
-  // from the replay's block which instances are its own
-  const unsigned reduce_blocks = (unsigned)c->num_cus * 8;
-  if (e == hipSuccess && P.nreq64 > 0) e = launch_tiles64_reduce(A, 4ull * reduce_blocks, reduce_blocks, cap_stream);
-  if (e == hipSuccess && P.nreq64 > 0) e = launch_tiles64_table(A, P.nreq64, cap_stream);
-  if (e == hipSuccess && P.nreq64 > 0) e = launch_tiles64_scan(A, P.nreq64, cap_stream);
-  if (e == hipSuccess)
-    e = launch_persistent(A, (unsigned)(c->num_cus * T.blocks_per_cu), T.block_threads, T.unroll, P.has64, cap_stream);
-  hipError_t e2 = hipStreamEndCapture(cap_stream, &g->graph);
-  (void)hipStreamDestroy(cap_stream);
-  if (e != hipSuccess || e2 != hipSuccess) return c->hip_fail(e != hipSuccess ? e : e2, "graph capture");
-  if ((e = hipGraphInstantiate(&g->exec, g->graph, nullptr, nullptr, 0)) != hipSuccess)
-    return c->hip_fail(e, "graph instantiate");
+  if (cap64) {
+    const hipError_t e = hipMalloc(&g->d_t64, 3 * cap64 * sizeof(uint64_t));
+    if (e != hipSuccess) return c->hip_fail(e, "graph alloc");
+  }
   *graph = g.release();
   return PHPRNG_OK;
 }
@@ -1791,24 +1878,15 @@ extern "C" phprng_status phprng_graph_launch(phprng_graph *g, void *stream) {
     return c->fail(PHPRNG_E_INVALID, "graph requests no longer match their instances");
   hipStream_t s = (hipStream_t)stream;
   hipError_t e;
-  // the previous launch must be done with the request block before it is rewritten
-  if (g->launched && (e = hipStreamWaitEvent(s, g->done, 0)) != hipSuccess) return c->hip_fail(e, "graph wait");
-  const uint64_t bytes = sizeof(BatchHdr) + nreq * sizeof(ReqRec);
-  if ((e = hipMemcpyAsync(g->d_blk, slot->h_blk, bytes, hipMemcpyHostToDevice, s)) != hipSuccess)
-    return c->hip_fail(e, "request copy");
-  if (g->nreq64 > 0 && c->chain_pending && (e = hipStreamWaitEvent(s, c->chain_ev, 0)) != hipSuccess)
-    return c->hip_fail(e, "chain wait");
-  if (c->timing_on && (e = hipEventRecord(slot->ev0, s)) != hipSuccess) return c->hip_fail(e, "event");
-  if ((e = hipGraphLaunch(g->exec, s)) != hipSuccess) return c->hip_fail(e, "graph launch");
-  if ((e = hipEventRecord(slot->ev1, s)) != hipSuccess) return c->hip_fail(e, "event");
-  if ((e = hipEventRecord(g->done, s)) != hipSuccess) return c->hip_fail(e, "event");
-  if (g->nreq64 > 0) {
-    if ((e = hipEventRecord(c->chain_ev, s)) != hipSuccess) return c->hip_fail(e, "chain record");
-    c->chain_pending = true;
-  }
-  g->launched = true;
+  // replays write the same outputs (and tile state): each follows the one before
+  if (g->done && (e = hipStreamWaitEvent(s, g->done, 0)) != hipSuccess) return c->hip_fail(e, "graph wait");
+  const uint8_t *blk = nullptr;
+  if ((st = c->stage(*slot, nreq, s, &blk)) != PHPRNG_OK) return st;
+  const GenArgs A = c->args(P, blk, slot->h_blk, slot->d_ctr, g->d_t64, g->cap64, g->out_c32, g->out_c64, g->out_r);
+  st = c->launch(P, A, nullptr, s, PHPRNG_MODE_PERSISTENT, slot);
+  if (st != PHPRNG_OK) return st;
+  g->done = slot->ev1;
   slot->busy = true;
-  slot->timed = c->timing_on;
   c->last_timed = c->timing_on ? c->cur_slot : -1;
   c->commit_plan();
   return PHPRNG_OK;
