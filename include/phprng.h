@@ -491,8 +491,9 @@ phprng_status phprng_battery_fourier(phprng_battery *battery, const double *r, u
 
 /* Kernel time (ms) and launches since the last reset for the six kernel
  * classes (ms and launches are host arrays of 6): histogram keys, collision,
- * runs, transform pass 1, transform pass 2, histogram counting (HIP events
- * on the launch stream; waits for them). */
+ * runs, transform pass 1, transform pass 2, histogram counting (each from
+ * the end of the kernel before it to its own, by HIP events on the launch
+ * stream; waits for them). */
 phprng_status phprng_battery_timing(phprng_battery *battery, double *ms, uint64_t *launches);
 
 /* One-sided P-value min(Q, 1 - Q) of chi^2 with `dof` degrees of freedom (host). */

@@ -8,6 +8,7 @@
 #include <cstdio>
 #include <algorithm>
 #include <cstring>
+#include <mutex>
 #include <string>
 #include <vector>
 
@@ -105,9 +106,12 @@ double equal_cells_chi2(uint64_t total, unsigned __int128 sq, uint32_t cells) {
 
 constexpr uint32_t kReportMoments = kPartTests * kMomentSlices;
 
+// A timed launch, from the end a of the one before it to its own end b; b
+// belongs to the launch after it, unless this is the last of its call.
 struct Pending {
   int cls;
   hipEvent_t a, b;
+  bool last;
 };
 
 }  // namespace
@@ -129,6 +133,7 @@ struct phprng_battery {
   // report: per-slice moments of the large histograms, then the small
   // histograms, written by the device into mapped host memory
   void *h_report = nullptr;
+  std::mutex report_lock;  // over writing and reading it (counts may be read from several threads)
   Moments *report_moments = nullptr;            // device addresses of the two parts
   unsigned long long *report_small = nullptr;
   unsigned long long *d_discard = nullptr;  // Fourier category replicas of phprng_battery_fourier calls
@@ -186,7 +191,7 @@ void resolve(phprng_battery *b, bool wait) {
         b->launches[p.cls] += 1;
       }
       b->free_events.push_back(p.a);
-      b->free_events.push_back(p.b);
+      if (p.last) b->free_events.push_back(p.b);
     } else {
       b->pending[keep++] = p;
     }
@@ -194,21 +199,58 @@ void resolve(phprng_battery *b, bool wait) {
   b->pending.resize(keep);
 }
 
-template <class F>
-phprng_status timed(phprng_battery *b, int cls, hipStream_t st, const char *what, F launch) {
-  hipEvent_t a = take_event(b), c = take_event(b);
-  if (a) (void)hipEventRecord(a, st);
-  hipError_t e = launch();
-  if (e != hipSuccess) return hip_fail(b, e, what);
-  if (a && c && hipEventRecord(c, st) == hipSuccess) {
-    b->pending.push_back({cls, a, c});
-  } else {
-    if (a) b->free_events.push_back(a);
-    if (c) b->free_events.push_back(c);
+// The timed launches of one call: each completes its own event (a record
+// before and one after each kernel left the GPU idle for 10 us), and its time
+// runs from the event of the launch before, the first one's from a record.  A
+// stream that is being captured gets records only.
+struct TimedLaunches {
+  phprng_battery *b;
+  hipStream_t st;
+  hipEvent_t prev = nullptr;
+  bool records = false, used = false;
+  TimedLaunches(phprng_battery *bat, hipStream_t stream) : b(bat), st(stream) {
+    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+    records = hipStreamIsCapturing(st, &cap) != hipSuccess || cap != hipStreamCaptureStatusNone;
+    prev = take_event(b);
+    if (prev && hipEventRecord(prev, st) != hipSuccess) drop(prev);
   }
-  if (b->pending.size() > 1024) resolve(b, false);
-  return PHPRNG_OK;
-}
+  ~TimedLaunches() {
+    if (used)
+      b->pending.back().last = true;
+    else if (prev)
+      b->free_events.push_back(prev);
+    if (b->pending.size() > 1024) resolve(b, false);
+  }
+  TimedLaunches(const TimedLaunches &) = delete;
+  TimedLaunches &operator=(const TimedLaunches &) = delete;
+
+  template <class F>
+  phprng_status operator()(int cls, const char *what, F launch) {
+    hipEvent_t stop = prev ? take_event(b) : nullptr;
+    phprng::LaunchEvents ev;
+    if (!records) ev.stop = stop;
+    const hipError_t e = launch(ev);
+    if (e != hipSuccess) {
+      if (stop) drop(stop);
+      return hip_fail(b, e, what);
+    }
+    if (!stop) return PHPRNG_OK;
+    if (records && hipEventRecord(stop, st) != hipSuccess) {
+      drop(stop);
+      return PHPRNG_OK;
+    }
+    b->pending.push_back({cls, prev, stop, false});
+    used = true;
+    prev = stop;
+    return PHPRNG_OK;
+  }
+
+ private:
+  void drop(hipEvent_t &e) {
+    b->free_events.push_back(e);
+    e = nullptr;
+  }
+};
 
 phprng_status check_blocks(phprng_battery *b, const double *r, uint64_t count) {
   if (!b) return PHPRNG_E_INVALID;
@@ -362,36 +404,41 @@ phprng_status phprng_battery_accumulate(phprng_battery *b, const double *r, uint
   (void)hipSetDevice(b->device);
   hipStream_t st = (hipStream_t)stream;
   const uint64_t nblocks = count / kBlock;
+  if (nblocks == 0) return PHPRNG_OK;
+  TimedLaunches timed(b, st);
   for (uint64_t b0 = 0; b0 < nblocks; b0 += kChunkBlocks) {
     const uint64_t nb = nblocks - b0 < kChunkBlocks ? nblocks - b0 : kChunkBlocks;
     const double *src = r + b0 * kBlock;
-    if ((s = timed(b, 0, st, "hist kernel",
-                   [&] {
-                     return launch_hist(src, nb, b->parts, b->bparts, b->rep[PHPRNG_TEST_POKER], b->d_bits, st);
+    using Ev = phprng::LaunchEvents;
+    if ((s = timed(0, "hist kernel",
+                   [&](Ev ev) {
+                     return launch_hist(src, nb, b->parts, b->bparts, b->rep[PHPRNG_TEST_POKER], b->d_bits, st, ev);
                    })) != PHPRNG_OK ||
-        (s = timed(b, 1, st, "collision kernel",
-                   [&] { return launch_collision(src, nb, b->rep[PHPRNG_TEST_COLLISION], st); })) != PHPRNG_OK ||
-        (s = timed(b, 2, st, "runs kernel",
-                   [&] { return launch_runs(b->d_bits, nb, b->rep[PHPRNG_TEST_RUNS], st); })) != PHPRNG_OK ||
-        (s = timed(b, 3, st, "fft pass 1", [&] { return launch_fft_pass1(src, nb, b->d_y, b->tw, st); })) != PHPRNG_OK ||
-        (s = timed(b, 4, st, "fft pass 2", [&] {
-           return launch_fft_pass2(b->d_y, nb, b->rep[PHPRNG_TEST_FOURIER], nullptr, b->tw, b->fourier_scale, st);
-         })) != PHPRNG_OK ||
-        (s = timed(b, 5, st, "histogram count", [&] { return ph::launch_count(b->parts, st); })) != PHPRNG_OK)
+        (s = timed(1, "collision kernel",
+                   [&](Ev ev) { return launch_collision(src, nb, b->rep[PHPRNG_TEST_COLLISION], st, ev); })) !=
+            PHPRNG_OK ||
+        (s = timed(2, "runs kernel",
+                   [&](Ev ev) { return launch_runs(b->d_bits, nb, b->rep[PHPRNG_TEST_RUNS], st, ev); })) != PHPRNG_OK ||
+        (s = timed(3, "fft pass 1", [&](Ev ev) { return launch_fft_pass1(src, nb, b->d_y, b->tw, st, ev); })) !=
+            PHPRNG_OK ||
+        (s = timed(4, "fft pass 2",
+                   [&](Ev ev) {
+                     return launch_fft_pass2(b->d_y, nb, b->rep[PHPRNG_TEST_FOURIER], nullptr, b->tw, b->fourier_scale,
+                                             st, ev);
+                   })) != PHPRNG_OK ||
+        (s = timed(5, "histogram count", [&](Ev ev) { return ph::launch_count(b->parts, st, ev); })) != PHPRNG_OK)
       return s;
   }
   // the small histograms' replicas into their histograms
-  if (nblocks) {
-    SmallHists S{};
-    const int tests[kSmallTests] = {PHPRNG_TEST_POKER, PHPRNG_TEST_COLLISION, PHPRNG_TEST_RUNS, PHPRNG_TEST_FOURIER};
-    for (int i = 0; i < kSmallTests; ++i) {
-      S.rep[i] = b->rep[tests[i]];
-      S.dst[i] = b->d_cat[tests[i]];
-      S.ncat[i] = kCats[tests[i]];
-    }
-    const hipError_t e = launch_fold(S, st);
-    if (e != hipSuccess) return hip_fail(b, e, "fold");
+  SmallHists S{};
+  const int tests[kSmallTests] = {PHPRNG_TEST_POKER, PHPRNG_TEST_COLLISION, PHPRNG_TEST_RUNS, PHPRNG_TEST_FOURIER};
+  for (int i = 0; i < kSmallTests; ++i) {
+    S.rep[i] = b->rep[tests[i]];
+    S.dst[i] = b->d_cat[tests[i]];
+    S.ncat[i] = kCats[tests[i]];
   }
+  const hipError_t e = launch_fold(S, st);
+  if (e != hipSuccess) return hip_fail(b, e, "fold");
   return PHPRNG_OK;
 }
 
@@ -423,6 +470,7 @@ phprng_status phprng_battery_report(phprng_battery *b, phprng_test_result *out, 
   }
   J.small = b->d_cat[PHPRNG_TEST_POKER];
   J.nsmall = (uint32_t)b->probs.size();
+  std::lock_guard<std::mutex> hold(b->report_lock);
   hipError_t e = launch_moments(J, b->report_moments, b->report_small, st);
   if (e == hipSuccess) e = hipStreamSynchronize(st);
   if (e != hipSuccess) return hip_fail(b, e, "report");
@@ -474,8 +522,18 @@ phprng_status phprng_battery_counts(phprng_battery *b, int test, uint64_t *out, 
   if (capacity < kCats[test]) return fail(b, PHPRNG_E_RANGE, "capacity below %u", kCats[test]);
   (void)hipSetDevice(b->device);
   hipStream_t st = (hipStream_t)stream;
-  hipError_t e = hipMemcpyAsync(out, b->d_cat[test], kCats[test] * sizeof(uint64_t), hipMemcpyDeviceToHost, st);
-  if (e == hipSuccess) e = hipStreamSynchronize(st);
+  hipError_t e;
+  if (test >= PHPRNG_TEST_POKER) {
+    // a small histogram: through the report's mapped memory
+    std::lock_guard<std::mutex> hold(b->report_lock);
+    e = launch_counts_out(b->d_cat[test], kCats[test], b->report_small, st);
+    if (e == hipSuccess) e = hipStreamSynchronize(st);
+    if (e == hipSuccess)
+      memcpy(out, static_cast<const Moments *>(b->h_report) + kReportMoments, kCats[test] * sizeof(uint64_t));
+  } else {
+    e = hipMemcpyAsync(out, b->d_cat[test], kCats[test] * sizeof(uint64_t), hipMemcpyDeviceToHost, st);
+    if (e == hipSuccess) e = hipStreamSynchronize(st);
+  }
   return e == hipSuccess ? PHPRNG_OK : hip_fail(b, e, "counts");
 }
 

@@ -13,9 +13,10 @@ namespace bat {
 namespace {
 
 // Bin of a uniform among B equal bins, clamped so that R = 1.0 (possible for
-// 64-bit moduli) falls in the last one.
+// 64-bit moduli) falls in the last one.  (The conversion truncates, and the
+// product is not negative.)
 __device__ __forceinline__ uint32_t bin_of(double x, uint32_t b) {
-  const uint32_t u = (uint32_t)floor(x * (double)b);
+  const uint32_t u = (uint32_t)(x * (double)b);
   return u < b ? u : b - 1;
 }
 
@@ -536,6 +537,13 @@ __global__ __launch_bounds__(256) void moments_kernel(MomentJobs J, Moments *out
   }
 }
 
+// A small histogram to mapped host memory (a copy to pageable memory takes
+// the host 25 us, this launch and the wait for it 12).
+__global__ __launch_bounds__(256) void counts_out_kernel(const unsigned long long *src, uint32_t n,
+                                                         unsigned long long *out) {
+  for (uint32_t i = threadIdx.x; i < n; i += 256) out[i] = src[i];
+}
+
 // out[t * S + a] = in[a * L + t] through a 64 x 64 LDS tile.
 __global__ __launch_bounds__(256) void interleave_kernel(const double *__restrict__ in, double *__restrict__ out,
                                                          uint64_t S, uint64_t L) {
@@ -555,37 +563,39 @@ __global__ __launch_bounds__(256) void interleave_kernel(const double *__restric
 }  // namespace
 
 hipError_t launch_hist(const double *r, uint64_t nblocks, const ph::PartSet &P, const BatteryParts &bp,
-                       unsigned long long *poker, uint64_t *bits, hipStream_t st) {
+                       unsigned long long *poker, uint64_t *bits, hipStream_t st, LaunchEvents ev) {
   clear_launch_error();
-  hist_kernel<<<dim3((unsigned)(nblocks * kHistTilesPerBlock)), dim3(kHistThreads), 0, st>>>(r, P, bp, poker, bits);
-  return hipGetLastError();
+  return launch_with(ev, hist_kernel, dim3((unsigned)(nblocks * kHistTilesPerBlock)), dim3(kHistThreads), st, r, P, bp,
+                     poker, bits);
 }
 
-hipError_t launch_collision(const double *r, uint64_t nblocks, unsigned long long *coll, hipStream_t st) {
+hipError_t launch_collision(const double *r, uint64_t nblocks, unsigned long long *coll, hipStream_t st,
+                            LaunchEvents ev) {
   clear_launch_error();
-  collision_kernel<<<dim3((unsigned)(nblocks * (kBlock / kCollBalls))), dim3(1024), 0, st>>>(r, coll);
-  return hipGetLastError();
+  return launch_with(ev, collision_kernel, dim3((unsigned)(nblocks * (kBlock / kCollBalls))), dim3(1024), st, r, coll);
 }
 
-hipError_t launch_runs(const uint64_t *bits, uint64_t nblocks, unsigned long long *runs, hipStream_t st) {
+hipError_t launch_runs(const uint64_t *bits, uint64_t nblocks, unsigned long long *runs, hipStream_t st,
+                       LaunchEvents ev) {
   clear_launch_error();
   const uint64_t nwords = nblocks * kWordsPerBlock;
-  runs_kernel<<<dim3((unsigned)(nwords / (256 * kRunsWords))), dim3(256), 0, st>>>(bits, runs);
-  return hipGetLastError();
+  return launch_with(ev, runs_kernel, dim3((unsigned)(nwords / (256 * kRunsWords))), dim3(256), st, bits, runs);
 }
 
-hipError_t launch_fft_pass1(const double *r, uint64_t nblocks, double2 *y, Twiddles tw, hipStream_t st) {
+hipError_t launch_fft_pass1(const double *r, uint64_t nblocks, double2 *y, Twiddles tw, hipStream_t st,
+                            LaunchEvents ev) {
   clear_launch_error();
-  fft_pass1_kernel<<<dim3((unsigned)(nblocks * kFftPass1Groups)), dim3(256), 0, st>>>(r, y, tw);
-  return hipGetLastError();
+  return launch_with(ev, fft_pass1_kernel, dim3((unsigned)(nblocks * kFftPass1Groups)), dim3(256), st, r, y, tw);
 }
 
 hipError_t launch_fft_pass2(const double2 *y, uint64_t nblocks, unsigned long long *fourier, double *coef,
-                            Twiddles tw, double scale, hipStream_t st) {
+                            Twiddles tw, double scale, hipStream_t st, LaunchEvents ev) {
   clear_launch_error();
-  fft_pass2_pairs_kernel<<<dim3((unsigned)(nblocks * kP2PairRows)), dim3(128), 0, st>>>(y, fourier, coef, tw, scale);
-  fft_pass2_self_kernel<<<dim3((unsigned)(nblocks * 2)), dim3(128), 0, st>>>(y, fourier, coef, tw, scale);
-  return hipGetLastError();
+  const hipError_t e = launch_with({ev.start, nullptr}, fft_pass2_pairs_kernel, dim3((unsigned)(nblocks * kP2PairRows)),
+                                   dim3(128), st, y, fourier, coef, tw, scale);
+  if (e != hipSuccess) return e;
+  return launch_with({nullptr, ev.stop}, fft_pass2_self_kernel, dim3((unsigned)(nblocks * 2)), dim3(128), st, y,
+                     fourier, coef, tw, scale);
 }
 
 hipError_t launch_fold(const SmallHists &S, hipStream_t st) {
@@ -593,6 +603,12 @@ hipError_t launch_fold(const SmallHists &S, hipStream_t st) {
   uint32_t cats = 0;
   for (uint32_t n : S.ncat) cats += n;
   fold_kernel<<<dim3(cats), dim3(kRep), 0, st>>>(S);
+  return hipGetLastError();
+}
+
+hipError_t launch_counts_out(const unsigned long long *src, uint32_t n, unsigned long long *out, hipStream_t st) {
+  clear_launch_error();
+  counts_out_kernel<<<dim3(1), dim3(256), 0, st>>>(src, n, out);
   return hipGetLastError();
 }
 

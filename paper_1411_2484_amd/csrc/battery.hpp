@@ -6,6 +6,7 @@
 
 #include <cstdint>
 
+#include "launch.hpp"
 #include "phist.hpp"
 
 namespace phprng {
@@ -86,14 +87,21 @@ struct SmallHists {
 };
 
 hipError_t launch_hist(const double *r, uint64_t nblocks, const ph::PartSet &P, const BatteryParts &bp,
-                       unsigned long long *poker_rep, uint64_t *bits, hipStream_t st);
-hipError_t launch_collision(const double *r, uint64_t nblocks, unsigned long long *coll_rep, hipStream_t st);
-hipError_t launch_runs(const uint64_t *bits, uint64_t nblocks, unsigned long long *runs_rep, hipStream_t st);
-hipError_t launch_fft_pass1(const double *r, uint64_t nblocks, double2 *y, Twiddles tw, hipStream_t st);
+                       unsigned long long *poker_rep, uint64_t *bits, hipStream_t st,
+                       LaunchEvents ev = {});
+hipError_t launch_collision(const double *r, uint64_t nblocks, unsigned long long *coll_rep, hipStream_t st,
+                       LaunchEvents ev = {});
+hipError_t launch_runs(const uint64_t *bits, uint64_t nblocks, unsigned long long *runs_rep, hipStream_t st,
+                       LaunchEvents ev = {});
+hipError_t launch_fft_pass1(const double *r, uint64_t nblocks, double2 *y, Twiddles tw, hipStream_t st,
+                       LaunchEvents ev = {});
 // coef (may be null): per block, M doubles = (Re, Im) of coefficients 0 .. M/2 - 1.
 hipError_t launch_fft_pass2(const double2 *y, uint64_t nblocks, unsigned long long *fourier_rep, double *coef,
-                            Twiddles tw, double scale, hipStream_t st);
+                            Twiddles tw, double scale, hipStream_t st,
+                       LaunchEvents ev = {});
 hipError_t launch_fold(const SmallHists &S, hipStream_t st);
+// src[0 .. n) to host memory mapped for the device.
+hipError_t launch_counts_out(const unsigned long long *src, uint32_t n, unsigned long long *out, hipStream_t st);
 // out: [kPartTests][kMomentSlices], small_out: J.nsmall counts, both host memory mapped for the device.
 hipError_t launch_moments(const MomentJobs &J, Moments *out, unsigned long long *small_out, hipStream_t st);
 hipError_t launch_interleave(const double *in, double *out, uint64_t nstreams, uint64_t length, hipStream_t st);

@@ -24,7 +24,6 @@
 // A chunk is a run of consecutive tiles of one request; a wave carries the
 // state from one tile to the next within a chunk.
 #include <hip/hip_runtime.h>
-#include <hip/hip_ext.h>
 
 #include <algorithm>
 #include <cstddef>
@@ -1136,16 +1135,6 @@ hipError_t launch_position64(const InstRec *inst, const uint32_t *ids, const uin
   unsigned blocks = (unsigned)((count + 255) / 256);
   hipLaunchKernelGGL(position64_kernel, dim3(blocks), dim3(256), 0, st, inst, ids, m0, ta, tb, count, u_lo, u_hi, u_s,
                      m64);
-  return hipGetLastError();
-}
-
-// A launch that completes the given events, or a plain one without any.
-template <class K, class... Args>
-static hipError_t launch_with(LaunchEvents ev, K kernel, unsigned grid, unsigned block, hipStream_t st, Args... args) {
-  if (ev.start || ev.stop)
-    hipExtLaunchKernelGGL(kernel, dim3(grid), dim3(block), 0, st, ev.start, ev.stop, 0, args...);
-  else
-    hipLaunchKernelGGL(kernel, dim3(grid), dim3(block), 0, st, args...);
   return hipGetLastError();
 }
 

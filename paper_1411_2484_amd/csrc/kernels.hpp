@@ -3,6 +3,7 @@
 
 #include <hip/hip_runtime.h>
 
+#include "launch.hpp"
 #include "layout.hpp"
 
 namespace phprng {
@@ -24,14 +25,6 @@ static_assert(kScratchTileOff % 256 == 0, "tile arrays aligned");
 // `device`).  The first call on a device looks the address up and clears the
 // work counter; later calls return the kept address.
 hipError_t scratch_address(int device, void **ptr);
-
-// Events that a launch completes by itself: `start` when its kernel begins,
-// `stop` when it ends (either may be null).  They ride on the kernel's own
-// packet; an event recorded beside it costs the host 5 us more (launch and
-// stop event 4.7 against 9.5 us, with a start event 10.2 against 14.2 us).
-struct LaunchEvents {
-  hipEvent_t start = nullptr, stop = nullptr;
-};
 
 hipError_t launch_table_segments32(uint64_t nseg, uint64_t *seg_sum, uint32_t *seg_start, hipStream_t st);
 hipError_t launch_table_segments64(uint64_t nseg, uint64_t *seg_lo, uint64_t *seg_hi, uint64_t *seg_start,

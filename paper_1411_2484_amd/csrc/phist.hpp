@@ -22,6 +22,8 @@
 
 #include <cstdint>
 
+#include "launch.hpp"
+
 namespace phprng {
 namespace ph {
 
@@ -115,7 +117,7 @@ __device__ __forceinline__ void scatter_staged(const uint32_t (&key)[K], const P
 }
 
 // Stages 2 and 3.
-hipError_t launch_count(const PartSet &P, hipStream_t st);
+hipError_t launch_count(const PartSet &P, hipStream_t st, LaunchEvents ev = {});
 
 }  // namespace ph
 }  // namespace phprng
