@@ -38,92 +38,117 @@ __device__ __forceinline__ uint32_t poker_cat(const uint32_t d[5]) {
   return pairs <= 4 ? pairs : (pairs == 6 ? 5u : 6u);
 }
 
+// Registers per thread for the keys of one tile: 8 + 4 + 3 + 2 + 2.
+constexpr int kT = (int)kHistThreads;
+constexpr int key_slots(int d) { return ((int)kHistTile / d + kT - 1) / kT; }
+constexpr int key_base(int d) { return d == 1 ? 0 : key_base(d - 1) + key_slots(d - 1); }
+constexpr int kKeys = key_base(6);
+// the test (tuple size) of a key slot, and its first item; plain expressions
+// of constants, which fold wherever the slot is one
+constexpr int kB2 = key_base(2), kB3 = key_base(3), kB4 = key_base(4), kB5 = key_base(5);
+__device__ __forceinline__ uint32_t key_test(int slot) {
+  return 1u + (slot >= kB2) + (slot >= kB3) + (slot >= kB4) + (slot >= kB5);
+}
+__device__ __forceinline__ uint32_t key_first(int slot) {
+  return (uint32_t)(slot - (slot >= kB5 ? kB5 : slot >= kB4 ? kB4 : slot >= kB3 ? kB3 : slot >= kB2 ? kB2 : 0)) *
+         kHistThreads;
+}
+
+// Whether a thread has a key in a slot: FULL (a whole tile of kHistTile
+// uniforms) by the wave's first thread `wbase` alone, since every test has a
+// multiple of 64 tuples.
+template <bool FULL>
+__device__ __forceinline__ bool has_key(int slot, uint32_t len, uint32_t wbase) {
+  const uint32_t d = key_test(slot), first = key_first(slot);
+  if constexpr (FULL) {
+    static_assert(kHistTile % (64 * 60) == 0, "whole waves of tuples of every size");
+    return first + kHistThreads <= kHistTile / d || first + wbase < kHistTile / d;
+  } else {
+    return first + threadIdx.x < len / d;
+  }
+}
+
 // Keys of one test for one tile, held in registers for the partitioned
 // histogram: item j = threadIdx.x + it * kHistThreads is the j-th D-tuple of
 // the tile (D = 1: the j-th uniform), its key the partition-space offset of
 // the test plus its cell (first element most significant).  The cells come
 // from each uniform's bins, found once per uniform: b20 among 2^20 bins, whose
 // top 10, 5 and 4 bits are the bins among 1024, 32 and 16 (x 2^k is exact, so
-// floor(x 2^k) = floor(x 2^20) >> (20 - k)), and b100 among 100.
-template <int D, int K>
-__device__ __forceinline__ void tuple_keys(const uint32_t *b20, const uint8_t *b100, uint32_t len, uint32_t key0,
-                                           uint32_t *key) {
+// floor(x 2^k) = floor(x 2^20) >> (20 - k)), and b100 among 100, in the low
+// byte of dec (b10, among 10, is the high byte).
+template <int D, bool FULL>
+__device__ __forceinline__ void tuple_keys(const uint32_t *b20, const uint8_t *dec, uint32_t len, uint32_t wbase,
+                                           uint32_t key0, uint32_t *key) {
   static_assert(kFreqBins == 1u << 20 && kAxis2 == 1024 && kAxis3 == 100 && kAxis4 == 32 && kAxis5 == 16,
                 "bins derived from the 2^20 bin");
-  const uint32_t ntup = len / D;
+  constexpr int kSlots = key_slots(D), kBase = key_base(D);
 #pragma unroll
-  for (int it = 0; it < K; ++it) {
+  for (int it = 0; it < kSlots; ++it) {
     const uint32_t j = threadIdx.x + it * kHistThreads;
     uint32_t cell = 0;
-    if (j < ntup) {
+    if (has_key<FULL>(kBase + it, len, wbase)) {
       if constexpr (D == 1) {
         cell = b20[j];
       } else if constexpr (D == 3) {
-        cell = (b100[3 * j] * 100u + b100[3 * j + 1]) * 100u + b100[3 * j + 2];
+        cell = (dec[6 * j] * 100u + dec[6 * j + 2]) * 100u + dec[6 * j + 4];
       } else {
         constexpr int kShift = D == 2 ? 10 : (D == 4 ? 15 : 16), kBits = 20 - kShift;
 #pragma unroll
         for (int i = 0; i < D; ++i) cell = (cell << kBits) | (b20[j * D + i] >> kShift);
       }
     }
-    key[it] = j < ntup ? key0 + cell : ph::kNoKey;
+    key[kBase + it] = key0 + cell;
   }
 }
-
-// Registers per thread for the keys of one tile: 8 + 4 + 3 + 2 + 2.
-constexpr int kT = (int)kHistThreads;
-constexpr int kK1 = (kHistTile + kT - 1) / kT, kK2 = (kHistTile / 2 + kT - 1) / kT, kK3 = (kHistTile / 3 + kT - 1) / kT;
-constexpr int kK4 = (kHistTile / 4 + kT - 1) / kT, kK5 = (kHistTile / 5 + kT - 1) / kT;
-constexpr int kKeys = kK1 + kK2 + kK3 + kK4 + kK5;
 
 // One tile of one block: frequency and serial D = 2..5 keys into the
 // partitioned histograms, the poker histogram, and the bits R > 1/2 packed
 // one 64-bit word per 64 uniforms (for the runs test).
-__global__ __launch_bounds__(kHistThreads, 8) void hist_kernel(const double *__restrict__ r, ph::PartSet P, BatteryParts bp,
-                                                   unsigned long long *poker_hist, uint64_t *__restrict__ bits) {
-  // the tile's bins (b20 among 2^20, b100 among 100, b10 among 10 for the
-  // poker digits), later reused as the key staging area of the scatter
-  __shared__ __align__(16) uint32_t buf[kKeys * kHistThreads];
-  static_assert(kKeys * kHistThreads * 4 >= kHistTile * 6, "staging area must hold the tile's bins");
-  __shared__ uint32_t poker[kPokerCats];
-  __shared__ uint32_t cnt[kMaxParts], poff[kMaxParts], base[kMaxParts];
-  uint32_t *b20 = buf;
-  uint8_t *b100 = reinterpret_cast<uint8_t *>(buf + kHistTile), *b10 = b100 + kHistTile;
-  const uint32_t tile = blockIdx.x % kHistTilesPerBlock;
-  const uint64_t blk = blockIdx.x / kHistTilesPerBlock;
-  const uint32_t off = tile * kHistTile;
-  const uint32_t len = (kBlock - off) < kHistTile ? (kBlock - off) : kHistTile;  // 7680 or 4096
-  const uint64_t base_i = blk * kBlock + off;
-  if (threadIdx.x < kPokerCats) poker[threadIdx.x] = 0;
+struct HistShared {
+  // the tile's bins (b20 among 2^20; 16 bits with b100 among 100 and b10 among
+  // 10, the poker digits), later reused as the key staging area of the scatter
+  uint32_t buf[kKeys * kHistThreads];
+  uint32_t poker[kPokerCats];
+  uint32_t cnt[kMaxParts], poff[kMaxParts], base[kMaxParts];
+};
+static_assert(kKeys * kHistThreads * 4 >= kHistTile * 6, "staging area must hold the tile's bins");
+
+template <bool FULL>
+__device__ __forceinline__ void hist_tile(const double *__restrict__ r, const ph::PartSet &P, const BatteryParts &bp,
+                                          unsigned long long *poker_hist, uint64_t *__restrict__ bits,
+                                          uint64_t base_i, uint32_t len, HistShared &S) {
+  uint32_t *b20 = S.buf;
+  uint16_t *dec = reinterpret_cast<uint16_t *>(S.buf + kHistTile);
+  const uint8_t *dec8 = reinterpret_cast<const uint8_t *>(dec);
+  if (threadIdx.x < kPokerCats) S.poker[threadIdx.x] = 0;
   // all of the thread's loads in flight at once (a loop that waits for each
   // load before the next pays the memory latency every step), then the LDS
   // copy and the run bits; len is a multiple of 64, so the bounds test is
   // uniform over a wave and every wave covers 64 consecutive uniforms per step
   constexpr uint32_t kPer = (kHistTile + kHistThreads - 1) / kHistThreads;
   static_assert(kHistTile % 64 == 0 && (kBlock % kHistTile) % 64 == 0, "whole wave steps");
+  const uint32_t lane = threadIdx.x & 63, wbase = dev::uniform_u32(threadIdx.x - lane);
   double x[kPer];
 #pragma unroll
-  for (uint32_t k = 0; k < kPer; ++k) {
-    const uint32_t i = threadIdx.x + kHistThreads * k;
-    x[k] = i < len ? r[base_i + i] : 0.0;
-  }
+  for (uint32_t k = 0; k < kPer; ++k)
+    x[k] = wbase + kHistThreads * k < len ? r[base_i + threadIdx.x + kHistThreads * k] : 0.0;
   // the wave's k-th run-bit word is kept by lane k and all are stored at the
   // end with one instruction: a store inside the loop would make every later
   // step wait for it
-  const uint32_t lane = threadIdx.x & 63, wbase = threadIdx.x - lane;
-  uint64_t mine = 0;
+  uint32_t mine_lo = 0, mine_hi = 0;
 #pragma unroll
   for (uint32_t k = 0; k < kPer; ++k) {
     const uint32_t i = threadIdx.x + kHistThreads * k;
-    if (i < len) {
+    if (wbase + kHistThreads * k < len) {
       b20[i] = bin_of(x[k], kFreqBins);
-      b100[i] = (uint8_t)bin_of(x[k], kAxis3);
-      b10[i] = (uint8_t)bin_of(x[k], 10);
+      dec[i] = (uint16_t)(bin_of(x[k], kAxis3) | bin_of(x[k], 10) << 8);
       const uint64_t word = __ballot(x[k] > 0.5);
-      if (lane == k) mine = word;
+      mine_lo = lane == k ? (uint32_t)word : mine_lo;
+      mine_hi = lane == k ? (uint32_t)(word >> 32) : mine_hi;
     }
   }
-  if (lane < kPer && wbase + kHistThreads * lane < len) bits[(base_i + wbase + kHistThreads * lane) >> 6] = mine;
+  if (lane < kPer && wbase + kHistThreads * lane < len)
+    bits[(base_i + wbase + kHistThreads * lane) >> 6] = (uint64_t)mine_hi << 32 | mine_lo;
   __syncthreads();
   // poker: a wave counts its hands per category with ballots and adds each
   // count once (an LDS atomic per hand queued on the seven addresses)
@@ -134,10 +159,10 @@ __global__ __launch_bounds__(kHistThreads, 8) void hist_kernel(const double *__r
   for (uint32_t j0 = wbase; j0 < nhand; j0 += kHistThreads) {  // wave-uniform bound
     const uint32_t j = j0 + lane;
     uint32_t cat = kPokerCats;  // lanes past the last hand count nowhere
-    if (j < nhand) {
+    if (FULL || j < nhand) {
       uint32_t d[5];
 #pragma unroll
-      for (int i = 0; i < 5; ++i) d[i] = b10[j * 5 + i];
+      for (int i = 0; i < 5; ++i) d[i] = dec8[10 * j + 2 * i + 1];
       cat = poker_cat(d);
     }
 #pragma unroll
@@ -147,20 +172,37 @@ __global__ __launch_bounds__(kHistThreads, 8) void hist_kernel(const double *__r
     uint32_t v = 0;
 #pragma unroll
     for (uint32_t c = 0; c < kPokerCats; ++c) v = lane == c ? wcount[c] : v;
-    if (v) atomicAdd(&poker[lane], v);
+    if (v) atomicAdd(&S.poker[lane], v);
   }
   // all five tests' keys of the tile in registers, then one scatter over the
   // partition space (its first barrier orders the last reads of the tile
   // before the staging area is overwritten)
   uint32_t key[kKeys];
-  tuple_keys<1, kK1>(b20, b100, len, bp.p0[0] << ph::kPartBits, key);
-  tuple_keys<2, kK2>(b20, b100, len, bp.p0[1] << ph::kPartBits, key + kK1);
-  tuple_keys<3, kK3>(b20, b100, len, bp.p0[2] << ph::kPartBits, key + kK1 + kK2);
-  tuple_keys<4, kK4>(b20, b100, len, bp.p0[3] << ph::kPartBits, key + kK1 + kK2 + kK3);
-  tuple_keys<5, kK5>(b20, b100, len, bp.p0[4] << ph::kPartBits, key + kK1 + kK2 + kK3 + kK4);
-  ph::scatter_staged<kHistThreads, kKeys>(key, P, 0, P.npart, cnt, poff, base, buf);
-  if (threadIdx.x < kPokerCats && poker[threadIdx.x])
-    atomicAdd(&poker_hist[(blockIdx.x % kRep) * kPokerCats + threadIdx.x], (unsigned long long)poker[threadIdx.x]);
+  tuple_keys<1, FULL>(b20, dec8, len, wbase, bp.p0[0] << ph::kPartBits, key);
+  tuple_keys<2, FULL>(b20, dec8, len, wbase, bp.p0[1] << ph::kPartBits, key);
+  tuple_keys<3, FULL>(b20, dec8, len, wbase, bp.p0[2] << ph::kPartBits, key);
+  tuple_keys<4, FULL>(b20, dec8, len, wbase, bp.p0[3] << ph::kPartBits, key);
+  tuple_keys<5, FULL>(b20, dec8, len, wbase, bp.p0[4] << ph::kPartBits, key);
+  ph::scatter_staged<kHistThreads, kKeys>(key, P, 0, P.npart, S.cnt, S.poff, S.base, S.buf,
+                                          [&](int slot) { return has_key<FULL>(slot, len, wbase); });
+  if (threadIdx.x < kPokerCats && S.poker[threadIdx.x])
+    atomicAdd(&poker_hist[(blockIdx.x % kRep) * kPokerCats + threadIdx.x], (unsigned long long)S.poker[threadIdx.x]);
+}
+
+// The last tile of a block (4096 of its 2^20 uniforms) tests every key; the
+// 136 whole ones before it know theirs by the wave.  2^26 uniforms: 238 us (79
+// vector instructions per uniform, and about half of the LDS turns), against
+// 266 with a test per key in every tile (99).
+__global__ __launch_bounds__(kHistThreads, 8) void hist_kernel(const double *__restrict__ r, ph::PartSet P,
+                                                               BatteryParts bp, unsigned long long *poker_hist,
+                                                               uint64_t *__restrict__ bits) {
+  __shared__ __align__(16) HistShared S;
+  const uint32_t tile = blockIdx.x % kHistTilesPerBlock;
+  const uint64_t base_i = (uint64_t)(blockIdx.x / kHistTilesPerBlock) * kBlock + tile * kHistTile;
+  if (tile + 1 < kHistTilesPerBlock)
+    hist_tile<true>(r, P, bp, poker_hist, bits, base_i, kHistTile, S);
+  else
+    hist_tile<false>(r, P, bp, poker_hist, bits, base_i, kBlock - tile * kHistTile, S);
 }
 
 // One collision trial per workgroup: 2^14 uniforms into 2^20 urns held as a
