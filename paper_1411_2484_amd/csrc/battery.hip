@@ -376,10 +376,11 @@ __global__ __launch_bounds__(256) void fft_pass1_kernel(const double *__restrict
   }
 }
 
-__device__ __forceinline__ uint32_t fourier_cat(double v, double scale) {
-  const double u = floor(v * scale);
-  const double c = u < -kFourierHalf - 1 ? (double)(-kFourierHalf - 1) : (u > kFourierHalf ? (double)kFourierHalf : u);
-  return (uint32_t)(int)(c + kFourierHalf + 1);
+// Category of a coefficient's part, less kFourierHalf + 1 (a value that is not
+// a number falls in the first).
+__device__ __forceinline__ int fourier_bin(double v, double scale) {
+  const int u = (int)fmax(floor(v * scale), (double)(-kFourierHalf - 1));
+  return min(u, kFourierHalf);
 }
 
 // Pass 2: the 1024-point transforms of rows k1 and 512 - k1 (rows 0 and 256
@@ -388,17 +389,28 @@ __device__ __forceinline__ uint32_t fourier_cat(double v, double scale) {
 //   E = (F_k + conj F_{N-k}) / 2,  O = (F_k - conj F_{N-k}) / (2i),
 //   X_k = E + w_M^k O,  X_{N-k} = conj(E - w_M^k O),
 // scaled by 1/sqrt(M), and the categories of their real and imaginary parts.
-// split_and_bin takes A = F_k, B = F_{N-k} and wk = w_M^k.
+// split_and_bin takes A = F_k, B = F_{N-k} and wk = w_M^k.  The categories are
+// counted in kFourierRep copies, lane by lane: a third of the coefficients
+// fall in eight categories, and lanes that count in one of them queue.
+constexpr int kFourierRep = 4;
+__device__ __forceinline__ void add_fourier(unsigned long long *hist, const uint32_t *h) {
+  if (threadIdx.x >= kFourierCats) return;
+  uint32_t v = 0;
+#pragma unroll
+  for (int k = 0; k < kFourierRep; ++k) v += h[threadIdx.x * kFourierRep + k];
+  if (v) atomicAdd(&hist[(blockIdx.x % kRep) * kFourierCats + threadIdx.x], (unsigned long long)v);
+}
 __device__ __forceinline__ void split_and_bin(double2 A, double2 B, double2 wk, uint32_t k, double scale,
                                               uint32_t *h, double *cb) {
+  h += (kFourierHalf + 1) * kFourierRep + (threadIdx.x & (kFourierRep - 1));
   const double fs = 1.0 / 1024.0;  // 1 / sqrt(M), exact
   const double ar = A.x, ai = A.y, br = B.x, bi = B.y;
   const double er = (ar + br) * 0.5, ei = (ai - bi) * 0.5;
   const double orr = (ai + bi) * 0.5, oi = (br - ar) * 0.5;
   const double tr = orr * wk.x - oi * wk.y, ti = orr * wk.y + oi * wk.x;
   const double xr = (er + tr) * fs, xi = (ei + ti) * fs;
-  atomicAdd(&h[fourier_cat(xr, scale)], 1u);
-  atomicAdd(&h[fourier_cat(xi, scale)], 1u);
+  atomicAdd(&h[fourier_bin(xr, scale) * kFourierRep], 1u);
+  atomicAdd(&h[fourier_bin(xi, scale) * kFourierRep], 1u);
   if (cb) {
     cb[2 * k] = xr;
     cb[2 * k + 1] = xi;
@@ -406,8 +418,8 @@ __device__ __forceinline__ void split_and_bin(double2 A, double2 B, double2 wk, 
   const uint32_t kp = (kFftN - k) % kFftN;
   if (kp != k) {  // the partner coefficient, unless it is the same one (k = 0 or N/2)
     const double pr = (er - tr) * fs, pi = -(ei - ti) * fs;
-    atomicAdd(&h[fourier_cat(pr, scale)], 1u);
-    atomicAdd(&h[fourier_cat(pi, scale)], 1u);
+    atomicAdd(&h[fourier_bin(pr, scale) * kFourierRep], 1u);
+    atomicAdd(&h[fourier_bin(pi, scale) * kFourierRep], 1u);
     if (cb) {
       cb[2 * kp] = pr;
       cb[2 * kp + 1] = pi;
@@ -430,11 +442,11 @@ __global__ __launch_bounds__(128) void fft_pass2_pairs_kernel(const double2 *__r
   constexpr int L = kFftN2;
   __shared__ __align__(16) double buf[2 * kP2Half];
   static_assert(8 * 64 * 2 <= kP2Half && (kP2Half * 8) % 16 == 0, "swap slots fit the area");
-  __shared__ uint32_t h[kFourierCats];
+  __shared__ uint32_t h[kFourierCats * kFourierRep];
   const uint64_t blk = blockIdx.x / kP2PairRows;
   const uint32_t ra = 1 + blockIdx.x % kP2PairRows, rb = kFftN1 - ra;
   const uint32_t w = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  if (threadIdx.x < kFourierCats) h[threadIdx.x] = 0;
+  for (uint32_t i = threadIdx.x; i < kFourierCats * kFourierRep; i += 128) h[i] = 0;
   const double2 *row = y + blk * (uint64_t)kFftN + (uint64_t)(w ? rb : ra) * L;
   double *area = buf + w * kP2Half;
   double2 v[16];
@@ -468,8 +480,7 @@ __global__ __launch_bounds__(128) void fft_pass2_pairs_kernel(const double2 *__r
     wc = cmul(wc, step);
   }
   __syncthreads();
-  if (threadIdx.x < kFourierCats && h[threadIdx.x])
-    atomicAdd(&hist[(blockIdx.x % kRep) * kFourierCats + threadIdx.x], (unsigned long long)h[threadIdx.x]);
+  add_fourier(hist, h);
 }
 
 // Rows 0 and 256, each paired with itself: one wave per copy of the row,
@@ -481,11 +492,11 @@ __global__ __launch_bounds__(128) void fft_pass2_self_kernel(const double2 *__re
                                                              double *__restrict__ coef, Twiddles tw, double scale) {
   constexpr int L = kFftN2;
   __shared__ double2 buf[2 * kP2Area];
-  __shared__ uint32_t h[kFourierCats];
+  __shared__ uint32_t h[kFourierCats * kFourierRep];
   const uint64_t blk = blockIdx.x >> 1;
   const uint32_t ra = (blockIdx.x & 1) ? kFftN1 / 2 : 0u;
   const uint32_t w = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  if (threadIdx.x < kFourierCats) h[threadIdx.x] = 0;
+  for (uint32_t i = threadIdx.x; i < kFourierCats * kFourierRep; i += 128) h[i] = 0;
   const double2 *row = y + blk * (uint64_t)kFftN + (uint64_t)ra * L;
   double2 *area = buf + w * kP2Area;
   double2 v[16];
@@ -509,8 +520,7 @@ __global__ __launch_bounds__(128) void fft_pass2_self_kernel(const double2 *__re
     split_and_bin(buf[pa], buf[pb], wk, ra + kFftN1 * k2, scale, h, cb);
   }
   __syncthreads();
-  if (threadIdx.x < kFourierCats && h[threadIdx.x])
-    atomicAdd(&hist[(blockIdx.x % kRep) * kFourierCats + threadIdx.x], (unsigned long long)h[threadIdx.x]);
+  add_fourier(hist, h);
 }
 
 // One workgroup per category of the four small histograms: dst[c] += sum of
