@@ -290,7 +290,7 @@ phprng_status histogram(const phprng_pattern &P, uint64_t ncell, const Rounds &R
   ph::PartSet PS;
   PS.data = (uint16_t *)cm;
   PS.slices = (uint32_t *)(cm + R.off_slices);
-  // table: hist pointers[npart] | fill[npart][nsub] | ncell[npart]
+  // table: hist pointers[npart] | fill[nsub][npart] | ncell[npart]
   unsigned long long **hist_d = (unsigned long long **)(cm + R.off_table);
   PS.fill = (uint32_t *)(hist_d + R.npart);
   PS.ncell = PS.fill + (uint64_t)R.npart * R.nsub;

@@ -19,7 +19,7 @@ __global__ __launch_bounds__(1024) void count_kernel(PartSet P) {
   for (uint32_t i = threadIdx.x; i < kPartCells; i += 1024) c[i] = 0;
   __syncthreads();
   for (uint32_t sb = 0; sb < P.nsub; ++sb) {
-    const uint32_t f = P.fill[p * P.nsub + sb];
+    const uint32_t f = P.fill[sb * P.npart + p];
     const uint32_t fill = f < P.cap ? f : P.cap;
     // slice bounds on 8-entry (16-byte) boundaries, the last slice takes the tail
     const uint32_t lo = (uint32_t)((uint64_t)fill * s / P.nslice) & ~7u;
@@ -63,7 +63,7 @@ __global__ __launch_bounds__(1024) void count_kernel(PartSet P) {
       for (uint32_t u = 0; u < kU; ++u)
         if (i0 + 1024 * u < nc) h[i0 + 1024 * u] = v[u] + c[i0 + 1024 * u];
     }
-    if (threadIdx.x < P.nsub) P.fill[p * P.nsub + threadIdx.x] = 0;
+    if (threadIdx.x < P.nsub) P.fill[threadIdx.x * P.npart + p] = 0;
   } else {
     uint32_t *out = P.slices + ((uint64_t)p * P.nslice + s) * kPartCells;
     for (uint32_t i = threadIdx.x; i < nc; i += 1024) out[i] = c[i];
@@ -75,7 +75,7 @@ __global__ __launch_bounds__(1024) void count_kernel(PartSet P) {
 __global__ __launch_bounds__(256) void add_kernel(PartSet P) {
   const uint32_t p = blockIdx.x / (kPartCells / 256);
   const uint32_t j = (blockIdx.x % (kPartCells / 256)) * 256 + threadIdx.x;
-  if (j < P.nsub) P.fill[p * P.nsub + j] = 0;
+  if (j < P.nsub) P.fill[j * P.npart + p] = 0;
   if (j >= P.ncell[p]) return;
   const uint32_t *in = P.slices + (uint64_t)p * P.nslice * kPartCells + j;
   unsigned long long s = 0;

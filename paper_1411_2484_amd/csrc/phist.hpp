@@ -35,7 +35,7 @@ constexpr uint32_t kNoKey = 0xffffffffu;
 // npart * nsub * cap < 2^32: the scatter indexes the data with 32 bits.
 struct PartSet {
   uint16_t *data;                     // [npart][nsub][cap] cell offsets (16-byte aligned, cap a multiple of 8)
-  uint32_t *fill;                     // [npart][nsub] entries written this round
+  uint32_t *fill;                     // [nsub][npart] entries written this round
   unsigned long long *const *hist;    // [npart] first cell of each partition in its histogram
   const uint32_t *ncell;              // [npart] cells of each partition (<= 2^15)
   uint32_t *slices;                   // [npart][nslice][2^15] stage-2 counts
@@ -71,7 +71,7 @@ __device__ __forceinline__ void scatter_staged(const uint32_t (&key)[K], const P
   const uint32_t sub = blockIdx.x & (P.nsub - 1);
   for (uint32_t i = threadIdx.x; i < np; i += NT) {
     const uint32_t c = cnt[i];
-    base[i] = c ? atomicAdd(&P.fill[(p0 + i) * P.nsub + sub], c) : 0u;
+    base[i] = c ? atomicAdd(&P.fill[sub * P.npart + p0 + i], c) : 0u;
   }
   if (threadIdx.x < 64) {
     const uint32_t lane = threadIdx.x;
