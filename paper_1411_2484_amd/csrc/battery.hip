@@ -596,19 +596,41 @@ __global__ __launch_bounds__(256) void counts_out_kernel(const unsigned long lon
   for (uint32_t i = threadIdx.x; i < n; i += 256) out[i] = src[i];
 }
 
-// out[t * S + a] = in[a * L + t] through a 64 x 64 LDS tile.
+// out[t * S + a] = in[a * L + t] through a 64 x 64 LDS tile.  PAIRS: S and L
+// even and both arrays at 16-byte addresses, so that a whole tile moves two
+// uniforms per access with all of a thread's loads in flight; the tiles at the
+// ends, and any other shape, move one at a time.
+template <bool PAIRS>
 __global__ __launch_bounds__(256) void interleave_kernel(const double *__restrict__ in, double *__restrict__ out,
                                                          uint64_t S, uint64_t L) {
   __shared__ double tile[64][65];
   const uint64_t t0 = (uint64_t)blockIdx.x * 64, a0 = (uint64_t)blockIdx.y * 64;
-  for (uint32_t j = threadIdx.y; j < 64; j += 4) {
-    const uint64_t a = a0 + j, t = t0 + threadIdx.x;
-    if (a < S && t < L) tile[j][threadIdx.x] = in[a * L + t];
+  if (PAIRS && a0 + 64 <= S && t0 + 64 <= L) {
+    const uint32_t p = 2 * (threadIdx.x & 31), q = threadIdx.x >> 5;
+    double2 v[8];
+#pragma unroll
+    for (uint32_t k = 0; k < 8; ++k) v[k] = *reinterpret_cast<const double2 *>(in + (a0 + q + 8 * k) * L + t0 + p);
+#pragma unroll
+    for (uint32_t k = 0; k < 8; ++k) {
+      tile[q + 8 * k][p] = v[k].x;
+      tile[q + 8 * k][p + 1] = v[k].y;
+    }
+    __syncthreads();
+#pragma unroll
+    for (uint32_t k = 0; k < 8; ++k)
+      *reinterpret_cast<double2 *>(out + (t0 + q + 8 * k) * S + a0 + p) =
+          make_double2(tile[p][q + 8 * k], tile[p + 1][q + 8 * k]);
+    return;
+  }
+  const uint32_t x = threadIdx.x & 63, y = threadIdx.x >> 6;
+  for (uint32_t j = y; j < 64; j += 4) {
+    const uint64_t a = a0 + j, t = t0 + x;
+    if (a < S && t < L) tile[j][x] = in[a * L + t];
   }
   __syncthreads();
-  for (uint32_t j = threadIdx.y; j < 64; j += 4) {
-    const uint64_t t = t0 + j, a = a0 + threadIdx.x;
-    if (a < S && t < L) out[t * S + a] = tile[threadIdx.x][j];
+  for (uint32_t j = y; j < 64; j += 4) {
+    const uint64_t t = t0 + j, a = a0 + x;
+    if (a < S && t < L) out[t * S + a] = tile[x][j];
   }
 }
 
@@ -672,8 +694,13 @@ hipError_t launch_moments(const MomentJobs &J, Moments *out, unsigned long long 
 
 hipError_t launch_interleave(const double *in, double *out, uint64_t nstreams, uint64_t length, hipStream_t st) {
   clear_launch_error();
-  interleave_kernel<<<dim3((unsigned)((length + 63) / 64), (unsigned)((nstreams + 63) / 64)), dim3(64, 4), 0, st>>>(
-      in, out, nstreams, length);
+  const bool pairs = ((nstreams | length) & 1) == 0 &&
+                     ((reinterpret_cast<uintptr_t>(in) | reinterpret_cast<uintptr_t>(out)) & 15) == 0;
+  const dim3 grid((unsigned)((length + 63) / 64), (unsigned)((nstreams + 63) / 64));
+  if (pairs)
+    interleave_kernel<true><<<grid, dim3(256), 0, st>>>(in, out, nstreams, length);
+  else
+    interleave_kernel<false><<<grid, dim3(256), 0, st>>>(in, out, nstreams, length);
   return hipGetLastError();
 }
 
