@@ -4,6 +4,8 @@
 // chi-square reduction, and the interstream interleave.
 #include "battery.hpp"
 
+#include <algorithm>
+
 #include "arith.hpp"
 #include "wavefft.hpp"
 
@@ -205,37 +207,6 @@ __global__ __launch_bounds__(kHistThreads, 8) void hist_kernel(const double *__r
     hist_tile<false>(r, P, bp, poker_hist, bits, base_i, kBlock - tile * kHistTile, S);
 }
 
-// One collision trial per workgroup: 2^14 uniforms into 2^20 urns held as a
-// 128 KB bitmap in LDS; a ball that finds its bit already set is a collision.
-__global__ __launch_bounds__(1024) void collision_kernel(const double *__restrict__ r, unsigned long long *hist) {
-  __shared__ uint32_t bm[kCollUrns / 32];
-  __shared__ uint32_t total;
-  const double *src = r + (uint64_t)blockIdx.x * kCollBalls;
-  // the balls' loads go out before the bitmap is cleared, all at once
-  constexpr uint32_t kPer = kCollBalls / 1024;
-  double x[kPer];
-#pragma unroll
-  for (uint32_t k = 0; k < kPer; ++k) x[k] = src[threadIdx.x + 1024 * k];
-  for (uint32_t i = threadIdx.x; i < kCollUrns / 32; i += 1024) bm[i] = 0;
-  if (threadIdx.x == 0) total = 0;
-  __syncthreads();
-  uint32_t coll = 0;
-#pragma unroll
-  for (uint32_t k = 0; k < kPer; ++k) {
-    const uint32_t u = bin_of(x[k], kCollUrns);
-    const uint32_t bit = 1u << (u & 31);
-    const uint32_t old = atomicOr(&bm[u >> 5], bit);
-    coll += (old & bit) ? 1u : 0u;
-  }
-  for (int s = 32; s > 0; s >>= 1) coll += __shfl_xor(coll, s);
-  if ((threadIdx.x & 63) == 0) atomicAdd(&total, coll);
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    const uint32_t c = total < kCollLo ? kCollLo : (total > kCollHi ? kCollHi : total);
-    atomicAdd(&hist[(blockIdx.x % kRep) * kCollCats + (c - kCollLo)], 1ull);
-  }
-}
-
 // Sum of v over the wave, in lane 63 (all lanes active).
 __device__ __forceinline__ uint32_t wave_total(uint32_t v) {
   v += __builtin_amdgcn_update_dpp(0, (int)v, 0x111, 0xf, 0xf, false);  // row_shr:1
@@ -245,6 +216,56 @@ __device__ __forceinline__ uint32_t wave_total(uint32_t v) {
   v += __builtin_amdgcn_update_dpp(0, (int)v, 0x142, 0xa, 0xf, false);  // row_bcast:15
   v += __builtin_amdgcn_update_dpp(0, (int)v, 0x143, 0xc, 0xf, false);  // row_bcast:31
   return v;
+}
+
+constexpr uint32_t kCollGroups = 256;  // one per compute unit
+
+// Collision trials: 2^14 uniforms into 2^20 urns held as a 128 KB bitmap in
+// LDS; a ball that finds its bit already set is a collision (their number does
+// not depend on the order).  The bitmap leaves room for one workgroup per
+// compute unit, so a workgroup goes from trial to trial and has the next
+// trial's loads in flight while it works on the one before (2^26 uniforms:
+// 105 us, 5.1 TB/s; a workgroup per trial waited for its loads, 117 us).
+__global__ __launch_bounds__(1024) void collision_kernel(const double *__restrict__ r, uint32_t trials,
+                                                         unsigned long long *hist) {
+  __shared__ __align__(16) uint32_t bm[kCollUrns / 32];
+  __shared__ uint32_t total;
+  constexpr uint32_t kPer = kCollBalls / 1024 / 2;
+  double2 x[kPer];
+  const double2 *src = reinterpret_cast<const double2 *>(r) + (uint64_t)blockIdx.x * (kCollBalls / 2);
+#pragma unroll
+  for (uint32_t k = 0; k < kPer; ++k) x[k] = src[threadIdx.x + 1024 * k];
+  for (uint32_t trial = blockIdx.x; trial < trials; trial += gridDim.x) {
+    for (uint32_t i = threadIdx.x; i < kCollUrns / 128; i += 1024) reinterpret_cast<uint4 *>(bm)[i] = make_uint4(0, 0, 0, 0);
+    if (threadIdx.x == 0) total = 0;
+    uint32_t urn[2 * kPer];
+#pragma unroll
+    for (uint32_t k = 0; k < kPer; ++k) {
+      urn[2 * k] = bin_of(x[k].x, kCollUrns);
+      urn[2 * k + 1] = bin_of(x[k].y, kCollUrns);
+    }
+    if (trial + gridDim.x < trials) {
+      src += (uint64_t)gridDim.x * (kCollBalls / 2);
+#pragma unroll
+      for (uint32_t k = 0; k < kPer; ++k) x[k] = src[threadIdx.x + 1024 * k];
+    }
+    __syncthreads();
+    uint32_t coll = 0;
+#pragma unroll
+    for (uint32_t k = 0; k < 2 * kPer; ++k) {
+      const uint32_t bit = 1u << (urn[k] & 31);
+      const uint32_t old = atomicOr(&bm[urn[k] >> 5], bit);
+      coll += (old & bit) ? 1u : 0u;
+    }
+    coll = wave_total(coll);
+    if ((threadIdx.x & 63) == 63) atomicAdd(&total, coll);
+    __syncthreads();
+    if (threadIdx.x == 0) {
+      const uint32_t c = total < kCollLo ? kCollLo : (total > kCollHi ? kCollHi : total);
+      atomicAdd(&hist[(trial % kRep) * kCollCats + (c - kCollLo)], 1ull);
+    }
+    __syncthreads();  // the total is read before it is cleared
+  }
 }
 
 // Interior runs: kRunsWords 64-bit words of run bits per thread, 256 words
@@ -646,7 +667,8 @@ hipError_t launch_hist(const double *r, uint64_t nblocks, const ph::PartSet &P, 
 hipError_t launch_collision(const double *r, uint64_t nblocks, unsigned long long *coll, hipStream_t st,
                             LaunchEvents ev) {
   clear_launch_error();
-  return launch_with(ev, collision_kernel, dim3((unsigned)(nblocks * (kBlock / kCollBalls))), dim3(1024), st, r, coll);
+  const uint32_t trials = (uint32_t)(nblocks * (kBlock / kCollBalls));
+  return launch_with(ev, collision_kernel, dim3(std::min(trials, kCollGroups)), dim3(1024), st, r, trials, coll);
 }
 
 hipError_t launch_runs(const uint64_t *bits, uint64_t nblocks, unsigned long long *runs, hipStream_t st,
