@@ -250,7 +250,6 @@ struct phprng_ctx {
     for (auto &s : slots) {
       (void)hipFree(s.d_blk);
       if (s.h_blk) (void)hipHostFree(s.h_blk);
-      if (s.h_stamp) (void)hipHostFree(s.h_stamp);
       (void)hipFree(s.d_ctr);
       (void)hipFree(s.d_t64);
       if (s.ev0) (void)hipEventDestroy(s.ev0);
@@ -401,14 +400,6 @@ struct phprng_ctx {
     if (!s.ev0) {
       if ((e = hipEventCreate(&s.ev0)) != hipSuccess) return hip_fail(e, "event");
       if ((e = hipEventCreate(&s.ev1)) != hipSuccess) return hip_fail(e, "event");
-      if ((e = hipHostMalloc(&s.h_stamp, (kStampWaves + 1) * sizeof(uint64_t),
-                             hipHostMallocMapped | hipHostMallocCoherent)) != hipSuccess) {
-        s.h_stamp = nullptr;
-        return fail(PHPRNG_E_NOMEM, "timing buffer: %s", hipGetErrorString(e));
-      }
-      void *dp = nullptr;
-      if ((e = hipHostGetDevicePointer(&dp, s.h_stamp, 0)) != hipSuccess) return hip_fail(e, "timing buffer address");
-      s.h_stamp_dev = static_cast<uint64_t *>(dp);
       if ((e = hipMalloc(&s.d_ctr, sizeof(WorkCtr))) != hipSuccess) return fail(PHPRNG_E_NOMEM, "work counter");
       // the generation kernel expects a zero counter and leaves it so
       if ((e = hipMemset(s.d_ctr, 0, sizeof(WorkCtr))) != hipSuccess) return hip_fail(e, "work counter");
@@ -1133,9 +1124,21 @@ extern "C" phprng_status phprng_create(phprng_ctx **out, int device, uint64_t ma
   void *sp = nullptr;
   if (scratch_address(device, &sp) != hipSuccess || !sp) return PHPRNG_E_DEVICE;
   c->scratch = static_cast<uint8_t *>(sp);
-  if (hipHostMalloc(&c->h_noalloc, kNoAllocMaxRequests * sizeof(ReqRec), hipHostMallocDefault) != hipSuccess) {
+  // one pinned allocation (each takes the host a tenth of a millisecond): its
+  // staging block, then the time stamps of every slot
+  constexpr uint64_t kStageBytes = kNoAllocMaxRequests * sizeof(ReqRec);
+  if (hipHostMalloc(&c->h_noalloc,
+                    kStageBytes + phprng_ctx::kSlots * (phprng_ctx::kStampWaves + 1) * sizeof(uint64_t),
+                    hipHostMallocMapped | hipHostMallocCoherent) != hipSuccess) {
     c->h_noalloc = nullptr;
     return PHPRNG_E_NOMEM;
+  }
+  void *noalloc_dev = nullptr;
+  if (hipHostGetDevicePointer(&noalloc_dev, c->h_noalloc, 0) != hipSuccess || !noalloc_dev) return PHPRNG_E_DEVICE;
+  for (int i = 0; i < phprng_ctx::kSlots; ++i) {
+    const uint64_t off = kStageBytes + (uint64_t)i * (phprng_ctx::kStampWaves + 1) * sizeof(uint64_t);
+    c->slots[i].h_stamp = reinterpret_cast<uint64_t *>(c->h_noalloc + off);
+    c->slots[i].h_stamp_dev = reinterpret_cast<uint64_t *>(static_cast<uint8_t *>(noalloc_dev) + off);
   }
   if (hipEventCreateWithFlags(&c->noalloc_copied, hipEventDisableTiming) != hipSuccess) return PHPRNG_E_DEVICE;
   // every staging slot ready for typical batches (8192 requests, 2^16
