@@ -8,7 +8,7 @@ to HBM, one batched persistent launch per step (1,073,741,824 uniforms per
 step; each step continues every stream).  Beside it, in the same run:
 
   - the same batch as one launch per instance (the plain form), as a
-    captured-graph replay, with u32 ciphertexts too, on the unit skip;
+    prepared replay, with u32 ciphertexts too, on the unit skip;
   - 1 instance x 10^6 draws (c + R);
   - 65,536 instances with log-uniform lengths in [2^10, 2^22] and starts in
     [0, 2^40) (c + R over the fewest launches whose outputs fit the device,
@@ -82,9 +82,9 @@ def committed_counters(path=COUNTERS_FILE):
 
 
 def algorithmic_ops_32(e):
-    """VALU operations per width-32 draw in the minimal instruction model of
-    algorithm (9): skip 6, message 4, Montgomery products 6 each (e = 9: 5,
-    e = 17: 6, e = 3: 3, e = 5: 4), uniform 5."""
+    """VALU operations per width-32 draw in the plain form of algorithm (9)
+    (the kernel issues fewer per product): skip 6, message 4, Montgomery
+    products 6 each (e = 9: 5, e = 17: 6, e = 3: 3, e = 5: 4), uniform 5."""
     chain = {3: 3, 5: 4, 9: 5, 17: 6}[int(e)]
     return 6 + 4 + 6 * chain + 5
 
@@ -251,7 +251,7 @@ def section_headline(args, torch, ph, out):
         g.close()
         out["graph_replay"] = {"value": total / (gms * 1e-3) / 1e9, "unit": "Guniforms/s", "ms_per_step": gms,
                                "kernel_ms": gk,
-                               "note": "request block copied, then the captured persistent kernel replayed"}
+                               "note": "prepared request list, planned again and launched by each replay"}
         log("graph replay: %s" % out["graph_replay"])
     if not args.no_ciphertexts:
         c32 = torch.empty(total, dtype=torch.int32, device=dev)
@@ -672,7 +672,7 @@ def main():
     ap.add_argument("--cpu-seconds", type=float, default=15.0, help="oracle time on the host for the baseline")
     ap.add_argument("--no-plain", action="store_true")
     ap.add_argument("--no-ciphertexts", action="store_true", help="skip the u32 + f64 output variant")
-    ap.add_argument("--no-graph", action="store_true", help="skip the captured-graph replay variant")
+    ap.add_argument("--no-graph", action="store_true", help="skip the prepared replay variant")
     ap.add_argument("--no-unit-skip", action="store_true", help="skip the unit-skip schedule variant")
     ap.add_argument("--no-autotune", action="store_true", help="time the library's default launch shapes")
     ap.add_argument("--workload", default=None, choices=["F", "G"],
