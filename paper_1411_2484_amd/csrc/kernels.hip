@@ -866,8 +866,9 @@ __device__ void run_chunk64(const GenArgs &A, const InstRec &I, const ReqRec &R,
 
 // Rows of tile g of a constant-skip request: the pass writes u in
 // [u_lo, u_hi), and row u_lo / 64 starts at state index `state` + lane (one
-// row later, `state` + 64 + lane, when the tile's first row would start
-// before state 0).
+// row later, `state` + 64 + lane, when that row would start before state 0).
+// At the other end a row may run past the last state, 2^64 - 1: the lanes in
+// use lie below it, and arithmetic modulo 2^64 gives them their indexes.
 struct RowsCS {
   uint32_t u_lo, u_hi;
   uint64_t state;
@@ -888,8 +889,8 @@ __device__ __forceinline__ RowsCS rows_cs(const ReqRec &R, uint64_t g, uint32_t 
   W.u_hi = last ? shift + (uint32_t)(R.x + R.count - x0) : (uint32_t)kTileCS;
   if (split) part_of_rows(split, part, kTileCS, &W.u_lo, &W.u_hi);
   const uint64_t r0 = W.u_lo & ~63u;
-  W.later = x0 + r0 < shift;
-  W.state = x0 + r0 + 1 - shift;  // wraps below 0 only when `later`
+  W.later = g == 0 && r0 < shift;  // (x0 + r0 is 0 modulo 2^64 past the last tile, too)
+  W.state = x0 + r0 + 1 - shift;
   W.first = base - (int64_t)shift;
   return W;
 }
