@@ -203,7 +203,15 @@ phprng_status phprng_generate(phprng_ctx *ctx, const phprng_request *reqs, uint6
  * changed.  Every call on a device shares that device's scratch: calls that
  * overlap on one device (different streams, or different contexts) race;
  * calls ordered on one stream do not.  Arguments and results as for
- * phprng_generate; no kernel timing is recorded. */
+ * phprng_generate; no kernel timing is recorded.
+ *
+ * A call that a stream capture records carries its request list by value:
+ * every replay repeats that call, its positions and its output ranges,
+ * whatever the context has done since.  The context's positions advance once,
+ * when the call is captured.  A width-64 pseudorandom-skip instance continues
+ * the message that the device holds, so a replay after the first repeats its
+ * draws only if phprng_set_state puts the instance back to the captured
+ * position before it. */
 phprng_status phprng_generate_noalloc(phprng_ctx *ctx, const phprng_request *reqs, uint64_t nreq, uint32_t *out_c32,
                                       uint64_t *out_c64, double *out_r, uint64_t capacity, void *stream);
 

@@ -27,6 +27,7 @@
 
 #include <algorithm>
 #include <cstddef>
+#include <cstring>
 #include <mutex>
 #include <type_traits>
 
@@ -1044,6 +1045,22 @@ __global__ void __launch_bounds__(BLOCK) gen_persistent(GenArgs A) {
   stamp_end(args_again(), blockIdx.x * (BLOCK / 64) + wave, lane);
 }
 
+// Planned requests from the kernel's arguments to device memory, a 64-bit word
+// per thread and step.
+struct PutArgs {
+  ReqRec req[kPutReqs];
+  ReqRec *dst;
+  uint32_t count;  // of the requests in use
+};
+static_assert(sizeof(PutArgs) <= 4096, "kernel arguments stay within 4 KB");
+__global__ void __launch_bounds__(256) put_requests_kernel(PutArgs P) {
+  constexpr uint32_t kWords = sizeof(ReqRec) / sizeof(uint64_t);
+  using WordPtr = const __attribute__((address_space(4))) uint64_t *;
+  const WordPtr src = (WordPtr)((ArgPtr)__builtin_amdgcn_kernarg_segment_ptr() + offsetof(PutArgs, req));
+  uint64_t *const dst = reinterpret_cast<uint64_t *>(P.dst);
+  for (uint32_t i = threadIdx.x; i < P.count * kWords; i += 256) dst[i] = src[i];
+}
+
 // One grid per request: block b (one wave) takes chunk b of request `r`.
 template <int UNROLL, bool HAS64>
 __global__ void __launch_bounds__(64) gen_plain(GenArgs A, uint64_t r) {
@@ -1199,6 +1216,20 @@ hipError_t launch_persistent(const GenArgs &A, unsigned grid, int block, int unr
                              LaunchEvents ev) {
   clear_launch_error();
   return has64 ? launch_pb<true>(A, grid, block, unroll, st, ev) : launch_pb<false>(A, grid, block, unroll, st, ev);
+}
+
+hipError_t launch_put_requests(const ReqRec *reqs, uint64_t count, ReqRec *dst, hipStream_t st) {
+  clear_launch_error();
+  PutArgs P;
+  memset(&P, 0, sizeof P);
+  for (uint64_t i = 0; i < count; i += kPutReqs) {
+    P.count = (uint32_t)std::min<uint64_t>(count - i, kPutReqs);
+    P.dst = dst + i;
+    memcpy(P.req, reqs + i, P.count * sizeof(ReqRec));
+    const hipError_t e = launch_with({}, put_requests_kernel, dim3(1), dim3(256), st, P);
+    if (e != hipSuccess) return e;
+  }
+  return hipSuccess;
 }
 
 template <bool HAS64>

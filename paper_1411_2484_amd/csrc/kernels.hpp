@@ -60,6 +60,10 @@ hipError_t launch_skip_total64(uint64_t t, uint64_t count, uint64_t n, const Lan
 // grid: number of blocks; block: 64/128/256/512 threads; unroll: 1/2/4.
 hipError_t launch_persistent(const GenArgs &A, unsigned grid, int block, int unroll, bool has64, hipStream_t st,
                              LaunchEvents ev);
+// Writes `count` planned requests to dst from kernel arguments, so that a
+// captured call carries its requests with it (one launch per kPutReqs).
+constexpr uint32_t kPutReqs = 60;
+hipError_t launch_put_requests(const ReqRec *reqs, uint64_t count, ReqRec *dst, hipStream_t st);
 // One plain grid of `grid` one-wave blocks for request r.
 hipError_t launch_plain(const GenArgs &A, uint64_t r, unsigned grid, int unroll, bool has64, hipStream_t st,
                         LaunchEvents ev);

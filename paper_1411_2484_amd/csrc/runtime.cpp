@@ -112,6 +112,12 @@ struct TuneKey {
 std::mutex g_tune_mu;
 std::map<TuneKey, phprng_tuning> g_tune_cache;
 
+// Whether calls on `s` are being captured (or cannot be told from it).
+bool capturing(hipStream_t s) {
+  hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+  return hipStreamIsCapturing(s, &st) != hipSuccess || st != hipStreamCaptureStatusNone;
+}
+
 uint64_t add_u64_mod(uint64_t x, uint64_t y, uint64_t m) {  // (x + y) mod m, x, y < m
   const uint64_t s = x + y;
   return (s < x || s >= m) ? s - m : s;
@@ -435,14 +441,22 @@ struct phprng_ctx {
   // travel in the kernel arguments; up to kDirectRequests are read straight
   // from the pinned block (a few reads over the bus per chunk, no copy ahead
   // of them); larger batches are copied to device memory first, where the
-  // chunk searches run locally.
-  phprng_status stage(Slot &s, uint64_t nreq, hipStream_t st, const uint8_t **blk) {
+  // chunk searches run locally.  A captured call is replayed when the block
+  // holds another call's requests, so it carries its own (put_requests).
+  phprng_status stage(Slot &s, uint64_t nreq, hipStream_t st, bool captured, const uint8_t **blk) {
     *blk = s.h_blk_dev;
-    if (nreq <= kDirectRequests) return PHPRNG_OK;
-    const hipError_t e = hipMemcpyAsync(s.d_blk, s.h_blk, nreq * sizeof(ReqRec), hipMemcpyHostToDevice, st);
-    if (e != hipSuccess) return hip_fail(e, "request copy");
+    if (nreq <= (captured ? kInlineReqs : kDirectRequests)) return PHPRNG_OK;
     *blk = s.d_blk;
-    return PHPRNG_OK;
+    if (captured) return put_requests(s.h_blk, nreq, s.d_blk, st);
+    const hipError_t e = hipMemcpyAsync(s.d_blk, s.h_blk, nreq * sizeof(ReqRec), hipMemcpyHostToDevice, st);
+    return e == hipSuccess ? PHPRNG_OK : hip_fail(e, "request copy");
+  }
+
+  // The planned requests of a captured call to device memory, by value.
+  phprng_status put_requests(const uint8_t *stage, uint64_t nreq, uint8_t *dst, hipStream_t st) {
+    const hipError_t e =
+        launch_put_requests(reinterpret_cast<const ReqRec *>(stage), nreq, reinterpret_cast<ReqRec *>(dst), st);
+    return e == hipSuccess ? PHPRNG_OK : hip_fail(e, "captured requests");
   }
 
   phprng_status ensure_tiles(Slot &s, uint64_t tiles64) {
@@ -464,7 +478,8 @@ struct phprng_ctx {
   void commit_plan();
   GenArgs args(const Plan &P, const uint8_t *blk, const uint8_t *stage, WorkCtr *ctr, uint64_t *t64, uint64_t t64cap,
                uint32_t *c32, uint64_t *c64, double *r) const;
-  phprng_status launch(const Plan &P, GenArgs A, const ReqRec *hreq, hipStream_t s, int mode, Slot *slot);
+  phprng_status launch(const Plan &P, GenArgs A, const ReqRec *hreq, hipStream_t s, int mode, Slot *slot,
+                       bool captured);
   phprng_status sync_chain();
   phprng_status read_m64(uint32_t id, uint64_t *m);
   phprng_status write_m64(uint32_t id, uint64_t m);
@@ -810,13 +825,12 @@ GenArgs phprng_ctx::args(const Plan &P, const uint8_t *blk, const uint8_t *stage
 // generation kernel(s).  The batch's requests must already be where the
 // kernels read them.  `slot` (may be null: neither timing nor completion is
 // recorded) gets the call's time as set by timing_on and its completion event;
-// events ride on the kernels' launches, except that a capturing stream gets
-// plain launches and records.
-phprng_status phprng_ctx::launch(const Plan &P, GenArgs A, const ReqRec *hreq, hipStream_t s, int mode, Slot *slot) {
+// events ride on the kernels' launches, except that a captured call gets plain
+// launches and records.
+phprng_status phprng_ctx::launch(const Plan &P, GenArgs A, const ReqRec *hreq, hipStream_t s, int mode, Slot *slot,
+                                 bool captured) {
   hipError_t e;
-  hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
-  const bool plain_events =
-      !slot || hipStreamIsCapturing(s, &cap) != hipSuccess || cap != hipStreamCaptureStatusNone;
+  const bool plain_events = !slot || captured;
   const phprng_tuning &T = tuning[P.cls];
   // A batch with fewer chunks than the tuned grid has waves runs one wave per
   // chunk in one-wave blocks, so that its waves spread over every compute
@@ -1467,10 +1481,11 @@ extern "C" phprng_status phprng_generate(phprng_ctx *c, const phprng_request *re
   if (st != PHPRNG_OK) return st;
   if ((st = c->ensure_tiles(*slot, P.tiles64)) != PHPRNG_OK) return st;
   hipStream_t s = (hipStream_t)stream;
+  const bool captured = capturing(s);
   const uint8_t *blk = nullptr;
-  if ((st = c->stage(*slot, nreq, s, &blk)) != PHPRNG_OK) return st;
+  if ((st = c->stage(*slot, nreq, s, captured, &blk)) != PHPRNG_OK) return st;
   const GenArgs A = c->args(P, blk, slot->h_blk, slot->d_ctr, slot->d_t64, slot->cap64, out_c32, out_c64, out_r);
-  st = c->launch(P, A, reinterpret_cast<const ReqRec *>(slot->h_blk), s, mode, slot);
+  st = c->launch(P, A, reinterpret_cast<const ReqRec *>(slot->h_blk), s, mode, slot, captured);
   if (st != PHPRNG_OK) return st;
   slot->busy = true;
   c->last_timed = c->timing_on ? c->cur_slot : -1;
@@ -1502,7 +1517,10 @@ extern "C" phprng_status phprng_generate_noalloc(phprng_ctx *c, const phprng_req
     return c->fail(PHPRNG_E_RANGE, "allocation-free generation takes at most %llu width-64 tiles (%llu draws) per call",
                    (unsigned long long)kNoAllocMaxTiles64, (unsigned long long)(kNoAllocMaxTiles64 * kTile64));
   uint8_t *blk = c->scratch + kScratchReqOff;
-  if (nreq > kInlineReqs) {
+  const bool captured = nreq > kInlineReqs && capturing(s);
+  if (captured) {
+    if ((st = c->put_requests(c->h_noalloc, nreq, blk, s)) != PHPRNG_OK) return st;
+  } else if (nreq > kInlineReqs) {
     if ((e = hipMemcpyAsync(blk, c->h_noalloc, nreq * sizeof(ReqRec), hipMemcpyHostToDevice, s)) != hipSuccess)
       return c->hip_fail(e, "request copy");
     if ((e = hipEventRecord(c->noalloc_copied, s)) != hipSuccess) return c->hip_fail(e, "event");
@@ -1511,7 +1529,7 @@ extern "C" phprng_status phprng_generate_noalloc(phprng_ctx *c, const phprng_req
   const GenArgs A = c->args(P, blk, c->h_noalloc, reinterpret_cast<WorkCtr *>(c->scratch + kScratchCtrOff),
                             reinterpret_cast<uint64_t *>(c->scratch + kScratchTileOff), kNoAllocMaxTiles64, out_c32,
                             out_c64, out_r);
-  st = c->launch(P, A, reinterpret_cast<const ReqRec *>(c->h_noalloc), s, PHPRNG_MODE_PERSISTENT, nullptr);
+  st = c->launch(P, A, reinterpret_cast<const ReqRec *>(c->h_noalloc), s, PHPRNG_MODE_PERSISTENT, nullptr, captured);
   if (st != PHPRNG_OK) return st;
   c->commit_plan();
   return PHPRNG_OK;
@@ -1883,10 +1901,11 @@ extern "C" phprng_status phprng_graph_launch(phprng_graph *g, void *stream) {
   hipError_t e;
   // replays write the same outputs (and tile state): each follows the one before
   if (g->done && (e = hipStreamWaitEvent(s, g->done, 0)) != hipSuccess) return c->hip_fail(e, "graph wait");
+  const bool captured = capturing(s);
   const uint8_t *blk = nullptr;
-  if ((st = c->stage(*slot, nreq, s, &blk)) != PHPRNG_OK) return st;
+  if ((st = c->stage(*slot, nreq, s, captured, &blk)) != PHPRNG_OK) return st;
   const GenArgs A = c->args(P, blk, slot->h_blk, slot->d_ctr, g->d_t64, g->cap64, g->out_c32, g->out_c64, g->out_r);
-  st = c->launch(P, A, nullptr, s, PHPRNG_MODE_PERSISTENT, slot);
+  st = c->launch(P, A, nullptr, s, PHPRNG_MODE_PERSISTENT, slot, captured);
   if (st != PHPRNG_OK) return st;
   g->done = slot->ev1;
   slot->busy = true;
