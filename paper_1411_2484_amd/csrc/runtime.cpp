@@ -207,12 +207,14 @@ struct phprng_ctx {
     uint32_t stamps = 0;  // waves of the last call
     hipEvent_t ev0 = nullptr, ev1 = nullptr;
     bool busy = false;
+    bool captured = false;  // a captured call uses its buffers: replays may come at any time
     enum { kUntimed, kStamps, kEvents } timed = kUntimed;
   };
   static constexpr uint32_t kStampWaves = 8192;
   static constexpr int kSlots = 8;
   static constexpr uint64_t kMinSlotRequests = 8192;
   Slot slots[kSlots];
+  std::vector<void *> kept;  // device buffers that a captured call uses and that its slot outgrew
   int cur_slot = 0;
   int last_timed = -1;
   bool timing_on = true;  // time each call's kernels (phprng_set_timing)
@@ -261,6 +263,7 @@ struct phprng_ctx {
       if (s.ev0) (void)hipEventDestroy(s.ev0);
       if (s.ev1) (void)hipEventDestroy(s.ev1);
     }
+    for (void *p : kept) (void)hipFree(p);
   }
 
   phprng_status fail(phprng_status st, const char *fmt, ...) {
@@ -414,7 +417,7 @@ struct phprng_ctx {
       // room for typical batches from the start: growing frees buffers,
       // which waits for the device
       uint64_t cap = std::max<uint64_t>({nreq, 2 * s.cap, kMinSlotRequests});
-      if (s.d_blk) (void)hipFree(s.d_blk);
+      outgrown(s, s.d_blk);
       if (s.h_blk) (void)hipHostFree(s.h_blk);
       s.d_blk = nullptr;
       s.h_blk = nullptr;
@@ -435,6 +438,16 @@ struct phprng_ctx {
       s.cap = cap;
     }
     return PHPRNG_OK;
+  }
+
+  // A device buffer that a slot replaces: freed, or kept until the context is
+  // destroyed where the replays of a captured call still use it (each growth
+  // at least doubles, so no more is kept than the slots hold).
+  void outgrown(const Slot &s, void *buf) {
+    if (s.captured && buf)
+      kept.push_back(buf);
+    else
+      (void)hipFree(buf);
   }
 
   // Where the kernels read a slot's planned requests.  The smallest batches
@@ -462,7 +475,7 @@ struct phprng_ctx {
   phprng_status ensure_tiles(Slot &s, uint64_t tiles64) {
     if (tiles64 <= s.cap64) return PHPRNG_OK;
     const uint64_t cap = std::max<uint64_t>({tiles64, 2 * s.cap64, 1ull << 16});
-    if (s.d_t64) (void)hipFree(s.d_t64);
+    outgrown(s, s.d_t64);
     s.d_t64 = nullptr;
     s.cap64 = 0;
     hipError_t e = hipMalloc(&s.d_t64, 3 * cap * sizeof(uint64_t));
@@ -1110,6 +1123,7 @@ extern "C" phprng_status phprng_create(phprng_ctx **out, int device, uint64_t ma
     for (auto *v : {&c->touched, &c->seg_count, &c->seg_start, &c->req_pos, &c->order})
       v->reserve(kPlanReserve);
     c->seg_tab.reserve(kPlanReserve);
+    c->kept.reserve(2 * 64 * phprng_ctx::kSlots);  // a slot's two buffers double at most 64 times
     for (auto *v : {&c->cur_x, &c->cur_k, &c->req_x}) v->reserve(kPlanReserve);
   } catch (...) {
     return PHPRNG_E_NOMEM;
@@ -1482,6 +1496,7 @@ extern "C" phprng_status phprng_generate(phprng_ctx *c, const phprng_request *re
   if ((st = c->ensure_tiles(*slot, P.tiles64)) != PHPRNG_OK) return st;
   hipStream_t s = (hipStream_t)stream;
   const bool captured = capturing(s);
+  slot->captured = slot->captured || captured;
   const uint8_t *blk = nullptr;
   if ((st = c->stage(*slot, nreq, s, captured, &blk)) != PHPRNG_OK) return st;
   const GenArgs A = c->args(P, blk, slot->h_blk, slot->d_ctr, slot->d_t64, slot->cap64, out_c32, out_c64, out_r);
@@ -1902,6 +1917,7 @@ extern "C" phprng_status phprng_graph_launch(phprng_graph *g, void *stream) {
   // replays write the same outputs (and tile state): each follows the one before
   if (g->done && (e = hipStreamWaitEvent(s, g->done, 0)) != hipSuccess) return c->hip_fail(e, "graph wait");
   const bool captured = capturing(s);
+  slot->captured = slot->captured || captured;
   const uint8_t *blk = nullptr;
   if ((st = c->stage(*slot, nreq, s, captured, &blk)) != PHPRNG_OK) return st;
   const GenArgs A = c->args(P, blk, slot->h_blk, slot->d_ctr, g->d_t64, g->cap64, g->out_c32, g->out_c64, g->out_r);

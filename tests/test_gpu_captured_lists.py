@@ -116,3 +116,45 @@ def test_width64_replays_from_the_captured_states(ph, orc, k):
     torch.cuda.synchronize()
     del graph
     ctx.close()
+
+
+def test_replays_after_the_staging_slots_grew(ph, orc):
+    """Later calls with more requests and tiles than a staging slot holds give
+    the slots larger buffers; a captured call's replays keep theirs."""
+    import torch
+    k = 40
+    ctx = ph.Context(0, max_instances=400)
+    p, a = orc.lcg_params(64)
+    n, e, _ = orc.seed(64, SEED + 4, k, (9, 17))
+    s0 = np.arange(3, k + 3, dtype=np.uint64) * np.uint64(0x1234567890abc)
+    ids = ctx.add_instances(64, n, e, s0=s0)
+    starts = [ctx.get_state(int(i)) for i in ids]
+    counts = 100 + np.arange(k) * 300
+    reqs = _requests(ph, ids, counts)
+    c = torch.empty(int(counts.sum()), dtype=torch.int64, device="cuda")
+    want = [orc.generate(p, a, int(n[i]), int(e[i]), 0, int(s0[i]), int(counts[i]))[0] for i in range(k)]
+    many = ctx.seed_instances(32, SEED + 5, 300, (9, 17), 0, 0)
+    long = ctx.seed_instances(64, SEED + 6, 1, (9, 17), 0, 0)
+    big = _requests(ph, np.concatenate([many[np.arange(9000) % 300], long]), [3] * 9000 + [(1 << 26) + (1 << 20)])
+    room = torch.empty(27000 + (1 << 26) + (1 << 20), dtype=torch.float64, device="cuda")
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, capture_error_mode="relaxed"):
+        ctx.generate(reqs, None, c, None, stream=torch.cuda.current_stream())
+    for replay in range(3):
+        c.fill_(-1)
+        if replay:
+            for i, (m, s, _, pos) in zip(ids, starts):
+                ctx.set_state(int(i), m, s, pos)
+        torch.cuda.synchronize()
+        graph.replay()
+        torch.cuda.synchronize()
+        got = c.cpu().numpy().view(np.uint64)
+        for i in range(k):
+            compare_request(got, None, int(reqs["out_offset"][i]), int(counts[i]), want[i], None,
+                            "replay %d, request %d" % (replay, i))
+        for _ in range(9):
+            ctx.generate(big, None, None, room)
+        torch.cuda.synchronize()
+    del graph
+    ctx.close()
