@@ -136,9 +136,11 @@ struct phprng_graph {
   uint64_t *out_c64 = nullptr;
   double *out_r = nullptr;
   uint64_t *d_t64 = nullptr;  // width-64 tile state
-  // after the previous replay: the completion event of its staging slot (a
-  // slot that has been taken again since had waited for it)
-  hipEvent_t done = nullptr;
+  // The previous replay's staging slot and that slot's count of uses: while the
+  // count stands, the slot's completion event is the replay's; a slot that has
+  // been taken again since had waited for it.
+  int done_slot = -1;
+  uint64_t done_use = 0;
   std::vector<phprng_request> reqs;
   uint64_t nreq64 = 0;
   uint64_t cap64 = 0;  // width-64 tile-state entries: enough for either way of finding tile starts
@@ -207,6 +209,7 @@ struct phprng_ctx {
     uint32_t stamps = 0;  // waves of the last call
     hipEvent_t ev0 = nullptr, ev1 = nullptr;
     bool busy = false;
+    uint64_t uses = 0;  // times the slot was taken
     bool captured = false;  // a captured call uses its buffers: replays may come at any time
     enum { kUntimed, kStamps, kEvents } timed = kUntimed;
   };
@@ -395,6 +398,7 @@ struct phprng_ctx {
       hipError_t e = retire(s);
       if (e != hipSuccess) return hip_fail(e, "slot wait");
     }
+    ++s.uses;
     phprng_status st = prepare_slot(s, nreq);
     if (st != PHPRNG_OK) return st;
     *out = &s;
@@ -1915,7 +1919,9 @@ extern "C" phprng_status phprng_graph_launch(phprng_graph *g, void *stream) {
   hipStream_t s = (hipStream_t)stream;
   hipError_t e;
   // replays write the same outputs (and tile state): each follows the one before
-  if (g->done && (e = hipStreamWaitEvent(s, g->done, 0)) != hipSuccess) return c->hip_fail(e, "graph wait");
+  if (g->done_slot >= 0 && c->slots[g->done_slot].uses == g->done_use &&
+      (e = hipStreamWaitEvent(s, c->slots[g->done_slot].ev1, 0)) != hipSuccess)
+    return c->hip_fail(e, "graph wait");
   const bool captured = capturing(s);
   slot->captured = slot->captured || captured;
   const uint8_t *blk = nullptr;
@@ -1923,7 +1929,8 @@ extern "C" phprng_status phprng_graph_launch(phprng_graph *g, void *stream) {
   const GenArgs A = c->args(P, blk, slot->h_blk, slot->d_ctr, g->d_t64, g->cap64, g->out_c32, g->out_c64, g->out_r);
   st = c->launch(P, A, nullptr, s, PHPRNG_MODE_PERSISTENT, slot, captured);
   if (st != PHPRNG_OK) return st;
-  g->done = slot->ev1;
+  g->done_slot = c->cur_slot;
+  g->done_use = slot->uses;
   slot->busy = true;
   c->last_timed = c->timing_on ? c->cur_slot : -1;
   c->commit_plan();
