@@ -14,6 +14,7 @@
 
 #include "battery.hpp"
 #include "stats.hpp"
+#include "timed_chain.hpp"
 #include "phprng.h"
 
 using namespace phprng::bat;
@@ -106,14 +107,6 @@ double equal_cells_chi2(uint64_t total, unsigned __int128 sq, uint32_t cells) {
 
 constexpr uint32_t kReportMoments = kPartTests * kMomentSlices;
 
-// A timed launch, from the end a of the one before it to its own end b; b
-// belongs to the launch after it, unless this is the last of its call.
-struct Pending {
-  int cls;
-  hipEvent_t a, b;
-  bool last;
-};
-
 }  // namespace
 
 struct phprng_battery {
@@ -142,7 +135,7 @@ struct phprng_battery {
   unsigned long long *rep[PHPRNG_TEST_COUNT] = {};
   Twiddles tw{};
   double fourier_scale = 0;
-  std::vector<Pending> pending;
+  std::vector<Pending<hipEvent_t>> pending;
   std::vector<hipEvent_t> free_events;
   double ms[kKernelClasses] = {};
   uint64_t launches[kKernelClasses] = {};
@@ -178,25 +171,18 @@ hipEvent_t take_event(phprng_battery *b) {
   return e;
 }
 
-// Fold finished event pairs into the per-class totals; with `wait`, wait for all.
+// Fold finished launches into the per-class totals; with `wait`, wait for all.
 void resolve(phprng_battery *b, bool wait) {
-  size_t keep = 0;
-  for (size_t i = 0; i < b->pending.size(); ++i) {
-    Pending &p = b->pending[i];
-    bool done = wait ? hipEventSynchronize(p.b) == hipSuccess : hipEventQuery(p.b) == hipSuccess;
-    if (done) {
-      float t = 0;
-      if (hipEventElapsedTime(&t, p.a, p.b) == hipSuccess) {
+  take_finished(
+      b->pending,
+      [&](hipEvent_t e) { return (wait ? hipEventSynchronize(e) : hipEventQuery(e)) == hipSuccess; },
+      [&](const Pending<hipEvent_t> &p) {
+        float t = 0;
+        if (hipEventElapsedTime(&t, p.a, p.b) != hipSuccess) return;
         b->ms[p.cls] += t;
         b->launches[p.cls] += 1;
-      }
-      b->free_events.push_back(p.a);
-      if (p.last) b->free_events.push_back(p.b);
-    } else {
-      b->pending[keep++] = p;
-    }
-  }
-  b->pending.resize(keep);
+      },
+      [&](hipEvent_t e) { b->free_events.push_back(e); });
 }
 
 // The timed launches of one call: each completes its own event (a record
