@@ -546,7 +546,9 @@ phprng_status phprng_pattern_histogram(const phprng_pattern *pat, uint64_t *hist
  * pattern): *bytes receives what phprng_pattern_histogram_ws needs for `pat`;
  * workspace is device memory of at least that size, 256-byte aligned, free
  * for use on `stream` until the call returns.  PHPRNG_E_RANGE if it is too
- * small. */
+ * small.  (The Python binding borrows it from torch's allocator where the call
+ * runs on torch's current stream; the block then stays in torch's cache, where
+ * this library's own allocations cannot have it until torch gives it back.) */
 phprng_status phprng_pattern_workspace(const phprng_pattern *pat, uint64_t *bytes);
 phprng_status phprng_pattern_histogram_ws(const phprng_pattern *pat, uint64_t *hist, void *workspace, uint64_t bytes,
                                           void *stream);

@@ -209,6 +209,28 @@ def _check(st, ctx=None):
         raise PhprngError(st, msg)
 
 
+def _torch_gives_back():
+    """Has torch's allocator return the blocks that it keeps for reuse (the
+    library's memory does not come from there; a pattern histogram leaves up
+    to 2.8 GB of it).  False where it cannot: before torch's first use of the
+    device, and while a stream is being captured."""
+    import torch
+    if not torch.cuda.is_initialized() or torch.cuda.is_current_stream_capturing():
+        return False
+    torch.cuda.empty_cache()
+    return True
+
+
+def _allocating(fn, *args):
+    """Status of a call that allocates device memory: one that found none has
+    changed nothing and is made again once torch has given back what it does
+    not use."""
+    st = fn(*args)
+    if st == PHPRNG_E_NOMEM and _torch_gives_back():
+        st = fn(*args)
+    return st
+
+
 # ---- host-only helpers -----------------------------------------------------
 
 def phprng_skip_params(width):
@@ -301,7 +323,7 @@ class Context:
 
     def __init__(self, device=0, max_instances=1 << 16):
         h = _vp()
-        _check(lib().phprng_create(ctypes.byref(h), int(device), int(max_instances)))
+        _check(_allocating(lib().phprng_create, ctypes.byref(h), int(device), int(max_instances)))
         self._h = h
         self.device = device
 
@@ -343,8 +365,8 @@ class Context:
                 keep.append(a)
                 args.append(pa)
         ids = np.zeros(count, dtype=np.uint32)
-        self._chk(lib().phprng_add_instances(self._h, count, width, pn, pe, args[0], args[1], args[2],
-                                             ids.ctypes.data_as(_pu32)))
+        self._chk(_allocating(lib().phprng_add_instances, self._h, count, width, pn, pe, args[0], args[1], args[2],
+                              ids.ctypes.data_as(_pu32)))
         return ids
 
     def add_instances_skip(self, width, n, e, b, m0=None, k0=None):
@@ -361,8 +383,8 @@ class Context:
                 keep.append(a)
                 args.append(pa)
         ids = np.zeros(n.size, dtype=np.uint32)
-        self._chk(lib().phprng_add_instances_skip(self._h, n.size, width, pn, pe, pb, args[0], args[1],
-                                                  ids.ctypes.data_as(_pu32)))
+        self._chk(_allocating(lib().phprng_add_instances_skip, self._h, n.size, width, pn, pe, pb, args[0], args[1],
+                              ids.ctypes.data_as(_pu32)))
         return ids
 
     def get_schedule(self, inst):
@@ -373,8 +395,8 @@ class Context:
     def seed_instances(self, width, seed, count, e_set=(9, 17), k_lo=0, k_hi=0):
         es, pes = _u64arr(e_set)
         ids = np.zeros(count, dtype=np.uint32)
-        self._chk(lib().phprng_seed_instances(self._h, count, width, seed, pes, int(es.size), k_lo, k_hi,
-                                              ids.ctypes.data_as(_pu32)))
+        self._chk(_allocating(lib().phprng_seed_instances, self._h, count, width, seed, pes, int(es.size), k_lo, k_hi,
+                              ids.ctypes.data_as(_pu32)))
         return ids
 
     def instance_count(self):
@@ -387,8 +409,11 @@ class Context:
         float64) or None."""
         reqs = np.ascontiguousarray(requests, dtype=REQUEST_DTYPE)
         p32, p64, pr, cap = _outputs(out_c32, out_c64, out_r, self.device, capacity)
-        self._chk(lib().phprng_generate(self._h, reqs.ctypes.data, reqs.size, p32, p64, pr, cap,
-                                        _stream_handle(stream, self.device), int(mode)))
+        args = (self._h, reqs.ctypes.data, reqs.size, p32, p64, pr, cap, _stream_handle(stream, self.device), int(mode))
+        st = lib().phprng_generate(*args)
+        if st == PHPRNG_E_NOMEM and _torch_gives_back():  # a staging slot could not grow
+            st = lib().phprng_generate(*args)
+        self._chk(st)
 
     def generate_noalloc(self, requests, out_c32=None, out_c64=None, out_r=None, capacity=None, stream=None):
         """phprng_generate_noalloc: the persistent generation without any
@@ -462,7 +487,7 @@ class Context:
 
     def autotune(self, draws=1 << 26):
         t = phprng_tuning()
-        self._chk(lib().phprng_autotune(self._h, int(draws), ctypes.byref(t)))
+        self._chk(_allocating(lib().phprng_autotune, self._h, int(draws), ctypes.byref(t)))
         return dict(block_threads=t.block_threads, blocks_per_cu=t.blocks_per_cu,
                     tiles_per_chunk=t.tiles_per_chunk, unroll=t.unroll)
 
@@ -477,14 +502,18 @@ class Graph:
         reqs = np.ascontiguousarray(requests, dtype=REQUEST_DTYPE)
         p32, p64, pr, cap = _outputs(out_c32, out_c64, out_r, ctx.device, capacity)
         h = _vp()
-        _check(lib().phprng_graph_create(ctx.handle, reqs.ctypes.data, reqs.size, p32, p64, pr, cap,
-                                         _stream_handle(stream, ctx.device), ctypes.byref(h)),
+        _check(_allocating(lib().phprng_graph_create, ctx.handle, reqs.ctypes.data, reqs.size, p32, p64, pr, cap,
+                           _stream_handle(stream, ctx.device), ctypes.byref(h)),
                ctx.handle)
         self._h = h
         self._ctx = ctx
 
     def launch(self, stream=None):
-        _check(lib().phprng_graph_launch(self._h, _stream_handle(stream, self._ctx.device)), self._ctx.handle)
+        raw = _stream_handle(stream, self._ctx.device)
+        st = lib().phprng_graph_launch(self._h, raw)
+        if st == PHPRNG_E_NOMEM and _torch_gives_back():  # a staging slot could not grow
+            st = lib().phprng_graph_launch(self._h, raw)
+        _check(st, self._ctx.handle)
 
     def close(self):
         if getattr(self, "_h", None):
@@ -507,7 +536,7 @@ class Server:
         cfg = phprng_server_config(int(arena_doubles), int(streams), int(max_inflight), int(max_batch_requests), 0,
                                    int(max_batch_draws))
         h = _vp()
-        _check(lib().phprng_server_create(ctx.handle, ctypes.byref(cfg), ctypes.byref(h)), ctx.handle)
+        _check(_allocating(lib().phprng_server_create, ctx.handle, ctypes.byref(cfg), ctypes.byref(h)), ctx.handle)
         self._h = h
         self._ctx = ctx
 
@@ -604,7 +633,7 @@ class Battery:
 
     def __init__(self, device=0):
         h = _vp()
-        _check(lib().phprng_battery_create(ctypes.byref(h), int(device)))
+        _check(_allocating(lib().phprng_battery_create, ctypes.byref(h), int(device)))
         self._h = h
 
     def _chk(self, st):
@@ -686,7 +715,7 @@ def pattern_histogram(spec, hist, stream=None):
     if ws is not None:
         _check(lib().phprng_pattern_histogram_ws(ctypes.byref(spec), ph, ws.data_ptr(), ws.numel(), st))
     else:
-        _check(lib().phprng_pattern_histogram(ctypes.byref(spec), ph, st))
+        _check(_allocating(lib().phprng_pattern_histogram, ctypes.byref(spec), ph, st))
 
 
 def _torch_scratch(spec, hist, raw_stream):
@@ -713,6 +742,6 @@ def pattern_chi2(spec, hist, stream=None):
     """(chi2, p_value, total) of a pattern histogram."""
     c, p, t = ctypes.c_double(), ctypes.c_double(), _u64()
     ph = _device_array(hist, _C64_DTYPES, None, "hist")
-    _check(lib().phprng_pattern_chi2(ctypes.byref(spec), ph, ctypes.byref(c), ctypes.byref(p),
-                                     ctypes.byref(t), _stream_handle(stream)))
+    _check(_allocating(lib().phprng_pattern_chi2, ctypes.byref(spec), ph, ctypes.byref(c), ctypes.byref(p),
+                       ctypes.byref(t), _stream_handle(stream)))
     return c.value, p.value, t.value

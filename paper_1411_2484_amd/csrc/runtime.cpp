@@ -279,7 +279,7 @@ struct phprng_ctx {
     return st;
   }
   phprng_status hip_fail(hipError_t e, const char *what) {
-    return fail(PHPRNG_E_DEVICE, "%s: %s", what, hipGetErrorString(e));
+    return fail(e == hipErrorOutOfMemory ? PHPRNG_E_NOMEM : PHPRNG_E_DEVICE, "%s: %s", what, hipGetErrorString(e));
   }
 
   // U(r) = sum_{j=1}^{r} (a^j mod p) and a^r mod p (width 32), from the table
