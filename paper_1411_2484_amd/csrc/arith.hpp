@@ -196,17 +196,6 @@ __device__ __forceinline__ W128 mul63w(uint64_t x, uint64_t y) {
   return {(mid << 32) | (uint32_t)p00, (uint64_t)x1 * y1 + (mid >> 32)};
 }
 
-// x^2 for x < 2^63: the cross term is one product with 2 x1 < 2^32.
-__device__ __forceinline__ W128 sqr63w(uint64_t x) {
-  const uint32_t x0 = (uint32_t)x, x1 = (uint32_t)(x >> 32);
-  const uint64_t p00 = (uint64_t)x0 * x0;
-  // 2 x1 as one shift (the compiler otherwise forms it from both words)
-  uint32_t x1d;
-  asm("v_lshlrev_b32 %0, 1, %1" : "=v"(x1d) : "v"(x1));
-  const uint64_t mid = (uint64_t)x0 * x1d + (p00 >> 32);
-  return {(mid << 32) | (uint32_t)p00, (uint64_t)x1 * x1 + (mid >> 32)};
-}
-
 // High word of q n for n < 2^63: with h = hi(q0 n0), a = q1 n0 + h < 2^64
 // and b = q0 n1 + lo(a) < 2^64, the high word is q1 n1 + hi(a) + hi(b).
 __device__ __forceinline__ uint64_t mulhi_n63(uint64_t q, uint64_t n) {
@@ -231,11 +220,6 @@ __device__ __forceinline__ uint64_t redc64(W128 v, uint64_t n, uint64_t ninv) {
 // x y 2^{-64} mod n for x, y < n < 2^63.
 __device__ __forceinline__ uint64_t mont64(uint64_t x, uint64_t y, uint64_t n, uint64_t ninv) {
   return redc64(mul63w(x, y), n, ninv);
-}
-
-// x^2 2^{-64} mod n for x < n < 2^63.
-__device__ __forceinline__ uint64_t msqr64(uint64_t x, uint64_t n, uint64_t ninv) {
-  return redc64(sqr63w(x), n, ninv);
 }
 
 // redc64 for a modulus that is the same in every lane of the wave (n and
@@ -633,12 +617,6 @@ __device__ __forceinline__ uint32_t uniform_u32(uint32_t v) { return __builtin_a
 __device__ __forceinline__ uint64_t uniform_u64(uint64_t v) {
   uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)v);
   uint32_t hi = __builtin_amdgcn_readfirstlane((uint32_t)(v >> 32));
-  return ((uint64_t)hi << 32) | lo;
-}
-
-__device__ __forceinline__ uint64_t shfl_up_u64(uint64_t v, int d) {
-  uint32_t lo = __shfl_up((int)(uint32_t)v, d, 64);
-  uint32_t hi = __shfl_up((int)(uint32_t)(v >> 32), d, 64);
   return ((uint64_t)hi << 32) | lo;
 }
 

@@ -22,12 +22,6 @@ __device__ __forceinline__ uint32_t bin_of(double x, uint32_t b) {
   return u < b ? u : b - 1;
 }
 
-__device__ __forceinline__ uint64_t shfl_xor_u64(uint64_t v, int mask) {
-  const uint32_t lo = __shfl_xor((int)(uint32_t)v, mask, 64);
-  const uint32_t hi = __shfl_xor((int)(uint32_t)(v >> 32), mask, 64);
-  return ((uint64_t)hi << 32) | lo;
-}
-
 // Poker hand category from the number of equal pairs among the five digits:
 // 0 all different, 1 one pair, 2 two pairs, 3 three of a kind, 4 full house,
 // 6 four of a kind, 10 five of a kind.
@@ -555,7 +549,7 @@ __global__ __launch_bounds__(kRep) void fold_kernel(SmallHists S) {
   unsigned long long v = *src;
   *src = 0;
 #pragma unroll
-  for (int d = 1; d < 64; d <<= 1) v += shfl_xor_u64(v, d);
+  for (int d = 1; d < 64; d <<= 1) v += dev::shfl_xor_u64(v, d);
   if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = v;
   __syncthreads();
   if (threadIdx.x == 0) {
@@ -594,8 +588,8 @@ __global__ __launch_bounds__(256) void moments_kernel(MomentJobs J, Moments *out
   }
 #pragma unroll
   for (int d = 1; d < 64; d <<= 1) {
-    sum += shfl_xor_u64(sum, d);
-    const uint64_t l = shfl_xor_u64((uint64_t)sq, d), h = shfl_xor_u64((uint64_t)(sq >> 64), d);
+    sum += dev::shfl_xor_u64(sum, d);
+    const uint64_t l = dev::shfl_xor_u64((uint64_t)sq, d), h = dev::shfl_xor_u64((uint64_t)(sq >> 64), d);
     sq += ((unsigned __int128)h << 64) | l;
   }
   __shared__ Moments part[4];
