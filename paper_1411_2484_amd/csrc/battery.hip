@@ -681,10 +681,10 @@ hipError_t launch_fft_pass1(const double *r, uint64_t nblocks, double2 *y, Twidd
 hipError_t launch_fft_pass2(const double2 *y, uint64_t nblocks, unsigned long long *fourier, double *coef,
                             Twiddles tw, double scale, hipStream_t st, LaunchEvents ev) {
   clear_launch_error();
-  const hipError_t e = launch_with({ev.start, nullptr}, fft_pass2_pairs_kernel, dim3((unsigned)(nblocks * kP2PairRows)),
+  const hipError_t e = launch_with({}, fft_pass2_pairs_kernel, dim3((unsigned)(nblocks * kP2PairRows)),
                                    dim3(128), st, y, fourier, coef, tw, scale);
   if (e != hipSuccess) return e;
-  return launch_with({nullptr, ev.stop}, fft_pass2_self_kernel, dim3((unsigned)(nblocks * 2)), dim3(128), st, y,
+  return launch_with(ev, fft_pass2_self_kernel, dim3((unsigned)(nblocks * 2)), dim3(128), st, y,
                      fourier, coef, tw, scale);
 }
 

@@ -1,4 +1,4 @@
-// Kernel launches that complete events by themselves.
+// Kernel launches that complete an event by themselves.
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -6,20 +6,21 @@
 
 namespace phprng {
 
-// Events that a launch completes by itself: `start` when its kernel begins,
-// `stop` when it ends (either may be null).  They ride on the kernel's own
-// packet; an event recorded beside it costs the host 5 us more (launch and
-// stop event 4.7 against 9.5 us, with a start event 10.2 against 14.2 us) and
-// leaves the GPU idle for 5 us.
+// The event that a launch completes by itself when its kernel ends (may be
+// null).  It rides on the kernel's own packet; an event recorded beside it costs
+// the host 5 us more (launch and stop event 4.7 against 9.5 us) and leaves the
+// GPU idle for 5 us.  A start event is better recorded beside the first launch
+// than put on it: plain calls of 1,000 draws in a row, timed by both events, take
+// 10 to 12 us each, and 17 to 21 us with the start on the launch.
 struct LaunchEvents {
-  hipEvent_t start = nullptr, stop = nullptr;
+  hipEvent_t stop = nullptr;
 };
 
-// A launch that completes the given events, or a plain one without any.
+// A launch that completes the given event, or a plain one without it.
 template <class K, class... Args>
 inline hipError_t launch_with(LaunchEvents ev, K kernel, dim3 grid, dim3 block, hipStream_t st, Args... args) {
-  if (ev.start || ev.stop)
-    hipExtLaunchKernelGGL(kernel, grid, block, 0, st, ev.start, ev.stop, 0, args...);
+  if (ev.stop)
+    hipExtLaunchKernelGGL(kernel, grid, block, 0, st, nullptr, ev.stop, 0, args...);
   else
     hipLaunchKernelGGL(kernel, grid, block, 0, st, args...);
   return hipGetLastError();

@@ -88,9 +88,9 @@ __global__ __launch_bounds__(256) void add_kernel(PartSet P) {
 hipError_t launch_count(const PartSet &P, hipStream_t st, LaunchEvents ev) {
   clear_launch_error();
   if (P.nslice == 1) return launch_with(ev, count_kernel<true>, dim3(P.npart), dim3(1024), st, P);
-  const hipError_t e = launch_with({ev.start, nullptr}, count_kernel<false>, dim3(P.npart * P.nslice), dim3(1024), st, P);
+  const hipError_t e = launch_with({}, count_kernel<false>, dim3(P.npart * P.nslice), dim3(1024), st, P);
   if (e != hipSuccess) return e;
-  return launch_with({nullptr, ev.stop}, add_kernel, dim3(P.npart * (kPartCells / 256)), dim3(256), st, P);
+  return launch_with(ev, add_kernel, dim3(P.npart * (kPartCells / 256)), dim3(256), st, P);
 }
 
 }  // namespace ph

@@ -842,8 +842,8 @@ GenArgs phprng_ctx::args(const Plan &P, const uint8_t *blk, const uint8_t *stage
 // generation kernel(s).  The batch's requests must already be where the
 // kernels read them.  `slot` (may be null: neither timing nor completion is
 // recorded) gets the call's time as set by timing_on and its completion event;
-// events ride on the kernels' launches, except that a captured call gets plain
-// launches and records.
+// events that end a kernel ride on its launch, except that a captured call gets
+// plain launches and records.
 phprng_status phprng_ctx::launch(const Plan &P, GenArgs A, const ReqRec *hreq, hipStream_t s, int mode, Slot *slot,
                                  bool captured) {
   hipError_t e;
@@ -861,11 +861,10 @@ phprng_status phprng_ctx::launch(const Plan &P, GenArgs A, const ReqRec *hreq, h
   } else {
     for (uint64_t p = 0; p < P.nreq; ++p) gens += hreq[p].nchunks != 0;
   }
-  hipEvent_t start = nullptr;
   const hipEvent_t stop = slot ? slot->ev1 : nullptr;
   if (slot) {
-    // Timing by the kernels themselves (a start event beside or on a launch
-    // costs about 5 us of every call), by events where that does not apply.
+    // Timing by the kernels themselves (a start event costs about 5 us of
+    // every call), by events where that does not apply.
     const uint64_t waves = (uint64_t)grid * (block / 64);
     slot->timed = Slot::kUntimed;
     if (timing_on && mode == PHPRNG_MODE_PERSISTENT && gens && waves <= kStampWaves && !plain_events) {
@@ -875,20 +874,11 @@ phprng_status phprng_ctx::launch(const Plan &P, GenArgs A, const ReqRec *hreq, h
       A.stamp_start = 1;
     } else if (timing_on) {
       slot->timed = Slot::kEvents;
-      start = slot->ev0;
+      if ((e = hipEventRecord(slot->ev0, s)) != hipSuccess) return hip_fail(e, "event");
     }
   }
-  if (plain_events && start && (e = hipEventRecord(start, s)) != hipSuccess) return hip_fail(e, "event");
-  // The launches: `start` and the start stamp go to the first, an event to
-  // complete to the one that is given it.
-  LaunchEvents next;
-  if (!plain_events) next.start = start;
-  auto ev = [&](hipEvent_t x) {
-    LaunchEvents v = next;
-    v.stop = plain_events ? nullptr : x;
-    next.start = nullptr;
-    return v;
-  };
+  // the event that a launch is to complete
+  auto ev = [&](hipEvent_t x) { return LaunchEvents{plain_events ? nullptr : x}; };
   if (P.nreq64 > 0) {
     if (P.any_reduce && P.units64 > 0) {
       if ((e = launch_tiles64_reduce(A, P.units64, (unsigned)num_cus * 8, s, ev(nullptr))) != hipSuccess)
@@ -910,8 +900,7 @@ phprng_status phprng_ctx::launch(const Plan &P, GenArgs A, const ReqRec *hreq, h
     chain_pending = true;
   }
   if (gens == 0) {
-    // no generation kernel: the events beside what ran
-    if (next.start && (e = hipEventRecord(next.start, s)) != hipSuccess) return hip_fail(e, "event");
+    // no generation kernel: the event beside what ran
     if (stop && (e = hipEventRecord(stop, s)) != hipSuccess) return hip_fail(e, "event");
     return PHPRNG_OK;
   }
