@@ -733,9 +733,10 @@ def _torch_scratch(spec, hist, raw_stream):
     if lib().phprng_pattern_workspace(ctypes.byref(spec), ctypes.byref(n)) != PHPRNG_OK:
         return None  # the call itself reports what is wrong with the shape
     try:
-        return torch.empty(n.value, dtype=torch.uint8, device=hist.device)
+        ws = torch.empty(n.value, dtype=torch.uint8, device=hist.device)
     except torch.cuda.OutOfMemoryError:
         return None
+    return ws if ws.data_ptr() % 256 == 0 else None  # torch's own allocator aligns more, another one may not
 
 
 def pattern_chi2(spec, hist, stream=None):

@@ -57,3 +57,14 @@ def test_made_again_after_torch_gave_back(monkeypatch, call, fails, initialized,
     else:
         CALLS[call]()
     assert given == ([1] if made == 2 else []) and len(set(short.log)) == 1 and short.calls == made
+
+
+@pytest.mark.parametrize("address,taken", [(0x10000, True), (0x10100, True), (0x10080, False), (0x10008, False)])
+def test_scratch_at_an_address_that_the_library_refuses_is_not_taken(monkeypatch, address, taken):
+    hist, block = FakeTensor(torch.int64), FakeTensor(torch.uint8)
+    block.data_ptr = lambda: address
+    monkeypatch.setattr(torch.cuda, "current_device", lambda: 0)
+    monkeypatch.setattr(ph, "_stream_handle", lambda stream, device=None: 0)
+    monkeypatch.setattr(torch, "empty", lambda *a, **k: block)
+    got = ph._torch_scratch(ph.pattern_spec(4294967087, 9, 0, 1, 2, 4), hist, 0)
+    assert got is (block if taken else None)
