@@ -478,8 +478,9 @@ phprng_status phprng_battery_reset(phprng_battery *battery, void *stream);
  * stream completes.  Calls on one battery must be ordered on one stream. */
 phprng_status phprng_battery_accumulate(phprng_battery *battery, const double *r, uint64_t count, void *stream);
 
-/* Reduce the histograms to chi^2 on the device and fill out[PHPRNG_TEST_COUNT]
- * (host array); waits for `stream`. */
+/* Reduce the histograms on the device (exact sums of the counts and of their
+ * squares), form chi^2 from them and fill out[PHPRNG_TEST_COUNT] (host array);
+ * waits for `stream`. */
 phprng_status phprng_battery_report(phprng_battery *battery, phprng_test_result *out, void *stream);
 
 /* Copy the histogram of `test` (host array of `capacity` counts) and/or its

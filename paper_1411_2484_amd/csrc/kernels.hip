@@ -46,8 +46,9 @@ static_assert((1ull << kTileShift32) == kTilesPerPeriod32, "tile shift");
 // row of the tile before it; the width-32 block, or the larger width-64 one.
 constexpr int kLdsWords32 = (65 * kRow32 + 1) / 2;  // 1073
 constexpr int kLdsWords64 = 65 * kRow64;            // 1105
-// Draws by which the rows of a tile are shifted back so that they start at
-// whole 128-byte lines of the outputs (32 4-byte or 16 8-byte elements).
+// The rows of a tile are shifted back to output elements that are multiples of
+// these, so that they start at whole 128-byte lines of an array that starts at
+// one (32 4-byte or 16 8-byte elements).
 constexpr uint32_t kAlign32 = 32, kAlign64 = 16;
 static_assert(kAlign32 <= kRun32 && kAlign64 <= kRun64, "one row of the tile before holds the shifted draws");
 
@@ -582,8 +583,9 @@ __device__ __forceinline__ void put_draw(const Draw<C> &d, C *c, double *r) {
 // Pass C works on rows of 64 consecutive draws, one per lane.  The rows of a
 // tile are shifted back by `shift` draws, so that row r holds the draws
 // t = 64 r + lane - shift and its stores cover whole 128-byte lines whatever
-// the request's output offset (rows that straddle lines cost 6% of the store
-// rate for uniforms and 10% with ciphertexts).  u = t + shift counts from the
+// the request's output offset, in arrays that start at a line (rows that
+// straddle lines cost 6% of the store rate for uniforms and 10% with
+// ciphertexts).  u = t + shift counts from the
 // first row; the pass writes u in [u_lo, u_hi): whole rows in groups of UNROLL
 // (all messages, then all encryptions, then all stores of a group), the rows
 // at either end masked one at a time.  get(k) gives this lane's message of the
